@@ -66,7 +66,7 @@ static __global__ __launch_bounds__(kConBlock) void k_con_dot(
 }
 
 // What the finishing kernel does with d = (C x)[k]:
-//   CON_ADD   : y_c[k] += d
+//   CON_ADD   : y_c[k] += d     (yin: the old y_c, its own array or yc itself)
 //   CON_RESID : y_c[k] = b_c[k] - d
 //   CON_LSQR  : y_c[k] = xs d - ys y_c[k], (xs, ys) = (sv, alpha su) for the forward operator
 //               A D or (su, beta sv) for the transposed one (TRANS); partial sum of y_c^2
@@ -77,7 +77,7 @@ enum { CON_ADD = 0, CON_RESID = 1, CON_LSQR = 2 };
 
 template <int MODE, bool TRANS = false, bool PENDING = false>
 static __global__ __launch_bounds__(kConBlock) void k_con_fin(
-    int64_t n_con, double* __restrict__ acc, double* __restrict__ yc,
+    int64_t n_con, double* __restrict__ acc, const double* yin, double* yc,
     const double* __restrict__ bc, const LsqrState* __restrict__ st, double* __restrict__ part,
     int stride, double* __restrict__ wc, double* __restrict__ zc,
     const int32_t* __restrict__ gate) {
@@ -96,11 +96,11 @@ static __global__ __launch_bounds__(kConBlock) void k_con_fin(
         const double d = acc[k];
         acc[k] = 0.0;
         if (MODE == CON_ADD) {
-            yc[k] += d;
+            yc[k] = yin[k] + d;
         } else if (MODE == CON_RESID) {
             yc[k] = bc[k] - d;
         } else {
-            const double yo = yc[k];
+            const double yo = yin[k];
             if (PENDING && pending) {
                 const double wo = wc[k];
                 const double zn = fma(f1, wo, zc[k]);

@@ -12,6 +12,7 @@
 #include <cstddef>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <string>
 #include <vector>
 
@@ -89,12 +90,12 @@ int grid_for(int64_t items, int per_block, int max_blocks) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(b, max_blocks));
 }
 
-// Arrays of 1 GiB and more are asked for as physically contiguous memory first, plain
-// hipMalloc when that fails.  Measured: with ordinary allocations the fused row pass over
-// tens of GB of row tiles ran up to 10% slower in a process started right after another one
-// had used and freed most of the device memory, and at full speed with contiguous ones.
-hipError_t device_alloc(void** p, size_t bytes) {
-    if (bytes >= (size_t(1) << 30)) {
+// Arrays of `contiguous_from` bytes and more are asked for as physically contiguous memory
+// first, plain hipMalloc when that fails.  From 1 GiB on by default: with ordinary allocations
+// the fused row pass over tens of GB of row tiles ran up to 10% slower in a process started
+// right after another one had used and freed most of the device memory.
+hipError_t device_alloc(void** p, size_t bytes, size_t contiguous_from) {
+    if (bytes >= contiguous_from) {
         if (hipExtMallocWithFlags(p, bytes, hipDeviceMallocContiguous) == hipSuccess)
             return hipSuccess;
         (void)hipGetLastError();
@@ -122,6 +123,8 @@ namespace {
 struct LsqrWork {
     int64_t rows = 0, cols = 0;
     double *u = nullptr, *v = nullptr, *w = nullptr, *z = nullptr;
+    double* u2 = nullptr;   // forward recurrences: u~ alternates between u and u2
+    void *slab_u = nullptr, *slab_v = nullptr;  // allocations behind u, u2 and v, w, z, var
     double* var = nullptr;  // [cols] variance estimate (solves that return it)
     hipGraphExec_t graph = nullptr;
     int graph_iters = 0;
@@ -129,16 +132,26 @@ struct LsqrWork {
 
 }  // namespace
 
+// Launch shape of a row pass (k_aprod12, k_aprod12_reg, k_aprod1, k_aprod2_star).
+struct RowPlan {
+    bool reg = false;   // register form (fused pass)
+    bool ldsi = true;   // instrumental unknowns / sums in LDS
+    int grid = 1, tw = 1, nsb = 0;
+    size_t lds = 0;
+};
+
 struct gsr_handle {
     int device = 0;
     int n_cu = 256;
     Geo g;
     const double* vals = nullptr;
     const int32_t *star = nullptr, *att = nullptr, *instr = nullptr;
-    float* vals32 = nullptr;
+    bool has_f32 = false;  // binary32 copies built
+    void* slab = nullptr;  // allocation behind p64, s, xt (and p32, dx)
     double *p64 = nullptr, *p32 = nullptr;
     double* s = nullptr;       // [n] aprod 2 accumulator (kept zero between uses)
     double* xt = nullptr;      // [n] operand of the next aprod 1 (p o v)
+    double* xa = nullptr;      // [3 T] its attitude part knot by knot (AttCopy)
     // attitude coefficients in (bucket and die, row slice, attitude start) order (built at
     // setup): row of each entry, its column offset in the bucket, group boundaries
     int32_t *rowT = nullptr, *tT = nullptr;
@@ -147,18 +160,16 @@ struct gsr_handle {
     int64_t* att_seg = nullptr;   // [att_ng + 1]
     double* att_part = nullptr;   // [att_ng][kAxes][att_lw] group sums of the attitude pass
     int att_ng = 1, att_w = 1, att_lw = kParAxis;
-    double* part_ig = nullptr;  // [G2s][n_instr + 1] block sums of the star-ordered pass
+    double* part_ig = nullptr;  // [blocks][n_instr + 1] block sums of the star-ordered pass
     double *partA = nullptr, *partB = nullptr;
     LsqrState* st = nullptr;   // device scalars
     LsqrState* st_host = nullptr;  // pinned mirror
-    int G1 = 1, G2s = 1, Gn = 1, Gm = 1;
-    int chunk1 = 16, chunk2s = 16;
-    int lds1 = 0, lds2 = 0;           // instrumental columns staged / privatized in LDS
-    size_t lds1_bytes = 0, lds2_bytes = 0;
-    // fused row pass (aprod 1 + star-ordered part of aprod 2), used when n_instr fits LDS
-    int fused = 0, G12 = 1, chunk12 = 16;
+    int Gn = 1, Gm = 1;
+    // launch shapes: aprod 1 and star-ordered aprod 2 by themselves, the fused row pass (used
+    // when its instrumental columns fit in LDS)
+    RowPlan dot, star_pass, row12;
+    int fused = 0;
     int allow_empty = 0;           // setup option: all-zero columns accepted
-    size_t lds12_bytes = 0;
     // row tiles of the fused pass (coefficients per precision, packed indices)
     int64_t ntiles = 0;
     double* tiles64 = nullptr;
@@ -190,12 +201,12 @@ struct gsr_handle {
 namespace {
 
 constexpr int kVecBlocksMax = 2048;
-constexpr int kGraphIters = 16;
+constexpr int kGraphIters = 16;  // even: u~ is back in its first array after a graph
 
 template <typename T>
-gsr_status dalloc(T** p, size_t count) {
+gsr_status dalloc(T** p, size_t count, size_t contiguous_from = kContiguous) {
     if (count == 0) count = 1;
-    hipError_t e = device_alloc((void**)p, count * sizeof(T));
+    hipError_t e = device_alloc((void**)p, count * sizeof(T), contiguous_from);
     if (e != hipSuccess) {
         *p = nullptr;
         return fail(GSR_E_NOMEM, "hipMalloc of %zu bytes failed: %s", count * sizeof(T),
@@ -208,26 +219,42 @@ void dfree(void* p) {
     if (p) (void)hipFree(p);
 }
 
+// Vectors of n doubles each, in one allocation.  The vectors that the row pass and the attitude
+// pass gather from and scatter to (u~, s, xt) are asked for as contiguous memory from 16 MiB
+// on: those passes' times depend on how the pages lie (2e7 rows: 0.98 -> 0.93 ms and 0.51 ->
+// 0.49 ms).  Not v, w, z, which the vector step streams side by side with s, xt and p: all of
+// them contiguous, it took 114 us instead of 72.
+constexpr size_t kGathered = size_t(16) << 20;
+
+gsr_status dalloc_vecs(void** slab, std::initializer_list<double**> vecs, int64_t n,
+                       size_t contiguous_from) {
+    const size_t step = ((size_t)std::max<int64_t>(n, 1) * sizeof(double) + 255) / 256 * 256;
+    char* base = nullptr;
+    GSR_TRY(dalloc(&base, step * vecs.size(), contiguous_from));
+    *slab = base;
+    for (double** v : vecs) {
+        *v = reinterpret_cast<double*>(base);
+        base += step;
+    }
+    return GSR_OK;
+}
+
 void free_work(LsqrWork& w) {
     if (w.graph) (void)hipGraphExecDestroy(w.graph);
-    dfree(w.u);
-    dfree(w.v);
-    dfree(w.w);
-    dfree(w.z);
-    dfree(w.var);
+    dfree(w.slab_u);
+    dfree(w.slab_v);
     w = LsqrWork();
 }
 
-gsr_status ensure_work(LsqrWork& w, int64_t rows, int64_t cols, bool with_var = false) {
-    if (w.u) return GSR_OK;
+gsr_status ensure_work(LsqrWork& w, int64_t rows, int64_t cols, bool with_var = false,
+                       bool alternating = true) {
+    if (w.slab_v) return GSR_OK;
     w.rows = rows;
     w.cols = cols;
-    GSR_TRY(dalloc(&w.u, rows));
-    GSR_TRY(dalloc(&w.v, cols));
-    GSR_TRY(dalloc(&w.w, cols));
-    GSR_TRY(dalloc(&w.z, cols));
-    if (with_var) GSR_TRY(dalloc(&w.var, cols));
-    return GSR_OK;
+    GSR_TRY(alternating ? dalloc_vecs(&w.slab_u, {&w.u, &w.u2}, rows, kGathered)
+                        : dalloc_vecs(&w.slab_u, {&w.u}, rows, kContiguous));
+    return with_var ? dalloc_vecs(&w.slab_v, {&w.v, &w.w, &w.z, &w.var}, cols, kContiguous)
+                    : dalloc_vecs(&w.slab_v, {&w.v, &w.w, &w.z}, cols, kContiguous);
 }
 
 hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
@@ -237,27 +264,103 @@ void fill(double* v, int64_t n, double val, hipStream_t s) {
                        n, val);
 }
 
+// ---- launch shapes of the row passes --------------------------------------------------
+
+// Rows are dealt to the blocks (one per compute unit) in rounds of tw wave steps per wave;
+// the fewest rounds that the cap on tw allows, of equal length.
+void deal_rounds(const Geo& g, int n_cu, int64_t cap, RowPlan* r) {
+    const int64_t ntiles = std::max<int64_t>(1, (g.m + kStepRows - 1) / kStepRows);
+    const int64_t all = (int64_t)kRowWaves * n_cu;
+    const int64_t rounds = (ntiles + all * cap - 1) / (all * cap);
+    r->tw = (int)std::max<int64_t>(1, (ntiles + all * rounds - 1) / (all * rounds));
+    r->grid = (int)std::min<int64_t>(n_cu, (ntiles + (int64_t)kRowWaves * r->tw - 1) /
+                                               ((int64_t)kRowWaves * r->tw));
+}
+
+// `fixed` doubles of LDS, then (with_u) the round's u~ or sums and (with_stars) the star slots,
+// a quarter more than the mean number of stars in a round (stars past the slots take atomics).
+// tw = 0 when not even one wave step fits.
+RowPlan plan_rows(const Geo& g, int n_cu, int64_t fixed, bool with_u, bool with_stars) {
+    RowPlan r;
+    const int64_t budget = (160 * 1024 - 256) / 8 - fixed;  // doubles
+    const double rows_per_star = std::max(1.0, (double)g.m / (double)g.n_stars);
+    auto slots = [&](int64_t tw) {
+        const int64_t rows = with_stars ? tw * kRoundRows : 0;
+        return std::min<int64_t>(rows, (int64_t)(1.25 * rows / rows_per_star) + 8);
+    };
+    auto need = [&](int64_t tw) { return (with_u ? tw * kRoundRows : 0) + kAstro * slots(tw); };
+    int64_t cap = kRoundLdsMax;
+    while (cap > 0 && need(cap) > budget) --cap;
+    r.tw = 0;
+    if (cap == 0) return r;
+    deal_rounds(g, n_cu, cap, &r);
+    r.nsb = (int)slots(r.tw);
+    r.lds = sizeof(double) * (size_t)(fixed + need(r.tw));
+    return r;
+}
+
+// Whether the plan's rounds are long enough, or one round holds the whole system.
+bool good_rounds(const Geo& g, int n_cu, const RowPlan& r) {
+    const int64_t ntiles = (g.m + kStepRows - 1) / kStepRows;
+    return r.tw >= kRoundLds || (r.tw > 0 && ntiles <= (int64_t)r.tw * kRowWaves * n_cu);
+}
+
+// The fused pass: the LDS form where a round holds at least kRoundLds wave steps or the whole
+// system fits one round, the register form otherwise (2e7 rows, n_instr 6,000: LDS form 0.84
+// ms at 22 wave steps, 0.90 at 9, 0.95 at 8; register form 0.90).
+RowPlan plan_fused(const Geo& g, int n_cu) {
+    RowPlan r = plan_rows(g, n_cu, 2 * (int64_t)g.I + 2, true, true);
+    if (good_rounds(g, n_cu, r)) return r;
+    r = RowPlan();
+    r.reg = true;
+    deal_rounds(g, n_cu, 4 * kRegGroups, &r);
+    const size_t base = sizeof(double) * (2 * (size_t)g.I + 1);
+    r.nsb = base + sizeof(double) * kRegXch <= 160 * 1024;
+    r.lds = base + (r.nsb ? sizeof(double) * kRegXch : 0);
+    return r;
+}
+
+// aprod 1 by itself: the instrumental unknowns staged in LDS where that leaves good rounds
+// (n_instr up to about 18,000).
+RowPlan plan_dot(const Geo& g, int n_cu) {
+    RowPlan r = plan_rows(g, n_cu, ((int64_t)g.I + 1) / 2 * 2, true, false);
+    if (good_rounds(g, n_cu, r)) return r;
+    r = plan_rows(g, n_cu, 0, true, false);
+    r.ldsi = false;
+    return r;
+}
+
+// Star-ordered aprod 2 by itself: instrumental sums in LDS up to about n_instr = 20,000.
+RowPlan plan_star(const Geo& g, int n_cu) {
+    RowPlan r = plan_rows(g, n_cu, (int64_t)g.I + 1, false, true);
+    if (r.tw > 0) return r;
+    r = plan_rows(g, n_cu, 1, false, true);
+    r.ldsi = false;
+    return r;
+}
+
 // ---- launches of the products --------------------------------------------------------
 
-constexpr int kBlock1 = 512;   // aprod 1
-constexpr int kBlock2s = 512;  // aprod 2, star-ordered pass
-
-const double* tiles_of(const gsr_handle* h, const double*) { return h->tiles64; }
-const float* tiles_of(const gsr_handle* h, const float*) { return h->tiles32; }
+template <typename VT>
+const VT* tiles_of(const gsr_handle* h);
+template <>
+const double* tiles_of<double>(const gsr_handle* h) { return h->tiles64; }
+template <>
+const float* tiles_of<float>(const gsr_handle* h) { return h->tiles32; }
 
 // Constraint rows.  y_c (op)= C x with the operation of k_con_fin (LSQR modes write their
 // partial sums to part[0] (and part[stride], ... with PENDING)).
 template <int MODE, bool TRANS = false, bool PENDING = false>
-void launch_con_a1(const gsr_handle* h, const double* x, double* yc, const double* bc,
-                   double* part, int stride, double* wc, double* zc, hipStream_t s,
-                   const int32_t* gate = nullptr) {
+void launch_con_a1(const gsr_handle* h, const double* x, const double* yin, double* yc,
+                   const double* bc, double* part, int stride, double* wc, double* zc,
+                   hipStream_t s, const int32_t* gate = nullptr) {
     if (!h->n_con) return;
     if (h->nnz_c > 0)
         hipLaunchKernelGGL(k_con_dot, dim3(h->Gcon), dim3(kConBlock), 0, s, h->nnz_c,
                            h->con_per_block, h->crow, h->ccol, h->cval, x, h->cacc, h->st,
                            (int)(MODE == CON_LSQR), gate);
     hipLaunchKernelGGL((k_con_fin<MODE, TRANS, PENDING>), dim3(1), dim3(kConBlock), 0, s,
-                       h->n_con, h->cacc, yc, bc, h->st, part, stride, wc, zc, gate);
+                       h->n_con, h->cacc, yin, yc, bc, h->st, part, stride, wc, zc, gate);
 }
 
 // x += C^T y_c (SQ: the squared coefficients, for the column norms; y_c unused)
@@ -270,33 +373,46 @@ void launch_con_a2(const gsr_handle* h, const double* yc, double* x, int check_s
                        yc, x, h->st, check_stop);
 }
 
-// y (op)= A xx, from the row tiles when the library built them for this precision; then the
-// constraint rows of y (binary64 coefficients in every precision)
+AttCopy att_copy(const gsr_handle* h) { return {h->xa, h->g.att0, h->g.T}; }
+
+// y (op)= A xx, then the constraint rows of y (binary64 coefficients in every precision).
+// The LSQR modes find the attitude copy of xx in h->xa (the vector step wrote it); the others
+// make one first from kAttCopyRows rows on, where the copy's launch costs less than the gathers
+// it saves (with / without: 6e4 rows 6.4 / 5.2 us, 3.2e5 rows 17.7 / 19.6, 1.1e6 rows 49 / 67,
+// 2e7 rows 853 / 1180).
+constexpr int64_t kAttCopyRows = 250000;
+
 template <typename VT, int MODE>
-void launch_aprod1(const gsr_handle* h, const VT* vals, const double* xx, double* y,
-                   const double* b, hipStream_t s, const int32_t* gate = nullptr) {
-    const VT* tiles = tiles_of(h, vals);
-    auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(h->G1), dim3(kBlock1), h->lds1_bytes, s, h->g, vals,
-                           h->star, h->att, h->instr, tiles, xx, y, b, h->st,
-                           h->partA, h->chunk1, gate);
-    };
-    if (tiles && h->lds1)
-        go(k_aprod1<VT, MODE, true, true>);
-    else if (tiles)
-        go(k_aprod1<VT, MODE, true, false>);
-    else if (h->lds1)
-        go(k_aprod1<VT, MODE, false, true>);
-    else
-        go(k_aprod1<VT, MODE, false, false>);
+void launch_aprod1(const gsr_handle* h, const double* xx, double* y, const double* b,
+                   hipStream_t s, const int32_t* gate = nullptr) {
+    constexpr bool kLsqr = (MODE == A1_LSQR || MODE == A1_LSQR_T);
+    const RowPlan& rp = h->dot;
     const int64_t m = h->g.m;
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(rp.grid), dim3(kRowBlock), rp.lds, s, h->g, tiles_of<VT>(h),
+                           h->star, xx, h->xa, y, b, h->st, h->partA, rp.tw, gate);
+    };
+    if (kLsqr || m >= kAttCopyRows) {
+        if (!kLsqr)
+            hipLaunchKernelGGL(k_att_copy, dim3(grid_for(kAxes * (int64_t)h->g.T, kBlock, 512)),
+                               dim3(kBlock), 0, s, att_copy(h), xx);
+        if (rp.ldsi)
+            go(k_aprod1<VT, MODE, true, true>);
+        else
+            go(k_aprod1<VT, MODE, true, false>);
+    } else if (rp.ldsi) {
+        go(k_aprod1<VT, MODE, false, true>);
+    } else {
+        go(k_aprod1<VT, MODE, false, false>);
+    }
     if (MODE == A1_ADD)
-        launch_con_a1<CON_ADD>(h, xx, y + m, nullptr, nullptr, 0, nullptr, nullptr, s);
+        launch_con_a1<CON_ADD>(h, xx, y + m, y + m, nullptr, nullptr, 0, nullptr, nullptr, s);
     else if (MODE == A1_RESID)
-        launch_con_a1<CON_RESID>(h, xx, y + m, b + m, nullptr, 0, nullptr, nullptr, s, gate);
-    else  // the u-step's (or transposed v-step's) sum of squares continues in slot G1
-        launch_con_a1<CON_LSQR, MODE == A1_LSQR_T>(h, xx, y + m, nullptr, h->partA + h->G1, 0,
-                                                   nullptr, nullptr, s);
+        launch_con_a1<CON_RESID>(h, xx, y + m, y + m, b + m, nullptr, 0, nullptr, nullptr, s,
+                                 gate);
+    else  // the u-step's (or transposed v-step's) sum of squares continues in slot rp.grid
+        launch_con_a1<CON_LSQR, MODE == A1_LSQR_T>(h, xx, y + m, y + m, nullptr,
+                                                   h->partA + rp.grid, 0, nullptr, nullptr, s);
 }
 
 // x[ins0 .. glb0] += the blocks' instrumental/global sums in part_ig
@@ -325,26 +441,33 @@ void launch_att(const gsr_handle* h, const VT* attT, const double* y, double* x,
 // x += A^T y: star-ordered pass (astrometric, instrumental, global), reduction of the
 // instrumental/global block sums, attitude pass over the library's copy.
 template <typename VT, int MODE>
-void launch_aprod2(const gsr_handle* h, const VT* vals, const VT* attT, const double* y,
-                   double* x, hipStream_t s) {
+void launch_aprod2(const gsr_handle* h, const VT* attT, const double* y, double* x,
+                   hipStream_t s) {
     const Geo& g = h->g;
-    hipLaunchKernelGGL((k_aprod2_star<VT, MODE>), dim3(h->G2s), dim3(kBlock2s), h->lds2_bytes, s,
-                       g, vals, h->star, h->instr, y, x, h->st, h->part_ig, h->chunk2s, h->lds2);
-    if (h->lds2) launch_reduce(h, h->G2s, x, (int)(MODE == A2_LSQR || MODE == A2_LSQR_T), s);
+    const RowPlan& rp = h->star_pass;
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(rp.grid), dim3(kRowBlock), rp.lds, s, g, tiles_of<VT>(h),
+                           h->star, y, x, h->st, h->part_ig, rp.tw, rp.nsb);
+    };
+    if (rp.ldsi)
+        go(k_aprod2_star<VT, MODE, true>);
+    else
+        go(k_aprod2_star<VT, MODE, false>);
+    if (rp.ldsi) launch_reduce(h, rp.grid, x, (int)(MODE == A2_LSQR || MODE == A2_LSQR_T), s);
     launch_att<VT, MODE>(h, attT, y, x, s);
     launch_con_a2<MODE == A2_SQ>(h, MODE == A2_SQ ? nullptr : y + g.m, x,
                                  (int)(MODE == A2_LSQR || MODE == A2_LSQR_T), s);
 }
 
-// p = 1 / column norms of `vals`.  Synchronizes.
+// p = 1 / column norms of the coefficients (row tiles and attitude copy).  Synchronizes.
 template <typename VT>
-gsr_status colnorm(gsr_handle* h, const VT* vals, const VT* attT, double* p, hipStream_t s,
+gsr_status colnorm(gsr_handle* h, const VT* attT, double* p, hipStream_t s,
                    unsigned long long* n_empty) {
     unsigned long long* d_cnt = nullptr;
     GSR_TRY(dalloc(&d_cnt, 1));
     HIP_TRY(hipMemsetAsync(d_cnt, 0, sizeof(*d_cnt), s));
     fill(h->s, h->g.n, 0.0, s);
-    launch_aprod2<VT, A2_SQ>(h, vals, attT, nullptr, h->s, s);
+    launch_aprod2<VT, A2_SQ>(h, attT, nullptr, h->s, s);
     hipLaunchKernelGGL(k_recip_sqrt, dim3(grid_for(h->g.n, kBlock, kVecBlocksMax)), dim3(kBlock),
                        0, s, h->g.n, h->s, p, d_cnt);
     hipError_t e = hipMemcpyAsync(n_empty, d_cnt, sizeof(*d_cnt), hipMemcpyDeviceToHost, s);
@@ -450,60 +573,64 @@ void mark(hipEvent_t e, hipStream_t s) {
     if (e) (void)hipEventRecord(e, s);
 }
 
-// Fused row pass: u~ = sv A xt - alpha su u~ and s += A^T u~ (astrometric, instrumental,
-// global), then the instrumental/global reduction and the attitude pass (s += A_att^T u~).
-// The fused row pass (u-step of the forward solve, or with TRANS the v-step of the adjoint
-// solve with its pending z/w update in ww/zz), then the instrumental/global block sums and
-// the attitude columns of s from the attitude copy.  Sum-of-squares partials go to `parts`.
-constexpr int kU12 = 1;  // row steps per load batch of the fused pass (measured best)
-template <typename VT, bool TRANS = false, bool INIT = false>
-void launch_fused(const gsr_handle* h, const VT* vals, const VT* attT, double* u, double* s_acc,
-                  double* parts, hipStream_t s, const IterEvents* ev, double* ww = nullptr,
-                  double* zz = nullptr) {
+// The fused row pass (u-step of the forward solve from uin to uout, or with TRANS the v-step
+// of the adjoint solve, uin == uout, with its pending z/w update in ww/zz), then the
+// instrumental/global block sums and the attitude columns of s from the attitude copy.
+// Sum-of-squares partials go to `parts`.
+template <typename VT, bool TRANS = false>
+void launch_fused(const gsr_handle* h, const VT* attT, const double* uin, double* uout,
+                  double* s_acc, double* parts, hipStream_t s,
+                  const IterEvents* ev, double* ww = nullptr, double* zz = nullptr) {
     const Geo& g = h->g;
-    const int pstride = h->G12 + h->nc1;  // partial sums: G12 blocks, then the constraint rows
+    const RowPlan& rp = h->row12;
+    const int pstride = rp.grid + h->nc1;  // partial sums: the blocks, then the constraint rows
     if (ev) mark(TRANS ? ev->a2_begin : ev->a1_begin, s);
-    if (!INIT)  // constraint rows of the same step (with the transposed operator, their
-                // pending z/w update too)
-        launch_con_a1<CON_LSQR, TRANS, TRANS>(h, h->xt, u + g.m, nullptr, parts + h->G12,
-                                              pstride, TRANS ? ww + g.m : nullptr,
-                                              TRANS ? zz + g.m : nullptr, s);
-    hipLaunchKernelGGL((k_aprod12<VT, kU12, TRANS, INIT>), dim3(h->G12), dim3(1024),
-                       h->lds12_bytes, s,
-                       g, tiles_of(h, vals), h->star, h->xt, u, s_acc, h->st, parts,
-                       h->part_ig, h->chunk12, pstride, ww, zz);
+    // constraint rows of the same step (with the transposed operator, their pending z/w update
+    // too)
+    launch_con_a1<CON_LSQR, TRANS, TRANS>(h, h->xt, uin + g.m, uout + g.m, nullptr,
+                                          parts + rp.grid, pstride, TRANS ? ww + g.m : nullptr,
+                                          TRANS ? zz + g.m : nullptr, s);
+    const RowArgs<VT> a = {g,     tiles_of<VT>(h), h->star,    h->xt, h->xa, uin,     uout,  s_acc,
+                           h->st, parts,           h->part_ig, ww,    zz,    pstride, rp.tw, rp.nsb};
+    if (rp.reg)
+        hipLaunchKernelGGL((k_aprod12_reg<VT, TRANS>), dim3(rp.grid), dim3(kRowBlock), rp.lds, s,
+                           a);
+    else
+        hipLaunchKernelGGL((k_aprod12<VT, TRANS>), dim3(rp.grid), dim3(kRowBlock), rp.lds, s, a);
     if (ev) mark(TRANS ? ev->a2_end : ev->a1_end, s);
     if (ev) mark(TRANS ? ev->a1_begin : ev->a2_begin, s);
-    launch_reduce(h, h->G12, s_acc, 1, s);
-    launch_att<VT, A2_LSQR>(h, attT, u, s_acc, s);
-    launch_con_a2<false>(h, u + g.m, s_acc, 1, s);
+    launch_reduce(h, rp.grid, s_acc, 1, s);
+    launch_att<VT, A2_LSQR>(h, attT, uout, s_acc, s);
+    launch_con_a2<false>(h, uout + g.m, s_acc, 1, s);
     if (ev) mark(TRANS ? ev->a1_end : ev->a2_end, s);
 }
 
 template <typename VT, bool VAR = false>
-void fwd_iteration(const gsr_handle* h, LsqrWork& w, const VT* vals, const VT* attT,
-                   const double* p, hipStream_t s, const IterEvents* ev = nullptr) {
+void fwd_iteration(const gsr_handle* h, LsqrWork& w, const VT* attT, const double* p,
+                   hipStream_t s, int it, const IterEvents* ev = nullptr) {
     const Geo& g = h->g;
     if (h->fused) {
-        // one read of every row: beta u = A (p o v) - alpha u and s = A^T u~ (unnormalized)
-        launch_fused<VT>(h, vals, attT, w.u, h->s, h->partA, s, ev);
+        // one read of every row: beta u = A (p o v) - alpha u and s = A^T u~ (unnormalized);
+        // iteration `it` of the solve reads u~ from u or u2 and writes it to the other
+        launch_fused<VT>(h, attT, it % 2 ? w.u2 : w.u, it % 2 ? w.u : w.u2, h->s, h->partA,
+                         s, ev);
         hipLaunchKernelGGL(k_scal_beta, dim3(1), dim3(kBlock), 0, s, h->st, h->partA,
-                           h->G12 + h->nc1);
+                           h->row12.grid + h->nc1);
     } else {
         // beta u = A (p o v) - alpha u        (xt = p o v~ from the previous vector step)
         if (ev) mark(ev->a1_begin, s);
-        launch_aprod1<VT, A1_LSQR>(h, vals, h->xt, w.u, nullptr, s);
+        launch_aprod1<VT, A1_LSQR>(h, h->xt, w.u, nullptr, s);
         if (ev) mark(ev->a1_end, s);
         hipLaunchKernelGGL(k_scal_beta, dim3(1), dim3(kBlock), 0, s, h->st, h->partA,
-                           h->G1 + h->nc1);
+                           h->dot.grid + h->nc1);
         // s = A^T u~ (unnormalized)
         if (ev) mark(ev->a2_begin, s);
-        launch_aprod2<VT, A2_LSQR>(h, vals, attT, w.u, h->s, s);
+        launch_aprod2<VT, A2_LSQR>(h, attT, w.u, h->s, s);
         if (ev) mark(ev->a2_end, s);
     }
     // alpha v = p o (s / beta) - beta v, with the pending z/w update of the previous iteration
     hipLaunchKernelGGL((k_vec_v<false, VAR>), dim3(h->Gn), dim3(kBlock), 0, s, g.n, h->s, p, w.v,
-                       w.w, w.z, h->xt, h->st, h->partB, w.var);
+                       w.w, w.z, h->xt, att_copy(h), h->st, h->partB, w.var);
     hipLaunchKernelGGL(k_scal_alpha, dim3(1), dim3(kBlock), 0, s, h->st, h->partB, h->Gn,
                        h->partB + h->Gn, h->Gn);
 }
@@ -516,30 +643,31 @@ void trans_iteration(const gsr_handle* h, LsqrWork& w, hipStream_t s,
     if (h->fused) {
         // beta u = D A^T v - alpha u  (s = A^T v~ left by the previous row pass)
         hipLaunchKernelGGL(k_vec_tu, dim3(h->Gn), dim3(kBlock), 0, s, g.n, h->s, h->p64, w.u,
-                           h->xt, h->st, h->partA);
+                           h->xt, att_copy(h), h->st, h->partA);
         hipLaunchKernelGGL(k_scal_beta, dim3(1), dim3(kBlock), 0, s, h->st, h->partA, h->Gn);
         // one read of every row: pending z/w update, alpha v = A D u - beta v, s = A^T v~
-        launch_fused<double, true>(h, h->vals, h->attT64, w.v, h->s, h->partB, s, ev, w.w, w.z);
-        const int P = h->G12 + h->nc1;
+        launch_fused<double, true>(h, h->attT64, w.v, w.v, h->s, h->partB, s, ev, w.w,
+                                   w.z);
+        const int P = h->row12.grid + h->nc1;
         hipLaunchKernelGGL(k_scal_alpha, dim3(1), dim3(kBlock), 0, s, h->st, h->partB, P,
                            h->partB + P, P);
         return;
     }
     // beta u = D A^T v - alpha u
     if (ev) mark(ev->a2_begin, s);
-    launch_aprod2<double, A2_LSQR_T>(h, h->vals, h->attT64, w.v, h->s, s);
+    launch_aprod2<double, A2_LSQR_T>(h, h->attT64, w.v, h->s, s);
     if (ev) mark(ev->a2_end, s);
     hipLaunchKernelGGL(k_vec_tu, dim3(h->Gn), dim3(kBlock), 0, s, g.n, h->s, h->p64, w.u, h->xt,
-                       h->st, h->partA);
+                       att_copy(h), h->st, h->partA);
     hipLaunchKernelGGL(k_scal_beta, dim3(1), dim3(kBlock), 0, s, h->st, h->partA, h->Gn);
     // pending z/w update, then alpha v = A D u - beta v
     hipLaunchKernelGGL(k_vec_zw, dim3(h->Gm), dim3(kBlock), 0, s, h->rows(), w.v, w.w, w.z,
                        h->st, h->partB);
     if (ev) mark(ev->a1_begin, s);
-    launch_aprod1<double, A1_LSQR_T>(h, h->vals, h->xt, w.v, nullptr, s);
+    launch_aprod1<double, A1_LSQR_T>(h, h->xt, w.v, nullptr, s);
     if (ev) mark(ev->a1_end, s);
     hipLaunchKernelGGL(k_scal_alpha, dim3(1), dim3(kBlock), 0, s, h->st, h->partA,
-                       h->G1 + h->nc1, h->partB, h->Gm);
+                       h->dot.grid + h->nc1, h->partB, h->Gm);
 }
 
 // Profile mode: the iterations are launched one by one with events around the products;
@@ -558,7 +686,7 @@ gsr_status run_profiled(gsr_handle* h, const gsr_solve_opts& o, hipStream_t s, F
     int launched = 0;
     gsr_status rc = GSR_OK;
     for (int it = 0; it < o.itnlim; ++it) {
-        iteration(s, &ev[(size_t)it]);
+        iteration(s, it, &ev[(size_t)it]);
         ++launched;
         if (!o.fixed_iters && (it + 1) % every == 0) {
             hipError_t e = hipMemcpyAsync(&h->st_host->stop, &h->st->stop, sizeof(int32_t),
@@ -600,7 +728,7 @@ gsr_status capture_graph(gsr_handle* h, LsqrWork& w, F&& body) {
     if (w.graph) return GSR_OK;
     hipGraph_t graph = nullptr;
     HIP_TRY(hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal));
-    for (int k = 0; k < kGraphIters; ++k) body(h->cap);
+    for (int k = 0; k < kGraphIters; ++k) body(h->cap, k);
     hipError_t e = hipStreamEndCapture(h->cap, &graph);
     if (e != hipSuccess) return hip_fail(e, "hipStreamEndCapture");
     e = hipGraphInstantiate(&w.graph, graph, nullptr, nullptr, 0);
@@ -665,33 +793,31 @@ gsr_status read_info(gsr_handle* h, gsr_solve_info* info, hipStream_t s,
 // PC-LSQR on A (binary64 or binary32 coefficients): x = p o z; VAR: also the variance
 // estimate var_out = p^2 o sum (w_i / rho_i)^2.  Synchronizes.
 template <typename VT, bool VAR = false>
-gsr_status fwd_solve(gsr_handle* h, LsqrWork& w, const VT* vals, const VT* attT,
-                     const double* p, const double* b, double* x, const gsr_solve_opts& o,
+gsr_status fwd_solve(gsr_handle* h, LsqrWork& w, const VT* attT, const double* p,
+                     const double* b, double* x, const gsr_solve_opts& o,
                      gsr_solve_info* info, hipStream_t s, double* var_out = nullptr) {
     const Geo& g = h->g;
     GSR_TRY(ensure_work(w, h->rows(), g.n, VAR));
     GSR_TRY(capture_graph(
-        h, w, [&](hipStream_t cs) { fwd_iteration<VT, VAR>(h, w, vals, attT, p, cs); }));
+        h, w,
+        [&](hipStream_t cs, int it) { fwd_iteration<VT, VAR>(h, w, attT, p, cs, it); }));
     // beta_1 u_1 = b
     hipLaunchKernelGGL(k_copy_norm<false>, dim3(h->Gm), dim3(kBlock), 0, s, h->rows(), b, nullptr,
-                       w.u, nullptr, h->partA);
+                       w.u, nullptr, AttCopy{}, h->partA);
     hipLaunchKernelGGL(k_scal_init1, dim3(1), dim3(kBlock), 0, s, h->st, h->partA, h->Gm,
                        o.itnlim, o.fixed_iters, o.atol, o.btol, o.conlim);
     // alpha_1 v_1 = p o A^T u_1  (the initial aprod 2)
     fill(h->s, g.n, 0.0, s);
-    if (h->fused)
-        launch_fused<VT, false, true>(h, vals, attT, w.u, h->s, h->partB, s, nullptr);
-    else
-        launch_aprod2<VT, A2_LSQR>(h, vals, attT, w.u, h->s, s);
+    launch_aprod2<VT, A2_LSQR>(h, attT, w.u, h->s, s);
     hipLaunchKernelGGL((k_vec_v<true, VAR>), dim3(h->Gn), dim3(kBlock), 0, s, g.n, h->s, p, w.v,
-                       w.w, w.z, h->xt, h->st, h->partB, w.var);
+                       w.w, w.z, h->xt, att_copy(h), h->st, h->partB, w.var);
     hipLaunchKernelGGL(k_scal_init2, dim3(1), dim3(kBlock), 0, s, h->st, h->partB, h->Gn);
     ProfileOut prof;
     if (o.profile)
         GSR_TRY(run_profiled(
             h, o, s,
-            [&](hipStream_t cs, const IterEvents* ev) {
-                fwd_iteration<VT, VAR>(h, w, vals, attT, p, cs, ev);
+            [&](hipStream_t cs, int it, const IterEvents* ev) {
+                fwd_iteration<VT, VAR>(h, w, attT, p, cs, it, ev);
             },
             &prof.ms1, &prof.ms2, &prof.n));
     else
@@ -733,23 +859,20 @@ static __global__ void k_write_info(const LsqrState* __restrict__ st, gsr_solve_
 // iterations are enqueued; once the device stop flag is set the rest return at once.
 // gate (may be NULL): when *gate is set at the time the solve would start, it is not started.
 template <typename VT>
-void fwd_enqueue(const gsr_handle* h, LsqrWork& w, const VT* vals, const VT* attT,
-                 const double* p, const double* b, double* x, const gsr_solve_opts& o,
+void fwd_enqueue(const gsr_handle* h, LsqrWork& w, const VT* attT, const double* p,
+                 const double* b, double* x, const gsr_solve_opts& o,
                  hipStream_t s, const int32_t* gate) {
     const Geo& g = h->g;
     hipLaunchKernelGGL(k_copy_norm<false>, dim3(h->Gm), dim3(kBlock), 0, s, h->rows(), b, nullptr,
-                       w.u, nullptr, h->partA);
+                       w.u, nullptr, AttCopy{}, h->partA);
     hipLaunchKernelGGL(k_scal_init1, dim3(1), dim3(kBlock), 0, s, h->st, h->partA, h->Gm,
                        o.itnlim, o.fixed_iters, o.atol, o.btol, o.conlim, gate);
     fill(h->s, g.n, 0.0, s);
-    if (h->fused)
-        launch_fused<VT, false, true>(h, vals, attT, w.u, h->s, h->partB, s, nullptr);
-    else
-        launch_aprod2<VT, A2_LSQR>(h, vals, attT, w.u, h->s, s);
+    launch_aprod2<VT, A2_LSQR>(h, attT, w.u, h->s, s);
     hipLaunchKernelGGL((k_vec_v<true>), dim3(h->Gn), dim3(kBlock), 0, s, g.n, h->s, p, w.v,
-                       w.w, w.z, h->xt, h->st, h->partB, nullptr);
+                       w.w, w.z, h->xt, att_copy(h), h->st, h->partB, nullptr);
     hipLaunchKernelGGL(k_scal_init2, dim3(1), dim3(kBlock), 0, s, h->st, h->partB, h->Gn);
-    for (int it = 0; it < o.itnlim; ++it) fwd_iteration<VT>(h, w, vals, attT, p, s);
+    for (int it = 0; it < o.itnlim; ++it) fwd_iteration<VT>(h, w, attT, p, s, it);
     hipLaunchKernelGGL((k_final<true>), dim3(h->Gn), dim3(kBlock), 0, s, g.n, p, w.z, w.w, w.v,
                        x, h->st);
 }
@@ -779,7 +902,7 @@ void ref_step(const gsr_handle* h, double* x, const gsr_solve_opts& o, hipStream
 // The binary64 PC-LSQR, stream-ordered.
 gsr_status fwd_solve_async(gsr_handle* h, const double* b, double* x, const gsr_solve_opts& o,
                            gsr_solve_info* info_dev, hipStream_t s) {
-    fwd_enqueue<double>(h, h->fwd64, h->vals, h->attT64, h->p64, b, x, o, s, nullptr);
+    fwd_enqueue<double>(h, h->fwd64, h->attT64, h->p64, b, x, o, s, nullptr);
     hipLaunchKernelGGL(k_write_info, dim3(1), dim3(64), 0, s, h->st, info_dev, (int32_t)h->fused,
                        nullptr);
     HIP_TRY(hipGetLastError());
@@ -798,11 +921,11 @@ gsr_status f32v_solve_async(gsr_handle* h, const double* b, double* x, const gsr
                        h->rows(), b, h->r);
     fill(x, g.n, 0.0, s);
     for (int k = 0; k < o.max_refine; ++k) {
-        fwd_enqueue<float>(h, h->fwd32, h->vals32, h->attT32, h->p32, h->r, h->dx,
+        fwd_enqueue<float>(h, h->fwd32, h->attT32, h->p32, h->r, h->dx,
                            inner_opts(o, k), s, gate);
         ref_step(h, x, o, s);
         if (k + 1 < o.max_refine)
-            launch_aprod1<double, A1_RESID>(h, h->vals, x, h->r, b, s, gate);
+            launch_aprod1<double, A1_RESID>(h, x, h->r, b, s, gate);
     }
     hipLaunchKernelGGL(k_write_info, dim3(1), dim3(64), 0, s, h->st, info_dev, (int32_t)h->fused,
                        h->ref);
@@ -814,11 +937,11 @@ gsr_status trans_solve(gsr_handle* h, const double* gvec, double* mu, const gsr_
                        gsr_solve_info* info, hipStream_t s) {
     const Geo& g = h->g;
     LsqrWork& w = h->trans;
-    GSR_TRY(ensure_work(w, g.n, h->rows()));
-    GSR_TRY(capture_graph(h, w, [&](hipStream_t cs) { trans_iteration(h, w, cs); }));
+    GSR_TRY(ensure_work(w, g.n, h->rows(), false, false));
+    GSR_TRY(capture_graph(h, w, [&](hipStream_t cs, int) { trans_iteration(h, w, cs); }));
     // beta_1 u_1 = D g
     hipLaunchKernelGGL(k_copy_norm<true>, dim3(h->Gn), dim3(kBlock), 0, s, g.n, gvec, h->p64,
-                       w.u, h->xt, h->partA);
+                       w.u, h->xt, att_copy(h), h->partA);
     hipLaunchKernelGGL(k_scal_init1, dim3(1), dim3(kBlock), 0, s, h->st, h->partA, h->Gn,
                        o.itnlim, o.fixed_iters, o.atol, o.btol, o.conlim);
     fill(w.w, h->rows(), 0.0, s);
@@ -826,19 +949,20 @@ gsr_status trans_solve(gsr_handle* h, const double* gvec, double* mu, const gsr_
     // alpha_1 v_1 = A D u_1 (and, fused, s = A^T v~_1 for the first u-step)
     if (h->fused) {
         fill(h->s, g.n, 0.0, s);
-        launch_fused<double, true>(h, h->vals, h->attT64, w.v, h->s, h->partB, s, nullptr, w.w,
-                                   w.z);
+        launch_fused<double, true>(h, h->attT64, w.v, w.v, h->s, h->partB, s, nullptr,
+                                   w.w, w.z);
         hipLaunchKernelGGL(k_scal_init2, dim3(1), dim3(kBlock), 0, s, h->st, h->partB,
-                           h->G12 + h->nc1);
+                           h->row12.grid + h->nc1);
     } else {
-        launch_aprod1<double, A1_LSQR_T>(h, h->vals, h->xt, w.v, nullptr, s);
+        launch_aprod1<double, A1_LSQR_T>(h, h->xt, w.v, nullptr, s);
         hipLaunchKernelGGL(k_scal_init2, dim3(1), dim3(kBlock), 0, s, h->st, h->partA,
-                           h->G1 + h->nc1);
+                           h->dot.grid + h->nc1);
     }
     ProfileOut prof;
     if (o.profile)
         GSR_TRY(run_profiled(
-            h, o, s, [&](hipStream_t cs, const IterEvents* ev) { trans_iteration(h, w, cs, ev); },
+            h, o, s,
+            [&](hipStream_t cs, int, const IterEvents* ev) { trans_iteration(h, w, cs, ev); },
             &prof.ms1, &prof.ms2, &prof.n));
     else
         GSR_TRY(run_iterations(h, w, o, s));
@@ -1065,69 +1189,27 @@ gsr_status gsr_lsqr_setup(const gsr_dims* dims, const double* vals, const int32_
         return st;
     };
 
-    // launch shapes: persistent grids sized by occupancy; row chunks of 16..1024 rows
-    // so that every wave slot of the GPU gets several chunks
     h->Gn = grid_for(g.n, kBlock, kVecBlocksMax);
     h->Gm = grid_for(g.m, kBlock, kVecBlocksMax);
-    h->lds1 = g.I <= kInstrLdsMax;
-    h->lds2 = g.I <= kInstrLdsMax;
-    h->lds1_bytes = h->lds1 ? sizeof(double) * g.I : 0;
-    h->lds2_bytes = h->lds2 ? sizeof(double) * (g.I + 1) : 0;
-    {
-        auto occ = [&](const void* fn, int threads, size_t lds) {
-            int per_cu = 0;
-            hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds);
-            return (e != hipSuccess || per_cu < 1) ? 1 : per_cu;
-        };
-        // rows per wave chunk: at most 1024, and sized so that every wave of the persistent
-        // grid gets (nearly) the same number of chunks (small systems: at least 4 per wave)
-        // rows per wave chunk: about `cap`, the same number of chunks for every wave, at
-        // least four chunks per wave for small systems
-        auto chunk_for = [&](int waves, int64_t cap = 1024) {
-            const int64_t w = std::max(waves, 1);
-            int64_t c;
-            if (g.m >= 4 * cap * w) {
-                const int64_t per = (g.m + cap * w - 1) / (cap * w);  // chunks per wave
-                c = (g.m + w * per - 1) / (w * per);
-            } else {
-                c = g.m / (4 * w);
-            }
-            c = std::max<int64_t>(kStepRows, std::min<int64_t>(cap, c));
-            return (int)((c + kStepRows - 1) / kStepRows * kStepRows);
-        };
-        auto grid = [&](int per_cu, int threads, int chunk) {
-            const int64_t chunks = (g.m + chunk - 1) / chunk;
-            const int64_t need = (chunks + threads / kWave - 1) / (threads / kWave);
-            return (int)std::max<int64_t>(1, std::min<int64_t>(need, (int64_t)per_cu * n_cu));
-        };
-        const int o1 = occ((const void*)k_aprod1<double, A1_LSQR, false, true>, kBlock1, h->lds1_bytes);
-        const int o2s = occ((const void*)k_aprod2_star<double, A2_LSQR>, kBlock2s, h->lds2_bytes);
-        h->chunk1 = chunk_for(o1 * n_cu * kBlock1 / kWave);
-        h->chunk2s = chunk_for(o2s * n_cu * kBlock2s / kWave);
-        h->G1 = grid(o1, kBlock1, h->chunk1);
-        h->G2s = grid(o2s, kBlock2s, h->chunk2s);
-        // the fused pass keeps the block's instrumental sums and the instrumental part of xt
-        // in LDS (160 KiB per CU)
-        h->lds12_bytes = sizeof(double) * (2 * (size_t)g.I + 1);
-        h->fused = h->lds2 && h->lds12_bytes <= 160 * 1024;
-        if (h->fused) {
-            const int o12 = occ((const void*)k_aprod12<double, kU12>, 1024, h->lds12_bytes);
-            // about 3,072-row chunks: measured 3.5 % faster than 1,024 at 2e8 rows (fewer
-            // chunk switches, each a fresh stream start)
-            h->chunk12 = chunk_for(o12 * n_cu * 1024 / kWave, 3072);
-            h->G12 = grid(o12, 1024, h->chunk12);
-        }
-    }
-    gsr_status st;
-    if ((st = dalloc(&h->p64, g.n)) != GSR_OK) return bail(st);
-    if ((st = dalloc(&h->s, g.n)) != GSR_OK) return bail(st);
-    if ((st = dalloc(&h->xt, g.n)) != GSR_OK) return bail(st);
+    h->dot = plan_dot(g, n_cu);
+    h->star_pass = plan_star(g, n_cu);
+    // the fused pass keeps the block's instrumental sums and the instrumental part of xt in LDS
+    // (160 KiB per compute unit)
+    h->fused = g.I <= kInstrLdsMax && sizeof(double) * (2 * (size_t)g.I + 1) <= 160 * 1024;
+    if (h->fused) h->row12 = plan_fused(g, n_cu);
+    gsr_status st =
+        so.build_f32
+            ? dalloc_vecs(&h->slab, {&h->p64, &h->s, &h->xt, &h->p32, &h->dx}, g.n, kGathered)
+            : dalloc_vecs(&h->slab, {&h->p64, &h->s, &h->xt}, g.n, kGathered);
+    if (st != GSR_OK) return bail(st);
+    if ((st = dalloc(&h->xa, (size_t)kAxes * g.T)) != GSR_OK) return bail(st);
     // one more slot than the largest grid: the constraint rows' partial sum
-    const int part_len = std::max(std::max(std::max(h->G1, h->Gm), h->Gn), h->G12) + 1;
+    const int part_len = std::max({h->dot.grid, h->Gm, h->Gn, h->row12.grid}) + 1;
     if ((st = dalloc(&h->partA, part_len)) != GSR_OK) return bail(st);
     if ((st = dalloc(&h->partB, 4 * (size_t)part_len)) != GSR_OK) return bail(st);
-    if (h->lds2 && (st = dalloc(&h->part_ig, (size_t)std::max(h->G2s, h->G12) * (g.I + 1))) !=
-                       GSR_OK)
+    if (h->star_pass.ldsi &&
+        (st = dalloc(&h->part_ig, (size_t)std::max(h->star_pass.grid, h->row12.grid) *
+                                      (g.I + 1))) != GSR_OK)
         return bail(st);
     if ((st = dalloc(&h->st, 1)) != GSR_OK) return bail(st);
     // the binary64 solve's vectors: allocated here so that a stream-ordered solve allocates
@@ -1162,14 +1244,7 @@ gsr_status gsr_lsqr_setup(const gsr_dims* dims, const double* vals, const int32_
                              (flags & 4) ? " attitude start out of [0, n_dfa-4]" : "",
                              (flags & 8) ? " instrumental index out of range" : ""));
     }
-    if ((st = build_att_order(h, s)) != GSR_OK) return bail(st);
-    unsigned long long n_empty = 0;
-    if ((st = colnorm<double>(h, vals, h->attT64, h->p64, s, &n_empty)) != GSR_OK)
-        return bail(st);
-    h->allow_empty = so.allow_empty_cols;
-    if (n_empty && !so.allow_empty_cols)
-        return bail(fail(GSR_E_LAYOUT, "%llu all-zero column(s); set allow_empty_cols", n_empty));
-    if (h->fused && g.m > 0) {
+    if (g.m > 0) {
         h->ntiles = (g.m + kStepRows - 1) / kStepRows;
         const int64_t nv = h->ntiles * kTileVals, ni = h->ntiles * kTileIdx;
         if ((st = dalloc(&h->tiles64, h->ntiles * tile_elems<double>())) != GSR_OK)
@@ -1188,22 +1263,24 @@ gsr_status gsr_lsqr_setup(const gsr_dims* dims, const double* vals, const int32_
                                h->tiles32);
         }
     }
+    if ((st = build_att_order(h, s)) != GSR_OK) return bail(st);
+    unsigned long long n_empty = 0;
+    if ((st = colnorm<double>(h, h->attT64, h->p64, s, &n_empty)) != GSR_OK)
+        return bail(st);
+    h->allow_empty = so.allow_empty_cols;
+    if (n_empty && !so.allow_empty_cols)
+        return bail(fail(GSR_E_LAYOUT, "%llu all-zero column(s); set allow_empty_cols", n_empty));
     if (so.build_f32) {
-        const int64_t nnz = (int64_t)g.m * kPar,
-                      natt = (g.m + kStepRows - 1) / kStepRows * kTileAtt;
-        if ((st = dalloc(&h->vals32, nnz)) != GSR_OK) return bail(st);
+        const int64_t natt = (g.m + kStepRows - 1) / kStepRows * kTileAtt;
+        h->has_f32 = true;
         if ((st = dalloc(&h->attT32, natt)) != GSR_OK) return bail(st);
-        if ((st = dalloc(&h->p32, g.n)) != GSR_OK) return bail(st);
-        hipLaunchKernelGGL(k_to_f32, dim3(grid_for(nnz, kBlock, 8192)), dim3(kBlock), 0, s, nnz,
-                           vals, h->vals32);
         hipLaunchKernelGGL(k_to_f32, dim3(grid_for(natt, kBlock, 8192)), dim3(kBlock), 0, s,
                            natt, h->attT64, h->attT32);
         unsigned long long n_empty32 = 0;
-        if ((st = colnorm<float>(h, h->vals32, h->attT32, h->p32, s, &n_empty32)) != GSR_OK)
+        if ((st = colnorm<float>(h, h->attT32, h->p32, s, &n_empty32)) != GSR_OK)
             return bail(st);
         // the precision form's workspaces, so that its stream-ordered solve allocates nothing
         if ((st = ensure_work(h->fwd32, g.m, g.n)) != GSR_OK) return bail(st);
-        if ((st = dalloc(&h->dx, g.n)) != GSR_OK) return bail(st);
         if ((st = dalloc(&h->r, g.m)) != GSR_OK) return bail(st);
         if ((st = dalloc(&h->ref_part, 2 * (size_t)h->Gn)) != GSR_OK) return bail(st);
         if ((st = dalloc(&h->ref, 1)) != GSR_OK) return bail(st);
@@ -1223,7 +1300,7 @@ gsr_status gsr_destroy(gsr_handle* h) {
     free_work(h->fwd64v);
     free_work(h->fwd32);
     free_work(h->trans);
-    dfree(h->vals32);
+    dfree(h->slab);
     dfree(h->tiles64);
     dfree(h->tiles32);
     dfree(h->attT32);
@@ -1232,15 +1309,11 @@ gsr_status gsr_destroy(gsr_handle* h) {
     dfree(h->tT);
     dfree(h->att_seg);
     dfree(h->att_part);
-    dfree(h->xt);
+    dfree(h->xa);
     dfree(h->part_ig);
-    dfree(h->p64);
-    dfree(h->p32);
-    dfree(h->s);
     dfree(h->partA);
     dfree(h->partB);
     dfree(h->st);
-    dfree(h->dx);
     dfree(h->r);
     dfree(h->ref_part);
     dfree(h->ref);
@@ -1267,7 +1340,6 @@ gsr_status gsr_update_values(gsr_handle* h, const double* vals, void* stream) {
     if ((uintptr_t)vals & 15) return fail(GSR_E_INVAL, "vals must be 16-byte aligned");
     GSR_TRY(set_device(h));
     hipStream_t s = as_stream(stream);
-    // the captured iterations of the unfused path read the coefficients from `vals`
     HIP_TRY(hipStreamSynchronize(s));
     HIP_TRY(hipStreamSynchronize(h->cap));
     for (LsqrWork* w : {&h->fwd64, &h->fwd64v, &h->fwd32, &h->trans}) {
@@ -1287,18 +1359,15 @@ gsr_status gsr_update_values(gsr_handle* h, const double* vals, void* stream) {
         if (h->tiles32)
             hipLaunchKernelGGL(k_make_tiles<float>, dim3(grid_for(nv, kBlock, 8192)),
                                dim3(kBlock), 0, s, g.m, h->ntiles, vals, h->tiles32);
-        if (h->vals32) {
-            const int64_t nnz = g.m * kPar;
-            hipLaunchKernelGGL(k_to_f32, dim3(grid_for(nnz, kBlock, 8192)), dim3(kBlock), 0, s,
-                               nnz, vals, h->vals32);
+        if (h->has_f32) {
             hipLaunchKernelGGL(k_to_f32, dim3(grid_for(natt, kBlock, 8192)), dim3(kBlock), 0, s,
                                natt, h->attT64, h->attT32);
         }
         HIP_TRY(hipGetLastError());
     }
     unsigned long long n_empty = 0, n_empty32 = 0;
-    GSR_TRY(colnorm<double>(h, vals, h->attT64, h->p64, s, &n_empty));
-    if (h->vals32) GSR_TRY(colnorm<float>(h, h->vals32, h->attT32, h->p32, s, &n_empty32));
+    GSR_TRY(colnorm<double>(h, h->attT64, h->p64, s, &n_empty));
+    if (h->has_f32) GSR_TRY(colnorm<float>(h, h->attT32, h->p32, s, &n_empty32));
     if (n_empty && !h->allow_empty)
         return fail(GSR_E_LAYOUT, "%llu all-zero column(s) in the new values; set "
                                   "allow_empty_cols at setup", n_empty);
@@ -1338,11 +1407,11 @@ gsr_status gsr_set_constraints(gsr_handle* h, int64_t n_con, const int64_t* ptr,
     // the preconditioner includes the constraint rows (binary64 coefficients in both
     // precisions); the workspaces of the stream-ordered solves are allocated again here
     unsigned long long n_empty = 0;
-    gsr_status rc2 = colnorm<double>(h, h->vals, h->attT64, h->p64, s, &n_empty);
-    if (rc2 == GSR_OK && h->vals32)
-        rc2 = colnorm<float>(h, h->vals32, h->attT32, h->p32, s, &n_empty);
+    gsr_status rc2 = colnorm<double>(h, h->attT64, h->p64, s, &n_empty);
+    if (rc2 == GSR_OK && h->has_f32)
+        rc2 = colnorm<float>(h, h->attT32, h->p32, s, &n_empty);
     if (rc2 == GSR_OK) rc2 = ensure_work(h->fwd64, h->rows(), h->g.n);
-    if (rc2 == GSR_OK && h->vals32) {
+    if (rc2 == GSR_OK && h->has_f32) {
         dfree(h->r);
         h->r = nullptr;
         rc2 = dalloc(&h->r, h->rows());
@@ -1354,7 +1423,7 @@ gsr_status gsr_set_constraints(gsr_handle* h, int64_t n_con, const int64_t* ptr,
 gsr_status gsr_aprod1(gsr_handle* h, const double* x, double* y, void* stream) {
     if (!h || !x || !y) return fail(GSR_E_INVAL, "null argument");
     GSR_TRY(set_device(h));
-    launch_aprod1<double, A1_ADD>(h, h->vals, x, y, nullptr, as_stream(stream));
+    launch_aprod1<double, A1_ADD>(h, x, y, nullptr, as_stream(stream));
     HIP_TRY(hipGetLastError());
     return GSR_OK;
 }
@@ -1362,25 +1431,25 @@ gsr_status gsr_aprod1(gsr_handle* h, const double* x, double* y, void* stream) {
 gsr_status gsr_aprod2(gsr_handle* h, const double* y, double* x, void* stream) {
     if (!h || !x || !y) return fail(GSR_E_INVAL, "null argument");
     GSR_TRY(set_device(h));
-    launch_aprod2<double, A2_ADD>(h, h->vals, h->attT64, y, x, as_stream(stream));
+    launch_aprod2<double, A2_ADD>(h, h->attT64, y, x, as_stream(stream));
     HIP_TRY(hipGetLastError());
     return GSR_OK;
 }
 
 gsr_status gsr_aprod1_f32v(gsr_handle* h, const double* x, double* y, void* stream) {
     if (!h || !x || !y) return fail(GSR_E_INVAL, "null argument");
-    if (!h->vals32) return fail(GSR_E_UNSUPPORTED, "binary32 copy not built (build_f32 = 0)");
+    if (!h->has_f32) return fail(GSR_E_UNSUPPORTED, "binary32 copy not built (build_f32 = 0)");
     GSR_TRY(set_device(h));
-    launch_aprod1<float, A1_ADD>(h, h->vals32, x, y, nullptr, as_stream(stream));
+    launch_aprod1<float, A1_ADD>(h, x, y, nullptr, as_stream(stream));
     HIP_TRY(hipGetLastError());
     return GSR_OK;
 }
 
 gsr_status gsr_aprod2_f32v(gsr_handle* h, const double* y, double* x, void* stream) {
     if (!h || !x || !y) return fail(GSR_E_INVAL, "null argument");
-    if (!h->vals32) return fail(GSR_E_UNSUPPORTED, "binary32 copy not built (build_f32 = 0)");
+    if (!h->has_f32) return fail(GSR_E_UNSUPPORTED, "binary32 copy not built (build_f32 = 0)");
     GSR_TRY(set_device(h));
-    launch_aprod2<float, A2_ADD>(h, h->vals32, h->attT32, y, x, as_stream(stream));
+    launch_aprod2<float, A2_ADD>(h, h->attT32, y, x, as_stream(stream));
     HIP_TRY(hipGetLastError());
     return GSR_OK;
 }
@@ -1399,7 +1468,7 @@ gsr_status gsr_residual(gsr_handle* h, const double* b, const double* x, double*
                         void* stream) {
     if (!h || !b || !x || !r) return fail(GSR_E_INVAL, "null argument");
     GSR_TRY(set_device(h));
-    launch_aprod1<double, A1_RESID>(h, h->vals, x, r, b, as_stream(stream));
+    launch_aprod1<double, A1_RESID>(h, x, r, b, as_stream(stream));
     HIP_TRY(hipGetLastError());
     return GSR_OK;
 }
@@ -1413,23 +1482,23 @@ gsr_status gsr_lsqr_solve(gsr_handle* h, const double* b, double* x, const gsr_s
     GSR_TRY(set_device(h));
     hipStream_t s = as_stream(stream);
     if (o.precision == GSR_F64)
-        return fwd_solve<double>(h, h->fwd64, h->vals, h->attT64, h->p64, b, x, o, info, s);
+        return fwd_solve<double>(h, h->fwd64, h->attT64, h->p64, b, x, o, info, s);
 
     // binary32 coefficients inside, binary64 residual correction outside
-    if (!h->vals32) return fail(GSR_E_UNSUPPORTED, "binary32 copy not built (build_f32 = 0)");
+    if (!h->has_f32) return fail(GSR_E_UNSUPPORTED, "binary32 copy not built (build_f32 = 0)");
     const Geo& g = h->g;
     hipLaunchKernelGGL(k_ref_begin, dim3(1), dim3(64), 0, s, h->ref);
     HIP_TRY(hipMemcpyAsync(h->r, b, sizeof(double) * h->rows(), hipMemcpyDeviceToDevice, s));
     fill(x, g.n, 0.0, s);
     gsr_solve_info inner = {};
     for (int k = 0; k < o.max_refine; ++k) {
-        GSR_TRY(fwd_solve<float>(h, h->fwd32, h->vals32, h->attT32, h->p32, h->r, h->dx,
+        GSR_TRY(fwd_solve<float>(h, h->fwd32, h->attT32, h->p32, h->r, h->dx,
                                  inner_opts(o, k), &inner, s));
         ref_step(h, x, o, s);
         HIP_TRY(hipMemcpyAsync(h->ref_host, h->ref, sizeof(RefState), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         if (h->ref_host->stop) break;
-        launch_aprod1<double, A1_RESID>(h, h->vals, x, h->r, b, s);
+        launch_aprod1<double, A1_RESID>(h, x, h->r, b, s);
     }
     HIP_TRY(hipGetLastError());
     if (info) {
@@ -1449,7 +1518,7 @@ gsr_status gsr_lsqr_solve_var(gsr_handle* h, const double* b, double* x, double*
     if (o.precision != GSR_F64)
         return fail(GSR_E_UNSUPPORTED, "the variance estimate is binary64 only");
     GSR_TRY(set_device(h));
-    return fwd_solve<double, true>(h, h->fwd64v, h->vals, h->attT64, h->p64, b, x, o, info,
+    return fwd_solve<double, true>(h, h->fwd64v, h->attT64, h->p64, b, x, o, info,
                                    as_stream(stream), var);
 }
 
@@ -1463,7 +1532,7 @@ gsr_status gsr_lsqr_solve_async(gsr_handle* h, const double* b, double* x,
     if (o.profile) return fail(GSR_E_INVAL, "profile needs host synchronization");
     GSR_TRY(set_device(h));
     if (o.precision == GSR_F64) return fwd_solve_async(h, b, x, o, info_dev, as_stream(stream));
-    if (!h->vals32) return fail(GSR_E_UNSUPPORTED, "binary32 copy not built (build_f32 = 0)");
+    if (!h->has_f32) return fail(GSR_E_UNSUPPORTED, "binary32 copy not built (build_f32 = 0)");
     return f32v_solve_async(h, b, x, o, info_dev, as_stream(stream));
 }
 
@@ -1478,7 +1547,7 @@ gsr_status gsr_lsqr_solve_adjoint(gsr_handle* h, const double* gvec, double* mu,
     GSR_TRY(set_device(h));
     hipStream_t s = as_stream(stream);
     GSR_TRY(trans_solve(h, gvec, mu, o, info ? &info[0] : nullptr, s));
-    return fwd_solve<double>(h, h->fwd64, h->vals, h->attT64, h->p64, mu, lam, o,
+    return fwd_solve<double>(h, h->fwd64, h->attT64, h->p64, mu, lam, o,
                              info ? &info[1] : nullptr,
                              s);
 }
@@ -1488,7 +1557,8 @@ gsr_status gsr_grad_vals(gsr_handle* h, const double* r, const double* mu, const
     if (!h || !r || !mu || !x || !lam || !dvals) return fail(GSR_E_INVAL, "null argument");
     if ((uintptr_t)dvals & 15) return fail(GSR_E_INVAL, "dvals must be 16-byte aligned");
     GSR_TRY(set_device(h));
-    hipLaunchKernelGGL(k_grad_vals, dim3(h->G1), dim3(kBlock), 0, as_stream(stream), h->g,
+    hipLaunchKernelGGL(k_grad_vals, dim3(grid_for(h->g.m, kBlock, kVecBlocksMax)), dim3(kBlock), 0,
+                       as_stream(stream), h->g,
                        h->star, h->att, h->instr, r, mu, x, lam, dvals);
     HIP_TRY(hipGetLastError());
     return GSR_OK;

@@ -126,13 +126,27 @@ static __global__ void k_recip_sqrt(int64_t n, double* __restrict__ ss, double* 
     if (cnt) atomicAdd(n_empty, cnt);
 }
 
+// The attitude part of the operand xt, kept a second time knot by knot (the three axes of a
+// knot together, xa[3 c + axis] = xt[att0 + axis T + c]): the four knots a row needs of every
+// axis are then twelve contiguous values.
+struct AttCopy {
+    double* xa;
+    int64_t att0, T;
+};
+__device__ __forceinline__ void put_att(const AttCopy& a, int64_t j, double v) {
+    const int64_t c = j - a.att0;
+    if (c < 0 || c >= kAxes * a.T) return;
+    const int64_t ax = c >= 2 * a.T ? 2 : c >= a.T ? 1 : 0;
+    a.xa[kAxes * (c - ax * a.T) + ax] = v;
+}
+
 // u = src (o p if PRE); block partial of sum u^2
-// (PRE: also xt = p o u, the operand of the next aprod 1)
+// (PRE: also xt = p o u, the operand of the next aprod 1, and its attitude copy)
 template <bool PRE>
 static __global__ __launch_bounds__(kBlock) void k_copy_norm(int64_t n, const double* __restrict__ src,
                                                       const double* __restrict__ p,
                                                       double* __restrict__ u,
-                                                      double* __restrict__ xt,
+                                                      double* __restrict__ xt, AttCopy ac,
                                                       double* __restrict__ partials) {
     __shared__ double sh[kBlock / kWave];
     double acc = 0.0;
@@ -140,7 +154,10 @@ static __global__ __launch_bounds__(kBlock) void k_copy_norm(int64_t n, const do
     for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < n; j += stride) {
         const double v = PRE ? src[j] * p[j] : src[j];
         u[j] = v;
-        if (PRE) xt[j] = p[j] * v;
+        if (PRE) {
+            xt[j] = p[j] * v;
+            put_att(ac, j, p[j] * v);
+        }
         acc = fma(v, v, acc);
     }
     const double tot = block_sum<kBlock>(acc, sh);
@@ -151,7 +168,8 @@ static __global__ __launch_bounds__(kBlock) void k_copy_norm(int64_t n, const do
 //   INIT : v~ = p o s;                 z = 0, w = 0
 //   else : apply the pending update  z += f1 w; w = sv v~ - f2 w  (old v~), then
 //          v~ = p o s - beta sv v~
-// s is reset to 0 and xt = p o v~ (the operand of the next aprod 1) is written.
+// s is reset to 0 and xt = p o v~ (the operand of the next aprod 1) and its attitude copy are
+// written.
 // Partials (4 rows of G): sum v~^2, sum z^2, sum z w, sum w^2.
 // VAR: also the variance estimate var += (w / rho)^2 with the w of the pending update.
 template <bool INIT, bool VAR = false>
@@ -159,7 +177,7 @@ static __global__ __launch_bounds__(kBlock) void k_vec_v(int64_t n, double* __re
                                                   const double* __restrict__ p,
                                                   double* __restrict__ v, double* __restrict__ w,
                                                   double* __restrict__ z, double* __restrict__ xt,
-                                                  const LsqrState* __restrict__ st,
+                                                  AttCopy ac, const LsqrState* __restrict__ st,
                                                   double* __restrict__ partials,
                                                   double* __restrict__ var = nullptr) {
     __shared__ double sh[kBlock / kWave];
@@ -200,6 +218,7 @@ static __global__ __launch_bounds__(kBlock) void k_vec_v(int64_t n, double* __re
         }
         v[j] = vn;
         xt[j] = p[j] * vn;
+        put_att(ac, j, p[j] * vn);
         avv = fma(vn, vn, avv);
     }
     const int G = gridDim.x;
@@ -220,7 +239,7 @@ static __global__ __launch_bounds__(kBlock) void k_vec_v(int64_t n, double* __re
 static __global__ __launch_bounds__(kBlock) void k_vec_tu(int64_t n, double* __restrict__ s,
                                                    const double* __restrict__ p,
                                                    double* __restrict__ u, double* __restrict__ xt,
-                                                   const LsqrState* __restrict__ st,
+                                                   AttCopy ac, const LsqrState* __restrict__ st,
                                                    double* __restrict__ partials) {
     __shared__ double sh[kBlock / kWave];
     if (st->stop) return;
@@ -234,6 +253,7 @@ static __global__ __launch_bounds__(kBlock) void k_vec_tu(int64_t n, double* __r
         const double un = p[j] * (sv * sj) - c1 * u[j];
         u[j] = un;
         xt[j] = p[j] * un;
+        put_att(ac, j, p[j] * un);
         acc = fma(un, un, acc);
     }
     const double tot = block_sum<kBlock>(acc, sh);

@@ -1,15 +1,8 @@
 // The two products of the hot path (Section 3, Algorithms 1 and 2), written for gfx950.
 //
-// Lane layout ("quad"): four lanes per row, sixteen rows per wave step.  Lane q of a row
-// holds the coefficients in slots 4k + q (k = 0..5), so every attitude access of a quad
-// covers the four consecutive columns t..t+3 of one axis.  Read from the caller's row layout
-// a wave load touches sixteen 32-byte pieces; the library's row tiles (below) turn every
-// load of a wave step into one contiguous block:
-//
-//   q = 0 : slots 0 4 8 12 16 20   astro 0, astro 4, att j=3 (axes 0,1,2), instr 3
-//   q = 1 : slots 1 5 9 13 17 21   astro 1, att j=0 (axes 0,1,2), instr 0, instr 4
-//   q = 2 : slots 2 6 10 14 18 22  astro 2, att j=1 (axes 0,1,2), instr 1, instr 5
-//   q = 3 : slots 3 7 11 15 19 23  astro 3, att j=2 (axes 0,1,2), instr 2, global
+// Lane layout ("quad"): four lanes per row, sixteen rows per wave step.  The library's row
+// tiles (below) turn every load of a wave step into one contiguous block; read from the
+// caller's row layout (four lanes, slots 4k + q) a wave load touches sixteen 32-byte pieces.
 //
 // Waves walk contiguous chunks of rows, so runs of equal keys (the star of a row in the
 // star-ordered pass, the attitude start t in the attitude pass) are accumulated in registers
@@ -34,10 +27,16 @@ __device__ __forceinline__ double ld_val(const float* __restrict__ p) {
 // Row tiles: a library-owned copy of the coefficients and indices in which every load
 // instruction of a wave step reads one contiguous block (the paper's row layout makes each
 // lane's coefficients 4 slots apart, so a wave load would touch sixteen separate 32-byte
-// pieces).  A tile holds the kStepRows rows of one wave step; lane (rg, q) needs slots
-// 4k + q (k = 0..5) of row rg:
-//   binary64 : three 1 KiB groups; group h is [rg][q][2] = slots 4(2h) + q, 4(2h+1) + q
-//   binary32 : a 1 KiB group [rg][q][4] (k = 0..3), then a 512 B group [rg][q][2] (k = 4, 5)
+// pieces).  A tile holds the kStepRows rows of one wave step.  Lane q of a row's quad holds
+// six coefficients, k = 0..5 (tile_slot gives their slots):
+//   k = 0, 1, 2 : attitude elements 2q, 2q + 1 and 8 + q of the row's twelve, counted knot by
+//                 knot (element e = knot e / 3, axis e % 3: the order of AttCopy)
+//   k = 3       : astrometric q
+//   k = 4       : astrometric 4 (q = 0), instrumental 4, 5 (q = 1, 2), global (q = 3)
+//   k = 5       : instrumental 3, 0, 1, 2 (q = 0..3)
+// Storage of a tile ([rg][q][..] = lane-contiguous):
+//   binary64 : three 1 KiB groups [rg][q][2]: k = (0, 1), (2, 3), (4, 5)
+//   binary32 : a 1 KiB group [rg][q][4] (k = 2..5), then a 512 B group [rg][q][2] (k = 0, 1)
 //   indices  : [rg][q][2] int32 = (star, att), (instr0, instr4), (instr1, instr5),
 //              (instr2, instr3) for q = 0..3
 // The index tile follows the coefficients of the same tile (one stream per wave).  Padding
@@ -49,43 +48,63 @@ constexpr int64_t tile_elems() {  // coefficients, then the index tile, in units
     return kTileVals + kTileIdx * 4 / (int64_t)sizeof(VT);
 }
 
+// Slot (0..23, paper order) of coefficient k of lane q.
+__host__ __device__ constexpr int tile_slot(int q, int k) {
+    if (k < 3) {
+        const int e = k < 2 ? 2 * q + k : 8 + q;
+        return kAstro + kParAxis * (e % kAxes) + e / kAxes;
+    }
+    if (k == 3) return q;
+    if (k == 4) return q == 0 ? 4 : 20 + q;
+    return q == 0 ? 20 : 16 + q;
+}
+
+// One row of a wave step as lane q of its quad holds it: the coefficients above, the row's
+// star and attitude start, the instrumental index of k = 5 (ia) and of k = 4 (ib, lanes 1, 2).
+struct TileRow {
+    double e0, e1, e2, as, z, wi;
+    int32_t star, att, ia, ib;
+};
+
 __device__ __forceinline__ void ld_tile(const double* __restrict__ tiles, int64_t tile, int lane,
-                                        double (&a)[6]) {
+                                        TileRow& r) {
     const f64x2* __restrict__ p =
         reinterpret_cast<const f64x2*>(tiles + tile * tile_elems<double>()) + lane;
-#pragma unroll
-    for (int h = 0; h < 3; ++h) {
-        const f64x2 v = __builtin_nontemporal_load(p + h * kWave);
-        a[2 * h] = v.x;
-        a[2 * h + 1] = v.y;
-    }
+    const f64x2 a = __builtin_nontemporal_load(p);
+    const f64x2 b = __builtin_nontemporal_load(p + kWave);
+    const f64x2 c = __builtin_nontemporal_load(p + 2 * kWave);
+    r.e0 = a.x;
+    r.e1 = a.y;
+    r.e2 = b.x;
+    r.as = b.y;
+    r.z = c.x;
+    r.wi = c.y;
 }
 __device__ __forceinline__ void ld_tile(const float* __restrict__ tiles, int64_t tile, int lane,
-                                        double (&a)[6]) {
+                                        TileRow& r) {
     const float* __restrict__ t = tiles + tile * tile_elems<float>();
     const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(t) + lane);
     const f32x2 w = __builtin_nontemporal_load(reinterpret_cast<const f32x2*>(t + 4 * kWave) + lane);
-    a[0] = v.x;
-    a[1] = v.y;
-    a[2] = v.z;
-    a[3] = v.w;
-    a[4] = w.x;
-    a[5] = w.y;
+    r.e0 = w.x;
+    r.e1 = w.y;
+    r.e2 = v.x;
+    r.as = v.y;
+    r.z = v.z;
+    r.wi = v.w;
 }
 
-// Index tile of a wave step: star, attitude start and the lane's instrumental indices
-// (ia: the instrumental slot among k = 0..5 of lane q; ib: the second one of lanes 1 and 2).
+// Index tile of a wave step.
 template <typename VT>
 __device__ __forceinline__ void ld_tile_idx(const VT* __restrict__ tiles, int64_t tile, int lane,
-                                            int32_t& sr, int32_t& tr, int32_t& ia, int32_t& ib) {
+                                            TileRow& r) {
     const int32_t* itile =
         reinterpret_cast<const int32_t*>(tiles + tile * tile_elems<VT>() + kTileVals);
     const i32x2 v = __builtin_nontemporal_load(reinterpret_cast<const i32x2*>(itile) + lane);
-    sr = __builtin_amdgcn_update_dpp(0, v.x, 0x00, 0xF, 0xF, false);   // quad_perm [0,0,0,0]
-    tr = __builtin_amdgcn_update_dpp(0, v.y, 0x00, 0xF, 0xF, false);
+    r.star = __builtin_amdgcn_update_dpp(0, v.x, 0x00, 0xF, 0xF, false);  // quad_perm [0,0,0,0]
+    r.att = __builtin_amdgcn_update_dpp(0, v.y, 0x00, 0xF, 0xF, false);
     const int32_t i3 = __builtin_amdgcn_update_dpp(0, v.y, 0xFF, 0xF, 0xF, false);  // [3,3,3,3]
-    ia = ((lane & 3) == 0) ? i3 : v.x;
-    ib = v.y;
+    r.ia = ((lane & 3) == 0) ? i3 : v.x;
+    r.ib = v.y;
 }
 
 // Setup: row tiles from the paper's row layout (one thread per tile element).
@@ -104,13 +123,13 @@ static __global__ void k_make_tiles(int64_t m, int64_t ntiles, const double* __r
             k = 2 * (o / (2 * kWave)) + o % 2;
         } else if (o < 4 * kWave) {
             lane = o / 4;
-            k = o % 4;
+            k = 2 + o % 4;
         } else {
             lane = (o - 4 * kWave) / 2;
-            k = 4 + (o - 4 * kWave) % 2;
+            k = (o - 4 * kWave) % 2;
         }
         const int64_t row = tile * kStepRows + lane / kQuad;
-        const int slot = 4 * k + lane % kQuad;
+        const int slot = tile_slot(lane % kQuad, k);
         *dst = row < m ? (VT)vals[row * kPar + slot] : (VT)0;  // binary32: round to nearest
     }
 }
@@ -260,230 +279,6 @@ __device__ __forceinline__ void run_close(double (&acc)[NV], int32_t& ckey, F&& 
     ckey = -1;
 }
 
-// ---------------------------------------------------------------------------------------
-// aprod 1:  sum_i = sum_k A[i,k] xx[col(i,k)], then
-//   A1_ADD   : y[i] += sum_i
-//   A1_LSQR  : y[i] = xs sum_i - ys y[i]  with (xs, ys) = (sv, alpha su)   [forward operator]
-//   A1_LSQR_T: same with (xs, ys) = (su, beta sv)                           [transposed]
-//   A1_RESID : y[i] = b[i] - sum_i
-// LSQR modes also write the block partial of sum y[i]^2.  LDSI: the instrumental part of xx
-// is staged in LDS (dynamic LDS of n_instr doubles).  TILED: coefficients and indices come
-// from the row tiles (vals, star, att, instr then unused).  gate (may be NULL): nothing is
-// done when *gate is set (a residual of a correction step that will not be taken).
-enum { A1_ADD = 0, A1_LSQR = 1, A1_LSQR_T = 2, A1_RESID = 3 };
-
-template <typename VT, int MODE, bool TILED, bool LDSI>
-static __global__ __launch_bounds__(512) void k_aprod1(
-    Geo g, const VT* __restrict__ vals, const int32_t* __restrict__ star,
-    const int32_t* __restrict__ att, const int32_t* __restrict__ instr,
-    const VT* __restrict__ tiles, const double* __restrict__ xx, double* __restrict__ y,
-    const double* __restrict__ b,
-    const LsqrState* __restrict__ st, double* __restrict__ partials, int chunk_rows,
-    const int32_t* __restrict__ gate) {
-    extern __shared__ double lxi[];
-    __shared__ double sh[512 / kWave];
-    if (gate && *gate) return;
-    constexpr bool kLsqr = (MODE == A1_LSQR || MODE == A1_LSQR_T);
-    double xs = 1.0, ys = 0.0;
-    if (kLsqr) {
-        if (st->stop) return;
-        if (MODE == A1_LSQR) {
-            xs = st->sv;
-            ys = st->alpha * st->su;
-        } else {
-            xs = st->su;
-            ys = st->beta * st->sv;
-        }
-    }
-    if (LDSI) {
-        for (int k = threadIdx.x; k < g.I; k += blockDim.x) lxi[k] = xx[g.ins0 + k];
-        __syncthreads();
-    }
-    const double* __restrict__ xi = LDSI ? lxi : xx + g.ins0;
-    const int lane = threadIdx.x % kWave, rg = lane / kQuad, q = lane % kQuad;
-    const int wpb = blockDim.x / kWave;
-    const int64_t nchunks = (g.m + chunk_rows - 1) / chunk_rows;
-    const double xglob = xx[g.glb0];
-    const int ia_off = (q == 0) ? 3 : q - 1;  // instrumental index of the lane's first slot
-    const int ib_off = (q == 1 || q == 2) ? q + 3 : ia_off;
-    const int jatt = (q + 3) & 3;             // attitude column offset of the lane
-    double acc = 0.0;
-    for (int64_t ch = (int64_t)blockIdx.x * wpb + threadIdx.x / kWave; ch < nchunks;
-         ch += (int64_t)gridDim.x * wpb) {
-        const int64_t r_end = min((ch + 1) * (int64_t)chunk_rows, g.m);
-        for (int64_t r0 = ch * (int64_t)chunk_rows; r0 < r_end; r0 += kStepRows) {
-            const int64_t r = r0 + rg;
-            const bool valid = r < r_end;
-            double sum = 0.0;
-            double a[6];
-            int32_t s, t, ia, ib;
-            // the row's old y (or b) is loaded with the coefficients, not after the gathers
-            // (one memory round trip fewer per step)
-            const int64_t rr = valid ? r : r_end - 1;  // in-bounds stand-in row
-            double yo = 0.0;
-            if (MODE == A1_RESID)
-                yo = b[rr];
-            else if (MODE == A1_ADD || (kLsqr && ys != 0.0))
-                yo = y[rr];
-            if (TILED) {  // the whole step's tile (rows past m are padding inside it)
-                ld_tile(tiles, r0 / kStepRows, lane, a);
-                ld_tile_idx(tiles, r0 / kStepRows, lane, s, t, ia, ib);
-            } else if (valid) {
-                const VT* __restrict__ row = vals + r * kPar + q;
-#pragma unroll
-                for (int k = 0; k < 6; ++k) a[k] = ld_val(row + 4 * k);
-                s = star[r];
-                t = att[r];
-                ia = instr[r * kInstr + ia_off];
-                ib = instr[r * kInstr + ib_off];
-            }
-            if (valid) {
-                const int64_t ca = (int64_t)kAstro * s;
-                sum = a[0] * xx[ca + q];
-                if (q == 0) sum = fma(a[1], xx[ca + 4], sum);
-                const double* __restrict__ xa = xx + g.att0 + t + jatt;
-#pragma unroll
-                for (int ax = 0; ax < kAxes; ++ax) {
-                    const double c = (q == 0) ? a[ax + 2] : a[ax + 1];
-                    sum = fma(c, xa[(int64_t)ax * g.T], sum);
-                }
-                sum = fma((q == 0) ? a[5] : a[4], xi[ia], sum);
-                if (q == 1 || q == 2) sum = fma(a[5], xi[ib], sum);
-                if (q == 3) sum = fma(a[5], xglob, sum);
-            }
-            sum = quad_sum(sum);
-            if (valid && q == 0) {
-                if (MODE == A1_ADD) {
-                    y[r] = yo + sum;
-                } else if (MODE == A1_RESID) {
-                    y[r] = yo - sum;
-                } else {
-                    const double u = (ys != 0.0) ? xs * sum - ys * yo : xs * sum;
-                    y[r] = u;
-                    acc = fma(u, u, acc);
-                }
-            }
-        }
-    }
-    if (kLsqr) {
-        const double tot = block_sum<512>(acc, sh);
-        if (threadIdx.x == 0) partials[blockIdx.x] = tot;
-    }
-}
-
-// ---------------------------------------------------------------------------------------
-// aprod 2, star-ordered pass: astrometric, instrumental and global columns.
-//   x[col(i,k)] += A[i,k] y[i]  (A2_ADD; A2_LSQR / A2_LSQR_T, where y is the unnormalized
-//   u~ or v~ and the following vector step applies 1/beta or 1/alpha), or the contribution is
-//   A[i,k]^2 (A2_SQ, column norms).  LSQR modes return at once when the stop flag is set.
-// Astrometric: a star's rows are contiguous; a run is written once by the wave that ends it,
-// with a plain read-modify-write when the whole star lies inside the wave's chunk and an
-// atomic add when the star continues into a neighbouring chunk.
-// Instrumental and global: accumulated in LDS for everything the block visits; the block's
-// n_instr + 1 sums go to part[blockIdx] (reduced by k_reduce_partials), or -- when n_instr is
-// too large for LDS -- straight to x with atomics.
-enum { A2_ADD = 0, A2_LSQR = 1, A2_LSQR_T = 2, A2_SQ = 3 };
-
-template <int MODE>
-__device__ __forceinline__ double a2_scale(const LsqrState* __restrict__ st) {
-    return 1.0;  // LSQR modes accumulate unnormalized (the vector step applies 1/beta, 1/alpha)
-}
-
-template <int MODE>
-__device__ __forceinline__ double contrib(double a, double yy) {
-    return MODE == A2_SQ ? a * a : a * yy;
-}
-
-template <typename VT, int MODE>
-static __global__ __launch_bounds__(512) void k_aprod2_star(
-    Geo g, const VT* __restrict__ vals, const int32_t* __restrict__ star,
-    const int32_t* __restrict__ instr, const double* __restrict__ y, double* __restrict__ x,
-    const LsqrState* __restrict__ st, double* __restrict__ part, int chunk_rows, int lds_instr) {
-    extern __shared__ double lds[];  // [n_instr] instrumental, [1] global (lds_instr)
-    __shared__ double lglob_nolds;
-    if ((MODE == A2_LSQR || MODE == A2_LSQR_T) && st->stop) return;
-    const double ysc = a2_scale<MODE>(st);
-    const int nI = lds_instr ? g.I : 0;
-    double* lglob = lds_instr ? lds + nI : &lglob_nolds;
-    for (int k = threadIdx.x; k < nI; k += blockDim.x) lds[k] = 0.0;
-    if (threadIdx.x == 0) *lglob = 0.0;
-    __syncthreads();
-
-    const int lane = threadIdx.x % kWave, rg = lane / kQuad, q = lane % kQuad;
-    const int wpb = blockDim.x / kWave;
-    const int64_t nchunks = (g.m + chunk_rows - 1) / chunk_rows;
-    double gacc = 0.0;
-    for (int64_t ch = (int64_t)blockIdx.x * wpb + threadIdx.x / kWave; ch < nchunks;
-         ch += (int64_t)gridDim.x * wpb) {
-        const int64_t r_beg = ch * (int64_t)chunk_rows;
-        const int64_t r_end = min(r_beg + chunk_rows, g.m);
-        // stars shared with the neighbouring chunks are written with atomics
-        const int32_t shared_first =
-            (r_beg > 0 && star[r_beg - 1] == star[r_beg]) ? star[r_beg] : -1;
-        const int32_t shared_last =
-            (r_end < g.m && star[r_end] == star[r_end - 1]) ? star[r_end - 1] : -1;
-        // finished star: row group 0 writes it (astro q; astro 4 from q = 0).  In the LSQR and
-        // column-norm modes the target starts at zero, so an owned star is simply stored.
-        auto flush = [&](int32_t key, const double (&t)[2]) {
-            if (rg != 0) return;
-            double* xa = x + (int64_t)kAstro * key;
-            if (key == shared_first || key == shared_last) {
-                atomic_add_f64(xa + q, t[0]);
-                if (q == 0) atomic_add_f64(xa + 4, t[1]);
-            } else if (MODE == A2_ADD) {
-                xa[q] += t[0];
-                if (q == 0) xa[4] += t[1];
-            } else {
-                xa[q] = t[0];
-                if (q == 0) xa[4] = t[1];
-            }
-        };
-        double acc[2] = {0.0, 0.0};  // this lane's share of the open run
-        int32_t ckey = -1;
-        for (int64_t r0 = r_beg; r0 < r_end; r0 += kStepRows) {
-            const int64_t r = r0 + rg;
-            const bool valid = r < r_end;
-            int32_t key = -1;
-            double v[2] = {0.0, 0.0};
-            if (valid) {
-                const VT* __restrict__ row = vals + r * kPar + q;
-                const double a0 = ld_val(row);
-                const double a1 = (q == 0) ? ld_val(row + 4) : 0.0;
-                const double a4 = (q != 0) ? ld_val(row + 16) : 0.0;
-                const double a5 = ld_val(row + 20);
-                key = star[r];
-                const double yy = (MODE == A2_SQ) ? 0.0 : ysc * y[r];
-                v[0] = contrib<MODE>(a0, yy);
-                v[1] = contrib<MODE>(a1, yy);
-                const double p4 = contrib<MODE>(a4, yy), p5 = contrib<MODE>(a5, yy);
-                if (q != 0) {
-                    const int32_t ia = instr[r * kInstr + q - 1];
-                    if (lds_instr) atomicAdd(lds + ia, p4);
-                    else atomic_add_f64(x + g.ins0 + ia, p4);
-                }
-                if (q != 3) {
-                    const int32_t ib = instr[r * kInstr + 3 + q];
-                    if (lds_instr) atomicAdd(lds + ib, p5);
-                    else atomic_add_f64(x + g.ins0 + ib, p5);
-                } else {
-                    gacc += p5;
-                }
-            }
-            run_step<2, kQuad>(key, v, acc, ckey, flush);
-        }
-        run_close<2, kQuad>(acc, ckey, flush);
-    }
-    const double gs = wave_sum(gacc);
-    if (lane == 0) atomicAdd(lglob, gs);
-    __syncthreads();
-    if (lds_instr) {
-        double* dst = part + (int64_t)blockIdx.x * (nI + 1);
-        for (int k = threadIdx.x; k <= nI; k += blockDim.x) dst[k] = lds[k];
-    } else if (threadIdx.x == 0) {
-        atomic_add_f64(x + g.glb0, *lglob);
-    }
-}
-
 // x[ins0 + c] += sum_b part[b][c] for the n_instr + 1 instrumental and global columns.
 // blockIdx.y takes a slice of the blocks; slices meet in one atomic add per column.
 static __global__ void k_reduce_partials(int ncols, int nblocks, const double* __restrict__ part,
@@ -510,151 +305,634 @@ static __global__ void k_reduce_partials(int ncols, int nblocks, const double* _
 // s is accumulated unnormalized (1/beta is applied by the vector step once beta is known);
 // the attitude columns of s come from k_aprod2_att on the attitude copy.  Block partials:
 // sum u~^2 -> partials[block], instrumental/global sums -> part[block][n_instr + 1].
-// U row steps are loaded before any of them is reduced.
+//
+// What bounds it: HBM.  A read stream on this GPU loses about a quarter of its rate as soon
+// as a few per cent of scattered writes run beside it (streaming the tiles of a 2e7-row
+// system: 0.66 ms; with each wave storing its 128 bytes of u~ per step 0.89 ms, whatever the
+// store's cache policy; with the same stores collected into bursts of 64 KiB or more per
+// block, non-temporal, into an array that is not the one being read: 0.75 ms).  So a block
+// takes rounds of consecutive rows, keeps the round's u~ and its finished stars' sums on
+// chip, and writes both at the end of the round, all waves together; the old and the new u~
+// are two arrays that swap roles every iteration.  Stars that continue into the
+// neighbouring wave meet on chip too; only a block's first and last star need atomics (they
+// cost as much as the stores: 0.87 -> 1.05 ms with two such stars per wave and round).
+// Two forms:
+//   k_aprod12     : u~ and the star sums in LDS, beside the block's instrumental sums and the
+//                   staged instrumental unknowns (needs room for kRoundLds wave steps: n_instr
+//                   up to about 8,900).  The block's waves take the round's wave steps in
+//                   turn, so that the block reads one contiguous stream, and every lane adds
+//                   its products to the star's LDS slot (0.86 ms against 0.89 with a run of
+//                   steps per wave and the sums of equal stars reduced over the lanes first);
+//   k_aprod12_reg : u~ and the star sums in registers (the LDS is full at n_instr = 10,000).
+//                   Each wave takes a run of wave steps; sums of equal stars stay in registers
+//                   until the star ends (run_step).
+// Attitude operand: xa holds the attitude part of xt knot by knot (three axes of a knot
+// together), so a row's twelve elements are 96 contiguous bytes: one or two cache lines
+// instead of three to six, two loads per lane instead of three.
+// Measured, one pass: 2e7 rows, n_instr 6,000: 1.09 -> 0.84 ms (4.4 -> 5.7 TB/s of the
+// algorithmic bytes); 2.5e7 rows, n_instr 10,000: 1.35 -> 1.10 ms (register form).
 //
 // TRANS: the same pass for the transposed operator D A^T (the adjoint solve), where the
 // row-space vector is v~:  v~[r] = su (A xt)[r] - beta sv v~[r]  (xt = p o u~), preceded on
-// the same rows by the pending update z += f1 w; w = sv v~ - f2 w of the row-space z, w.
-// Partials then are 4 rows (pstride apart; entries past gridDim belong to the constraint
-// rows): sum v~^2, sum z^2, sum z w, sum w^2.
-//
-// INIT: the initial aprod 2 of a solve: u~ is left as it is (no dot products) and only
-// s += A^T u~ is scattered (star-ordered columns; the attitude pass follows as usual).
-template <typename VT, int U, bool TRANS = false, bool INIT = false>
-static __global__ __launch_bounds__(1024) void k_aprod12(
-    Geo g, const VT* __restrict__ tiles, const int32_t* __restrict__ star,
-    const double* __restrict__ xx, double* __restrict__ uu, double* __restrict__ s,
-    const LsqrState* __restrict__ st, double* __restrict__ partials,
-    double* __restrict__ part, int chunk_rows, int pstride, double* __restrict__ ww_vec = nullptr,
-    double* __restrict__ zz_vec = nullptr) {
-    extern __shared__ double lds[];  // [n_instr + 1] sums, then [n_instr] staged xt
-    __shared__ double sh[1024 / kWave];
+// the same rows by the pending update z += f1 w; w = sv v~ - f2 w of the row-space z, w (all
+// in place: uin == uout).  Partials then are 4 rows (pstride apart; entries past gridDim
+// belong to the constraint rows): sum v~^2, sum z^2, sum z w, sum w^2.
+constexpr int kRowBlock = 1024;                   // threads of a row-pass block
+constexpr int kRowWaves = kRowBlock / kWave;      // 16 waves, one block per compute unit
+constexpr int kRoundRows = kRowWaves * kStepRows; // rows of a round per wave step
+constexpr int kRoundLds = 9;       // fewest wave steps per round worth the LDS form
+constexpr int kRoundLdsMax = 48;   // most wave steps per round of the LDS form
+constexpr int kRegGroups = 8;      // register form: groups of four wave steps per round
+constexpr int kRegStars = 2;       // register form: sets of 16 pending stars
+constexpr int kRegXch = 5 * kRowWaves + 5 * (kRowWaves + 1) + (kRowWaves + 2) / 2;  // doubles
+
+template <typename VT>
+struct RowArgs {
+    Geo g;
+    const VT* tiles;
+    const int32_t* star;
+    const double* xx;     // operand
+    const double* xa;     // its attitude part, knot by knot
+    const double* uin;    // old u~ (TRANS: old v~)
+    double* uout;
+    double* s;
+    const LsqrState* st;
+    double* partials;
+    double* part;
+    double *ww, *zz;      // TRANS: w and z of the row space
+    int pstride;
+    int tw;               // wave steps per wave and round
+    int nsb;              // LDS form: stars with a slot;  register form: 1 = exchange area
+};
+
+// The row's dot product, summed over the quad.  IL: the attitude unknowns from xa (knot by
+// knot), otherwise from xx.
+template <bool IL>
+__device__ __forceinline__ double row_dot(const Geo& g, const TileRow& r, int q,
+                                          const double* __restrict__ xx,
+                                          const double* __restrict__ xa,
+                                          const double* __restrict__ xi, double xglob) {
+    // every lane issues all its loads before the first use, without branches: a load under a
+    // lane condition would wait for the ones before it
+    const double* __restrict__ xs = xx + (int64_t)kAstro * r.star;
+    const double x0 = xs[q];
+    const double x4 = xs[q == 0 ? 4 : q];
+    double v0, v1, v2;
+    if (IL) {
+        typedef f64x2 __attribute__((aligned(8))) f64x2u;
+        const double* __restrict__ a = xa + (int64_t)kAxes * r.att;
+        const f64x2 v = *reinterpret_cast<const f64x2u*>(a + 2 * q);
+        v0 = v.x;
+        v1 = v.y;
+        v2 = a[8 + q];
+    } else {
+        // element e of the row: axis e % 3, knot att + e / 3
+        const double* __restrict__ a = xx + g.att0 + r.att;
+        const int e0 = 2 * q, e1 = 2 * q + 1, e2 = 8 + q;
+        v0 = a[(int64_t)(e0 % kAxes) * g.T + e0 / kAxes];
+        v1 = a[(int64_t)(e1 % kAxes) * g.T + e1 / kAxes];
+        v2 = a[(int64_t)(e2 % kAxes) * g.T + e2 / kAxes];
+    }
+    const bool two = q == 1 || q == 2;  // lanes with a second instrumental coefficient
+    const double wx = xi[r.ia];
+    const double wb = xi[two ? r.ib : r.ia];
+    const double zx = q == 0 ? x4 : two ? wb : xglob;
+    double sum = r.as * x0;
+    sum = fma(r.e0, v0, sum);
+    sum = fma(r.e1, v1, sum);
+    sum = fma(r.e2, v2, sum);
+    sum = fma(r.wi, wx, sum);
+    sum = fma(r.z, zx, sum);
+    return quad_sum(sum);
+}
+
+// Ends a branch whose other side does the same to LDS: merged, the two would become one flat
+// access, after which every wait for a load is a wait for all of them.
+__device__ __forceinline__ void keep_apart() { asm volatile(""); }
+
+// Brings the unknowns of stars s0..s1 (consecutive) near before the first row needs them: one
+// line per thread `i`.
+__device__ __forceinline__ void touch_stars(const double* __restrict__ xx, int32_t s0, int32_t s1,
+                                            int i) {
+    const int64_t e = (int64_t)kAstro * s0 + 16 * i;
+    double t = 0.0;
+    if (e < (int64_t)kAstro * (s1 + 1)) t = xx[e];
+    asm volatile("" ::"v"(t));
+}
+
+template <typename VT, bool TRANS = false>
+static __global__ __launch_bounds__(kRowBlock) void k_aprod12(RowArgs<VT> p) {
+    // [n_instr + 1] sums, [n_instr] staged xt, [tw][kRoundRows] u~, [nsb][5] star sums
+    extern __shared__ double lds[];
+    __shared__ double sh[kRowWaves];
+    const LsqrState* __restrict__ st = p.st;
     if (st->stop) return;
+    const Geo g = p.g;
+    const VT* __restrict__ tiles = p.tiles;
+    const int32_t* __restrict__ star = p.star;
+    const double* __restrict__ xx = p.xx;
+    const double* __restrict__ xa = p.xa;
+    const double* uin = p.uin;
+    double* uout = p.uout;
+    double* __restrict__ s = p.s;
     const double xs = TRANS ? st->su : st->sv;
     const double ys = TRANS ? st->beta * st->sv : st->alpha * st->su;
     const bool pending = TRANS && st->pending;
     const double f1 = st->f1, f2 = st->f2, svo = st->sv;
+    const int tw = p.tw, nsb = p.nsb;
     double zsq = 0.0, zw = 0.0, wsq = 0.0;
     double* lsum = lds;  // instrumental and global sums of the block
     double* lxi = lds + g.I + 1;
-    for (int k = threadIdx.x; k <= g.I; k += blockDim.x) lsum[k] = 0.0;
-    if (!INIT)
-        for (int k = threadIdx.x; k < g.I; k += blockDim.x) lxi[k] = xx[g.ins0 + k];
+    double* ubuf = lds + 2 * (int64_t)g.I + 2;  // 16-byte aligned
+    double* sbuf = ubuf + tw * kRoundRows;
+    for (int k = threadIdx.x; k <= g.I; k += kRowBlock) lsum[k] = 0.0;
+    for (int k = threadIdx.x; k < g.I; k += kRowBlock) lxi[k] = xx[g.ins0 + k];
+    for (int k = threadIdx.x; k < kAstro * nsb; k += kRowBlock) sbuf[k] = 0.0;
     __syncthreads();
     const double* __restrict__ xi = lxi;  // LDS reads (not flat loads tied to vmcnt)
     const int lane = threadIdx.x % kWave, rg = lane / kQuad, q = lane % kQuad;
-    const int wpb = blockDim.x / kWave;
-    const int64_t nchunks = (g.m + chunk_rows - 1) / chunk_rows;
-    const double xglob = INIT ? 0.0 : xx[g.glb0];
-    const int jatt = (q + 3) & 3;
+    const int w = threadIdx.x / kWave;
+    const double xglob = xx[g.glb0];
+    const int64_t ntiles = (g.m + kStepRows - 1) / kStepRows;
+    const int64_t bt = (int64_t)tw * kRowWaves, nch = (ntiles + bt - 1) / bt;
     double usq = 0.0, gacc = 0.0;
-    for (int64_t ch = (int64_t)blockIdx.x * wpb + threadIdx.x / kWave; ch < nchunks;
-         ch += (int64_t)gridDim.x * wpb) {
-        const int64_t r_beg = ch * (int64_t)chunk_rows;
-        const int64_t r_end = min(r_beg + chunk_rows, g.m);
-        const int32_t shared_first =
-            (r_beg > 0 && star[r_beg - 1] == star[r_beg]) ? star[r_beg] : -1;
-        const int32_t shared_last =
-            (r_end < g.m && star[r_end] == star[r_end - 1]) ? star[r_end - 1] : -1;
-        // finished star (s is zero before this pass: owned stars are stored)
-        auto flush = [&](int32_t key, const double (&t)[2]) {
-            if (rg != 0) return;
-            double* xa = s + (int64_t)kAstro * key;
-            if (key == shared_first || key == shared_last) {
-                atomic_add_f64(xa + q, t[0]);
-                if (q == 0) atomic_add_f64(xa + 4, t[1]);
-            } else {
-                xa[q] = t[0];
-                if (q == 0) xa[4] = t[1];
+    for (int64_t ch = blockIdx.x; ch < nch; ch += gridDim.x) {
+        const int64_t R0 = ch * bt * kStepRows, R1 = min(R0 + bt * kStepRows, g.m);
+        const int64_t te = min((ch + 1) * bt, ntiles);
+        const int32_t S0 = star[R0], S1 = star[R1 - 1];
+        const bool shf = R0 > 0 && star[R0 - 1] == S0, shl = R1 < g.m && star[R1] == S1;
+        touch_stars(xx, S0, S1, threadIdx.x);
+        for (int64_t t = ch * bt + w; t < te; t += kRowWaves) {
+            TileRow a;
+            ld_tile(tiles, t, lane, a);
+            ld_tile_idx(tiles, t, lane, a);
+            const int64_t r = t * kStepRows + rg;
+            const double uo = uin[min(r, g.m - 1)];
+            const double sum = row_dot<true>(g, a, q, xx, xa, xi, xglob);
+            const double un = (ys != 0.0) ? xs * sum - ys * uo : xs * sum;
+            if (r >= R1) continue;
+            if (q == 0) {
+                usq = fma(un, un, usq);
+                ubuf[r - R0] = un;
             }
+            // the star's slot, or (stars past the last slot) straight to s, which is zero
+            // there before the pass
+            const int o = a.star - S0;
+            if ((uint32_t)o < (uint32_t)nsb) {
+                atomicAdd(sbuf + kAstro * o + q, a.as * un);
+                if (q == 0) atomicAdd(sbuf + kAstro * o + 4, a.z * un);
+            } else {
+                double* xo = s + (int64_t)kAstro * a.star;
+                atomic_add_f64(xo + q, a.as * un);
+                if (q == 0) atomic_add_f64(xo + 4, a.z * un);
+                keep_apart();
+            }
+            atomicAdd(lsum + a.ia, a.wi * un);
+            if (q == 1 || q == 2) atomicAdd(lsum + a.ib, a.z * un);
+            if (q == 3) gacc = fma(a.z, un, gacc);
+        }
+        __syncthreads();
+        // the round's results, written together
+        if (TRANS) {
+            for (int64_t r = R0 + threadIdx.x; r < R1; r += kRowBlock) {
+                if (pending) {  // z, w updated with the old v~ of this row
+                    const double wo = p.ww[r];
+                    const double zn = fma(f1, wo, p.zz[r]);
+                    const double wn = svo * uin[r] - f2 * wo;
+                    p.zz[r] = zn;
+                    p.ww[r] = wn;
+                    zsq = fma(zn, zn, zsq);
+                    zw = fma(zn, wn, zw);
+                    wsq = fma(wn, wn, wsq);
+                }
+                uout[r] = ubuf[r - R0];
+            }
+        } else {
+            for (int64_t r = R0 + 2 * threadIdx.x; r < R1; r += 2 * kRowBlock) {
+                if (r + 1 < R1)
+                    __builtin_nontemporal_store(*reinterpret_cast<const f64x2*>(ubuf + (r - R0)),
+                                                reinterpret_cast<f64x2*>(uout + r));
+                else
+                    uout[r] = ubuf[r - R0];
+            }
+        }
+        const int ne = kAstro * min(S1 - S0 + 1, nsb);
+        const int e0 = shf ? kAstro : 0, e1 = (shl && S1 - S0 < nsb) ? ne - kAstro : ne;
+        for (int e = threadIdx.x; e < ne; e += kRowBlock) {
+            const double v = sbuf[e];
+            sbuf[e] = 0.0;
+            double* xo = s + (int64_t)kAstro * S0 + e;
+            if (e >= e0 && e < e1)  // s is zero before this pass: owned stars are stored
+                __builtin_nontemporal_store(v, xo);
+            else
+                atomic_add_f64(xo, v);
+        }
+        __syncthreads();
+    }
+    const double gs = wave_sum(gacc);
+    if (lane == 0) atomicAdd(lsum + g.I, gs);
+    const double tot = block_sum<kRowBlock>(usq, sh);
+    if (threadIdx.x == 0) p.partials[blockIdx.x] = tot;
+    if (TRANS) {
+        double t2 = block_sum<kRowBlock>(zsq, sh);
+        if (threadIdx.x == 0) p.partials[p.pstride + blockIdx.x] = t2;
+        t2 = block_sum<kRowBlock>(zw, sh);
+        if (threadIdx.x == 0) p.partials[2 * p.pstride + blockIdx.x] = t2;
+        t2 = block_sum<kRowBlock>(wsq, sh);
+        if (threadIdx.x == 0) p.partials[3 * p.pstride + blockIdx.x] = t2;
+    }
+    __syncthreads();
+    double* dst = p.part + (int64_t)blockIdx.x * (g.I + 1);
+    for (int k = threadIdx.x; k <= g.I; k += kRowBlock) dst[k] = lsum[k];
+}
+
+// The register form.  Lane (rg, q) keeps u~ of row 16 q + rg of every group of four wave
+// steps, and of each finished star's sums the one of its place: star `base + 16 k + rg`
+// astrometric q in pv[k], astrometric 4 of star base + 16 q + rg in p5.  A star shared with
+// the neighbouring wave goes through the exchange area (nsb = 1; xw: the wave's share of the
+// star that continues from the rows before, xch: one slot per wave boundary of the block, the
+// star's slot being its first boundary) or, where the LDS has no room for it, to s with
+// atomics.
+template <typename VT, bool TRANS = false>
+static __global__ __launch_bounds__(kRowBlock) void k_aprod12_reg(RowArgs<VT> p) {
+    extern __shared__ double lds[];  // [n_instr + 1] sums, [n_instr] staged xt, exchange area
+    const LsqrState* __restrict__ st = p.st;
+    if (st->stop) return;
+    const Geo g = p.g;
+    const VT* __restrict__ tiles = p.tiles;
+    const int32_t* __restrict__ star = p.star;
+    const double* __restrict__ xx = p.xx;
+    const double* __restrict__ xa = p.xa;
+    const double* uin = p.uin;
+    double* uout = p.uout;
+    double* __restrict__ s = p.s;
+    const double xs = TRANS ? st->su : st->sv;
+    const double ys = TRANS ? st->beta * st->sv : st->alpha * st->su;
+    const int tw = p.tw;
+    const bool xb = p.nsb != 0;
+    double zsq = 0.0, zw = 0.0, wsq = 0.0;
+    double* lsum = lds;
+    double* lxi = lds + g.I + 1;
+    double* xw = lds + 2 * (int64_t)g.I + 1;
+    double* xch = xw + kAstro * kRowWaves;
+    int32_t* bkey = reinterpret_cast<int32_t*>(xch + kAstro * (kRowWaves + 1));
+    constexpr int kXch = kAstro * (kRowWaves + 1);
+    for (int k = threadIdx.x; k <= g.I; k += kRowBlock) lsum[k] = 0.0;
+    for (int k = threadIdx.x; k < g.I; k += kRowBlock) lxi[k] = xx[g.ins0 + k];
+    if (xb && threadIdx.x < kXch) xch[threadIdx.x] = 0.0;
+    __syncthreads();
+    const double* __restrict__ xi = lxi;
+    const int lane = threadIdx.x % kWave, rg = lane / kQuad, q = lane % kQuad;
+    const int w = threadIdx.x / kWave;
+    const double xglob = xx[g.glb0];
+    const int64_t ntiles = (g.m + kStepRows - 1) / kStepRows;
+    const int64_t bt = (int64_t)tw * kRowWaves, nch = (ntiles + bt - 1) / bt;
+    double usq = 0.0, gacc = 0.0;
+    for (int64_t ch = blockIdx.x; ch < nch; ch += gridDim.x) {
+        const int64_t tb = ch * bt + (int64_t)w * tw, te = min(tb + tw, ntiles);
+        const int64_t r_beg = tb * kStepRows, r_end = min(te * kStepRows, g.m);
+        int32_t sf = -1, sl = -1;  // stars shared with the rows before and after the wave's
+        if (tb < te) {
+            const int32_t s0 = star[r_beg], s1 = star[r_end - 1];
+            sf = (r_beg > 0 && star[r_beg - 1] == s0) ? s0 : -1;
+            sl = (r_end < g.m && star[r_end] == s1) ? s1 : -1;
+            touch_stars(xx, s0, s1, lane);
+        }
+        if (xb && lane == 0) {
+            bkey[w] = sf;
+            if (w == kRowWaves - 1) bkey[kRowWaves] = sl;
+        }
+        double pv[kRegStars], p5 = 0.0;
+        int32_t base = -1, top = -1;
+#pragma unroll
+        for (int k = 0; k < kRegStars; ++k) pv[k] = 0.0;
+        auto put = [&](int32_t key, int c, double v) {  // one sum of a finished star
+            double* xo = s + (int64_t)kAstro * key + c;
+            if (key == sl) {
+                if (xb) {
+                    atomicAdd(xch + kAstro * (w + 1) + c, v);
+                } else {
+                    atomic_add_f64(xo, v);
+                    keep_apart();
+                }
+            } else {
+                *xo = v;  // s is zero before this pass: owned stars are stored
+            }
+        };
+        auto emit = [&]() {
+            if (base < 0) return;
+#pragma unroll
+            for (int k = 0; k < kRegStars; ++k) {
+                const int32_t key = base + 16 * k + rg;
+                if (key <= top) put(key, q, pv[k]);
+                pv[k] = 0.0;
+            }
+            const int32_t key = base + 16 * q + rg;
+            if (q < kRegStars && key <= top) put(key, 4, p5);
+            p5 = 0.0;
+            base = -1;
+        };
+        auto flush = [&](int32_t key_, const double (&t)[2]) {
+            const int32_t key = __builtin_amdgcn_readfirstlane(key_);
+            if (key == sf) {
+                if (lane < kAstro) {  // lanes 0..3: t[0]; lane 4, a q = 0 lane: t[1]
+                    const double v = lane < 4 ? t[0] : t[1];
+                    if (xb) {
+                        xw[kAstro * w + lane] = v;
+                    } else {
+                        atomic_add_f64(s + (int64_t)kAstro * key + lane, v);
+                        keep_apart();
+                    }
+                }
+                return;
+            }
+            if (base >= 0 && key - base >= 16 * kRegStars) emit();
+            if (base < 0) base = key;
+            top = key;
+            const int o = key - base;
+            const double t4 = dpp_f64<0x00>(t[1]);  // quad_perm [0,0,0,0]
+#pragma unroll
+            for (int k = 0; k < kRegStars; ++k) pv[k] = (rg == o - 16 * k) ? t[0] : pv[k];
+            p5 = (16 * q + rg == o) ? t4 : p5;
         };
         double acc[2] = {0.0, 0.0};
         int32_t ckey = -1;
-        for (int64_t r0 = r_beg; r0 < r_end; r0 += kStepRows * U) {
-            double a[U][6], uo[U];
-            int32_t sr[U], tr[U], ia[U], ib[U];
-            bool valid[U];
+        double ub[kRegGroups];
 #pragma unroll
-            for (int w = 0; w < U; ++w) {
-                const int64_t r = r0 + w * kStepRows + rg;
-                valid[w] = r < r_end;
-                const int64_t rr = valid[w] ? r : r_beg;  // in-bounds stand-in row
-                // tiles past the chunk are replaced by its first one (rows of the system's
-                // last tile past m are padding inside the allocation)
-                const int64_t tile = (r0 + w * kStepRows < r_end) ? r0 / kStepRows + w
-                                                                  : r_beg / kStepRows;
-                ld_tile(tiles, tile, lane, a[w]);
-                ld_tile_idx(tiles, tile, lane, sr[w], tr[w], ia[w], ib[w]);
-                uo[w] = uu[rr];
-            }
-#pragma unroll
-            for (int w = 0; w < U; ++w) {
-                const int64_t r = r0 + w * kStepRows + rg;
-                const double regA = (q == 0) ? a[w][5] : a[w][4];
-                double un = uo[w];
-                if (!INIT) {
-                    // aprod 1 part: the row's dot product, spread over the quad
-                    const int64_t ca = (int64_t)kAstro * sr[w];
-                    double sum = a[w][0] * xx[ca + q];
-                    if (q == 0) sum = fma(a[w][1], xx[ca + 4], sum);
-                    const double* __restrict__ xa = xx + g.att0 + tr[w] + jatt;
-#pragma unroll
-                    for (int ax = 0; ax < kAxes; ++ax) {
-                        const double c = (q == 0) ? a[w][ax + 2] : a[w][ax + 1];
-                        sum = fma(c, xa[(int64_t)ax * g.T], sum);
-                    }
-                    sum = fma(regA, xi[ia[w]], sum);
-                    if (q == 1 || q == 2) sum = fma(a[w][5], xi[ib[w]], sum);
-                    if (q == 3) sum = fma(a[w][5], xglob, sum);
-                    sum = quad_sum(sum);
-                    un = (ys != 0.0) ? xs * sum - ys * uo[w] : xs * sum;
-                }
+        for (int gi = 0; gi < kRegGroups; ++gi) {
+            ub[gi] = 0.0;
+            const int64_t t0 = tb + 4 * gi;
+            if (t0 >= te) continue;
+#pragma clang loop unroll(disable)
+            for (int sq = 0; sq < 4; ++sq) {
+                const int64_t t = t0 + sq;
+                if (t >= te) break;
+                TileRow a;
+                ld_tile(tiles, t, lane, a);
+                ld_tile_idx(tiles, t, lane, a);
+                const int64_t r = t * kStepRows + rg;
+                const double uo = uin[min(r, g.m - 1)];
+                const double sum = row_dot<true>(g, a, q, xx, xa, xi, xglob);
+                const double un = (ys != 0.0) ? xs * sum - ys * uo : xs * sum;
                 int32_t key = -1;
                 double v[2] = {0.0, 0.0};
-                if (valid[w]) {
-                    if (q == 0 && !INIT) {
-                        if (TRANS && pending) {  // z, w updated with the old v~ of this row
-                            const double wo = ww_vec[r];
-                            const double zn = fma(f1, wo, zz_vec[r]);
-                            const double wn = svo * uo[w] - f2 * wo;
-                            zz_vec[r] = zn;
-                            ww_vec[r] = wn;
-                            zsq = fma(zn, zn, zsq);
-                            zw = fma(zn, wn, zw);
-                            wsq = fma(wn, wn, wsq);
-                        }
-                        uu[r] = un;
-                        usq = fma(un, un, usq);
-                    }
-                    key = sr[w];
-                    v[0] = a[w][0] * un;
-                    v[1] = (q == 0) ? a[w][1] * un : 0.0;
-                    atomicAdd(lsum + ia[w], regA * un);
-                    if (q == 1 || q == 2) atomicAdd(lsum + ib[w], a[w][5] * un);
-                    if (q == 3) gacc = fma(a[w][5], un, gacc);
+                if (r < r_end) {
+                    if (q == 0) usq = fma(un, un, usq);
+                    key = a.star;
+                    v[0] = a.as * un;
+                    v[1] = (q == 0) ? a.z * un : 0.0;
+                    atomicAdd(lsum + a.ia, a.wi * un);
+                    if (q == 1 || q == 2) atomicAdd(lsum + a.ib, a.z * un);
+                    if (q == 3) gacc = fma(a.z, un, gacc);
                 }
-                // aprod 2 part, astrometric columns: runs of equal star
+                ub[gi] = (q == sq) ? un : ub[gi];
                 run_step<2, kQuad>(key, v, acc, ckey, flush);
             }
         }
         run_close<2, kQuad>(acc, ckey, flush);
+        __syncthreads();
+        // the round's results, written together
+#pragma unroll
+        for (int gi = 0; gi < kRegGroups; ++gi) {
+            const int64_t r = (tb + 4 * gi) * kStepRows + kStepRows * q + rg;
+            if (r >= r_end) continue;
+            if (TRANS) {
+                if (st->pending) {  // z, w updated with the old v~ of this row
+                    const double wo = p.ww[r];
+                    const double zn = fma(st->f1, wo, p.zz[r]);
+                    const double wn = st->sv * uin[r] - st->f2 * wo;
+                    p.zz[r] = zn;
+                    p.ww[r] = wn;
+                    zsq = fma(zn, zn, zsq);
+                    zw = fma(zn, wn, zw);
+                    wsq = fma(wn, wn, wsq);
+                }
+                uout[r] = ub[gi];
+            } else {
+                __builtin_nontemporal_store(ub[gi], uout + r);
+            }
+        }
+        emit();
+        if (xb) {
+            if (sf >= 0 && lane < kAstro) {
+                int j = w;  // the star's first boundary in the block
+                while (j > 0 && bkey[j - 1] == sf) --j;
+                atomicAdd(xch + kAstro * j + lane, xw[kAstro * w + lane]);
+            }
+            __syncthreads();
+            if (threadIdx.x < kXch) {
+                const int j = threadIdx.x / kAstro, c = threadIdx.x % kAstro;
+                const int32_t key = bkey[j];
+                if (key >= 0 && (j == 0 || bkey[j - 1] != key)) {
+                    double* xo = s + (int64_t)kAstro * key + c;
+                    if (key == bkey[0] || key == bkey[kRowWaves])  // continues in another block
+                        atomic_add_f64(xo, xch[threadIdx.x]);
+                    else
+                        *xo = xch[threadIdx.x];
+                }
+                xch[threadIdx.x] = 0.0;
+            }
+            __syncthreads();
+        }
     }
     const double gs = wave_sum(gacc);
     if (lane == 0) atomicAdd(lsum + g.I, gs);
-    const double tot = block_sum<1024>(usq, sh);
-    if (threadIdx.x == 0) partials[blockIdx.x] = tot;
+    __syncthreads();
+    double* sh = lxi;  // the staged unknowns are no longer needed
+    const double tot = block_sum<kRowBlock>(usq, sh);
+    if (threadIdx.x == 0) p.partials[blockIdx.x] = tot;
     if (TRANS) {
-        const int G = pstride;
-        double t2 = block_sum<1024>(zsq, sh);
-        if (threadIdx.x == 0) partials[G + blockIdx.x] = t2;
-        t2 = block_sum<1024>(zw, sh);
-        if (threadIdx.x == 0) partials[2 * G + blockIdx.x] = t2;
-        t2 = block_sum<1024>(wsq, sh);
-        if (threadIdx.x == 0) partials[3 * G + blockIdx.x] = t2;
+        double t2 = block_sum<kRowBlock>(zsq, sh);
+        if (threadIdx.x == 0) p.partials[p.pstride + blockIdx.x] = t2;
+        t2 = block_sum<kRowBlock>(zw, sh);
+        if (threadIdx.x == 0) p.partials[2 * p.pstride + blockIdx.x] = t2;
+        t2 = block_sum<kRowBlock>(wsq, sh);
+        if (threadIdx.x == 0) p.partials[3 * p.pstride + blockIdx.x] = t2;
     }
     __syncthreads();
-    double* dst = part + (int64_t)blockIdx.x * (g.I + 1);
-    for (int k = threadIdx.x; k <= g.I; k += blockDim.x) dst[k] = lsum[k];
+    double* dst = p.part + (int64_t)blockIdx.x * (g.I + 1);
+    for (int k = threadIdx.x; k <= g.I; k += kRowBlock) dst[k] = lsum[k];
+}
+
+// ---------------------------------------------------------------------------------------
+// aprod 1 by itself:  sum_i = sum_k A[i,k] xx[col(i,k)], then
+//   A1_ADD   : y[i] += sum_i
+//   A1_LSQR  : y[i] = xs sum_i - ys y[i]  with (xs, ys) = (sv, alpha su)   [forward operator]
+//   A1_LSQR_T: same with (xs, ys) = (su, beta sv)                           [transposed]
+//   A1_RESID : y[i] = b[i] - sum_i
+// LSQR modes also write the block partial of sum y[i]^2.  gate (may be NULL): nothing is done
+// when *gate is set (a residual of a correction step that will not be taken).
+// Rounds as in the fused pass: the round's sums wait in LDS and y is read and written in one
+// go at its end (2e7 rows, n_instr 6,000: 1.12 ms with a load and a store of y per wave step,
+// 0.85 ms with the round and the knot-by-knot attitude operand).
+// IL: xa holds the attitude part of xx knot by knot (AttCopy); otherwise it is gathered from
+// xx, three loads per lane.  LDSI: the instrumental part of xx is staged in LDS.
+enum { A1_ADD = 0, A1_LSQR = 1, A1_LSQR_T = 2, A1_RESID = 3 };
+
+template <typename VT, int MODE, bool IL, bool LDSI>
+static __global__ __launch_bounds__(kRowBlock) void k_aprod1(
+    Geo g, const VT* __restrict__ tiles, const int32_t* __restrict__ star,
+    const double* __restrict__ xx, const double* __restrict__ xa, double* y,
+    const double* __restrict__ b, const LsqrState* __restrict__ st,
+    double* __restrict__ partials, int tw, const int32_t* __restrict__ gate) {
+    extern __shared__ double lds[];  // [n_instr] staged unknowns (LDSI), [tw][kRoundRows] sums
+    __shared__ double sh[kRowWaves];
+    if (gate && *gate) return;
+    constexpr bool kLsqr = (MODE == A1_LSQR || MODE == A1_LSQR_T);
+    double xs = 1.0, ys = 0.0;
+    if (kLsqr) {
+        if (st->stop) return;
+        xs = MODE == A1_LSQR ? st->sv : st->su;
+        ys = MODE == A1_LSQR ? st->alpha * st->su : st->beta * st->sv;
+    }
+    double* lxi = lds;
+    double* ubuf = lds + (LDSI ? (g.I + 1) / 2 * 2 : 0);
+    if (LDSI) {
+        for (int k = threadIdx.x; k < g.I; k += kRowBlock) lxi[k] = xx[g.ins0 + k];
+        __syncthreads();
+    }
+    const double* __restrict__ xi = LDSI ? lxi : xx + g.ins0;
+    const int lane = threadIdx.x % kWave, rg = lane / kQuad, q = lane % kQuad;
+    const int w = threadIdx.x / kWave;
+    const double xglob = xx[g.glb0];
+    const int64_t ntiles = (g.m + kStepRows - 1) / kStepRows;
+    const int64_t bt = (int64_t)tw * kRowWaves, nch = (ntiles + bt - 1) / bt;
+    double acc = 0.0;
+    for (int64_t ch = blockIdx.x; ch < nch; ch += gridDim.x) {
+        const int64_t R0 = ch * bt * kStepRows, R1 = min(R0 + bt * kStepRows, g.m);
+        const int64_t te = min((ch + 1) * bt, ntiles);
+        if (tw > 1) touch_stars(xx, star[R0], star[R1 - 1], threadIdx.x);
+        const double* yo = MODE == A1_RESID ? b : y;
+        const int64_t r1st = R0 + threadIdx.x;  // its old value arrives with the tiles
+        const double yo1st = r1st < R1 ? yo[r1st] : 0.0;
+        for (int64_t t = ch * bt + w; t < te; t += kRowWaves) {
+            TileRow a;
+            ld_tile(tiles, t, lane, a);
+            ld_tile_idx(tiles, t, lane, a);
+            const double sum = row_dot<IL>(g, a, q, xx, xa, xi, xglob);
+            if (q == 0) ubuf[(t - ch * bt) * kStepRows + rg] = sum;
+        }
+        __syncthreads();
+        for (int64_t r = r1st; r < R1; r += kRowBlock) {
+            const double sum = ubuf[r - R0], old = r == r1st ? yo1st : yo[r];
+            if (MODE == A1_ADD) {
+                y[r] = old + sum;
+            } else if (MODE == A1_RESID) {
+                y[r] = old - sum;
+            } else {
+                const double u = (ys != 0.0) ? xs * sum - ys * old : xs * sum;
+                y[r] = u;
+                acc = fma(u, u, acc);
+            }
+        }
+        __syncthreads();
+    }
+    if (kLsqr) {
+        const double tot = block_sum<kRowBlock>(acc, sh);
+        if (threadIdx.x == 0) partials[blockIdx.x] = tot;
+    }
+}
+
+// xa[3 c + axis] = xx[att0 + axis T + c] (AttCopy)
+static __global__ void k_att_copy(AttCopy ac, const double* __restrict__ xx) {
+    const int64_t n = kAxes * ac.T, stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride)
+        put_att(ac, ac.att0 + e, xx[ac.att0 + e]);
+}
+
+// ---------------------------------------------------------------------------------------
+// aprod 2, star-ordered columns (astrometric, instrumental, global) by themselves:
+//   x[col(i,k)] += A[i,k] y[i]  (A2_ADD; A2_LSQR / A2_LSQR_T, where y is the unnormalized
+//   u~ or v~ and the following vector step applies 1/beta or 1/alpha), or the contribution is
+//   A[i,k]^2 (A2_SQ, column norms).  LSQR modes return at once when the stop flag is set; in
+//   them and in A2_SQ the target starts at zero, so a star the block owns is stored.
+// The fused pass without its dot products: it reads the tiles' second and third groups and
+// the indices (binary32: the first group), 2,560 of 3,584 bytes a wave step (2e7 rows: 0.66 ms
+// against 1.15 over the caller's rows, of which it fetched every line).  LDSI: the block's
+// instrumental sums in LDS; otherwise (n_instr too large) atomics.
+enum { A2_ADD = 0, A2_LSQR = 1, A2_LSQR_T = 2, A2_SQ = 3 };
+
+template <int MODE>
+__device__ __forceinline__ double contrib(double a, double yy) {
+    return MODE == A2_SQ ? a * a : a * yy;
+}
+
+template <typename VT, int MODE, bool LDSI>
+static __global__ __launch_bounds__(kRowBlock) void k_aprod2_star(
+    Geo g, const VT* __restrict__ tiles, const int32_t* __restrict__ star,
+    const double* __restrict__ y, double* __restrict__ x, const LsqrState* __restrict__ st,
+    double* __restrict__ part, int tw, int nsb) {
+    extern __shared__ double lds[];  // [n_instr + 1] sums (LDSI) or [1] global, [nsb][5] stars
+    if ((MODE == A2_LSQR || MODE == A2_LSQR_T) && st->stop) return;
+    const int nI = LDSI ? g.I : 0;
+    double* lsum = lds;
+    double* sbuf = lds + nI + 1;
+    for (int k = threadIdx.x; k < nI + 1 + kAstro * nsb; k += kRowBlock) lds[k] = 0.0;
+    __syncthreads();
+    const int lane = threadIdx.x % kWave, rg = lane / kQuad, q = lane % kQuad;
+    const int w = threadIdx.x / kWave;
+    const int64_t ntiles = (g.m + kStepRows - 1) / kStepRows;
+    const int64_t bt = (int64_t)tw * kRowWaves, nch = (ntiles + bt - 1) / bt;
+    double gacc = 0.0;
+    for (int64_t ch = blockIdx.x; ch < nch; ch += gridDim.x) {
+        const int64_t R0 = ch * bt * kStepRows, R1 = min(R0 + bt * kStepRows, g.m);
+        const int64_t te = min((ch + 1) * bt, ntiles);
+        const int32_t S0 = star[R0], S1 = star[R1 - 1];
+        const bool shf = R0 > 0 && star[R0 - 1] == S0, shl = R1 < g.m && star[R1] == S1;
+        for (int64_t t = ch * bt + w; t < te; t += kRowWaves) {
+            TileRow a;
+            ld_tile(tiles, t, lane, a);
+            ld_tile_idx(tiles, t, lane, a);
+            const int64_t r = t * kStepRows + rg;
+            const double yy = (MODE == A2_SQ) ? 0.0 : y[min(r, g.m - 1)];
+            if (r >= R1) continue;
+            const double cs = contrib<MODE>(a.as, yy), cz = contrib<MODE>(a.z, yy),
+                         ci = contrib<MODE>(a.wi, yy);
+            // the star's slot, or (stars past the last slot) straight to x
+            const int o = a.star - S0;
+            if ((uint32_t)o < (uint32_t)nsb) {
+                atomicAdd(sbuf + kAstro * o + q, cs);
+                if (q == 0) atomicAdd(sbuf + kAstro * o + 4, cz);
+            } else {
+                double* xo = x + (int64_t)kAstro * a.star;
+                atomic_add_f64(xo + q, cs);
+                if (q == 0) atomic_add_f64(xo + 4, cz);
+                keep_apart();
+            }
+            if (LDSI) {
+                atomicAdd(lsum + a.ia, ci);
+                if (q == 1 || q == 2) atomicAdd(lsum + a.ib, cz);
+            } else {
+                atomic_add_f64(x + g.ins0 + a.ia, ci);
+                if (q == 1 || q == 2) atomic_add_f64(x + g.ins0 + a.ib, cz);
+            }
+            if (q == 3) gacc += cz;
+        }
+        __syncthreads();
+        const int ne = kAstro * min(S1 - S0 + 1, nsb);
+        const int e0 = shf ? kAstro : 0, e1 = (shl && S1 - S0 < nsb) ? ne - kAstro : ne;
+        for (int e = threadIdx.x; e < ne; e += kRowBlock) {
+            const double v = sbuf[e];
+            sbuf[e] = 0.0;
+            double* xo = x + (int64_t)kAstro * S0 + e;
+            if (e < e0 || e >= e1)
+                atomic_add_f64(xo, v);
+            else if (MODE == A2_ADD)
+                *xo += v;
+            else
+                __builtin_nontemporal_store(v, xo);
+        }
+        __syncthreads();
+    }
+    const double gs = wave_sum(gacc);
+    if (lane == 0) atomicAdd(lsum + nI, gs);
+    __syncthreads();
+    if (LDSI) {
+        double* dst = part + (int64_t)blockIdx.x * (nI + 1);
+        for (int k = threadIdx.x; k <= nI; k += kRowBlock) dst[k] = lsum[k];
+    } else if (threadIdx.x == 0) {
+        atomic_add_f64(x + g.glb0, *lsum);
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -681,7 +959,6 @@ static __global__ __launch_bounds__(kBlockAtt) void k_aprod2_att(
     extern __shared__ double acc[];  // [kAxes][lw]
     for (int i = threadIdx.x; i < kAxes * lw; i += blockDim.x) acc[i] = 0.0;
     __syncthreads();
-    const double ysc = a2_scale<MODE>(st);
     const int lane = threadIdx.x % kWave, rg = lane / kQuad, q = lane % kQuad;
     const int wave = threadIdx.x / kWave, wpb = blockDim.x / kWave;
     const int64_t lo = seg[blockIdx.x], hi = seg[blockIdx.x + 1];
@@ -702,7 +979,7 @@ static __global__ __launch_bounds__(kBlockAtt) void k_aprod2_att(
                     valid[w] = tl + w < c1 && k >= lo && k < hi;
                     const int64_t kk = valid[w] ? k : lo;  // in-bounds stand-in
                     col[w] = tL[kk] + q;
-                    yy[w] = (MODE == A2_SQ) ? 0.0 : ysc * y[rowT[kk]];
+                    yy[w] = (MODE == A2_SQ) ? 0.0 : y[rowT[kk]];
                     ld_att_tile(attT, tile, lane, va[w]);
                 }
 #pragma unroll

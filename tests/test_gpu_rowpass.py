@@ -1,0 +1,111 @@
+"""The row passes (the fused pass with u~ and finished stars kept in LDS or in registers until a
+round of rows ends, aprod 1 and the star-ordered aprod 2 by themselves) at the sizes where they
+can go wrong, through the C ABI against the oracle: rows that end inside a wave step, a wave's
+share and a round; stars that span several waves and blocks; one row per star; more stars in a
+round than it has slots; stars without rows; the register form with and without its exchange
+area; several rounds per block; instrumental columns beyond the fused pass and beyond LDS; enough
+rows for the knot-by-knot copy of the attitude unknowns.
+
+Tolerances: rounding-order differences of a product stay within 1e-13 of its largest entry where
+a column sums up to about 1e5 terms, 1e-12 beyond; LSQR iterates after three steps within 1e-10
+relative (the bounds of the other parity tests)."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from gpu_util import assert_close_scaled, cuda, host, open_system, oracle_system, rel
+from paper_2212_11675_amd import gsr
+
+pytestmark = pytest.mark.gpu
+
+
+def _runs(counts, n_dfa, n_instr, seed):
+    """A system whose star k has counts[k] rows."""
+    counts = np.asarray(counts, dtype=np.int64)
+    m = int(counts.sum())
+    shape = synth.Shape(1, m, m, n_dfa, n_instr, seed=seed)
+    out = synth.rows(shape, 0, m)
+    out["star"] = np.repeat(np.arange(counts.size, dtype=np.int32), counts)
+    out["dims"] = dict(n_rows=m, n_stars=int(counts.size), n_dfa=n_dfa, n_instr=n_instr, n_glob=1)
+    return out
+
+
+LONG = [3, 5000, 1, 1, 20000, 7, 16, 16, 300, 40000, 2]
+CROWD = [40000] + [1] * 30000  # far more stars than the mean in the second half
+GAPS = [0, 17, 0, 0, 5, 1, 0] * 900
+CASES = {
+    "one_row": ([1], 9, 12),
+    "tile_edge_17": ([10, 7], 9, 12),
+    "wave_edge": ([16] * 4096 + [1], 50, 40),
+    "wave_edge_under": ([16] * 4095 + [15], 50, 40),
+    "long_stars": (LONG, 40, 60),
+    "one_row_per_star": ([1] * 70001, 40, 60),
+    "crowded_slots": (CROWD, 40, 60),
+    "gaps": (GAPS, 30, 40),
+    "two_rounds_lds": ([23] * 27000 + [500, 1], 300, 8400),
+    "reg_exchange_long": (LONG + [25] * 6000, 40, 10100),
+    "reg_exchange_gaps": (GAPS * 2, 40, 10100),
+    "reg_no_exchange": (LONG + [25] * 2000 + GAPS, 40, 10200),
+    "reg_two_rounds": ([37] * 57000 + [3, 41], 300, 10100),
+    "wide": (LONG + [25] * 2000 + GAPS, 40, 11000),
+    "beyond_lds": (LONG + [25] * 2000 + GAPS, 40, 21000),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_iterates_of_every_form_match_the_oracle(name):
+    counts, n_dfa, n_instr = CASES[name]
+    print(f"[row pass] {name}", flush=True)
+    sysd = _runs(counts, n_dfa, n_instr, seed=171)
+    S = oracle_system(sysd)
+    h, _ = open_system(sysd, allow_empty_cols=True, build_f32=True)
+    rng = np.random.default_rng(172)
+    b = rng.standard_normal(S.m)
+    x = torch.empty(S.n, dtype=torch.float64, device="cuda")
+    it = 3 if S.m > 100 else 1  # a handful of rows is solved exactly after a few steps
+    info = gsr.gsr_lsqr_solve(h, cuda(b), x, gsr.solve_opts(itnlim=it, fixed_iters=True))
+    assert info["fused"] == int(n_instr <= 10239)
+    xo, io = S.lsqr(b, itnlim=it, fixed=True)
+    assert info["itn"] == io["itn"] == it
+    assert rel(host(x), xo) <= 1e-10
+    # binary32 coefficients, one inner solve
+    S32 = S.with_vals(sysd["vals"].astype(np.float32).astype(np.float64))
+    gsr.gsr_lsqr_solve(h, cuda(b), x, gsr.solve_opts(itnlim=it, fixed_iters=True,
+                                                     precision=gsr.GSR_F32V, max_refine=1))
+    assert rel(host(x), S32.lsqr(b, itnlim=it, fixed=True)[0]) <= 1e-10
+    # the transposed recurrence of the adjoint solve, in the space of the rows
+    g = rng.standard_normal(S.n)
+    mu = torch.empty(S.m, dtype=torch.float64, device="cuda")
+    lam = torch.empty(S.n, dtype=torch.float64, device="cuda")
+    gsr.gsr_lsqr_solve_adjoint(h, cuda(g), mu, lam, gsr.solve_opts(itnlim=it, fixed_iters=True))
+    assert rel(host(mu), S.lsqr_transposed(g, itnlim=it, fixed=True)[0]) <= 1e-10
+    h.close()
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_products_of_every_form_match_the_oracle(name):
+    counts, n_dfa, n_instr = CASES[name]
+    print(f"[row products] {name}", flush=True)
+    sysd = _runs(counts, n_dfa, n_instr, seed=173)
+    S = oracle_system(sysd)
+    S32 = S.with_vals(sysd["vals"].astype(np.float32).astype(np.float64))
+    h, _ = open_system(sysd, allow_empty_cols=True, build_f32=True)
+    rng = np.random.default_rng(174)
+    tol = 1e-13 if S.m < 200000 else 1e-12
+    x, y0 = rng.standard_normal(S.n), rng.standard_normal(S.m)
+    y, x0 = rng.standard_normal(S.m), rng.standard_normal(S.n)
+    for a1, a2, ref in ((gsr.gsr_aprod1, gsr.gsr_aprod2, S),
+                        (gsr.gsr_aprod1_f32v, gsr.gsr_aprod2_f32v, S32)):
+        yd, xd = cuda(y0), cuda(x0)
+        a1(h, cuda(x), yd)
+        assert_close_scaled(host(yd), ref.aprod1(x, y0), tol)
+        a2(h, cuda(y), xd)
+        assert_close_scaled(host(xd), ref.aprod2(y, x0), tol)
+    r = torch.empty(S.m, dtype=torch.float64, device="cuda")
+    gsr.gsr_residual(h, cuda(y0), cuda(x), r)
+    assert_close_scaled(host(r), S.residual(y0, x), tol)
+    p = torch.empty(S.n, dtype=torch.float64, device="cuda")
+    gsr.gsr_precond(h, p)
+    np.testing.assert_allclose(host(p), S.colnorm(), rtol=1e-12, atol=0)
+    h.close()
