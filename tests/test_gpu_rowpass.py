@@ -109,3 +109,26 @@ def test_products_of_every_form_match_the_oracle(name):
     gsr.gsr_precond(h, p)
     np.testing.assert_allclose(host(p), S.colnorm(), rtol=1e-12, atol=0)
     h.close()
+
+
+@pytest.mark.parametrize("itnlim", [15, 16, 17, 32])
+def test_steps_at_the_ends_of_a_replayed_sequence(itnlim):
+    """The scalar steps are taken by the kernels that follow them, the last one of a replayed
+    sequence (16 iterations) by a kernel of its own: solves that stop around its end.  Two replays
+    of the same handle; attitude buckets narrower than a row's knots (n_dfa 4) and wider."""
+    for n_dfa in (4, 60):
+        sysd = _runs([7, 1, 12, 30, 3] * 60, n_dfa, 40, seed=175)
+        S = oracle_system(sysd)
+        h, _ = open_system(sysd, allow_empty_cols=True)
+        rng = np.random.default_rng(176)
+        x = torch.empty(S.n, dtype=torch.float64, device="cuda")
+        mu = torch.empty(S.m, dtype=torch.float64, device="cuda")
+        o = gsr.solve_opts(itnlim=itnlim, fixed_iters=True)
+        for _ in range(2):
+            b, g = rng.standard_normal(S.m), rng.standard_normal(S.n)
+            assert gsr.gsr_lsqr_solve(h, cuda(b), x, o)["itn"] == itnlim
+            assert rel(host(x), S.lsqr(b, itnlim=itnlim, fixed=True)[0]) <= 1e-10
+            lam = torch.empty(S.n, dtype=torch.float64, device="cuda")
+            gsr.gsr_lsqr_solve_adjoint(h, cuda(g), mu, lam, o)
+            assert rel(host(mu), S.lsqr_transposed(g, itnlim=itnlim, fixed=True)[0]) <= 1e-10
+        h.close()
