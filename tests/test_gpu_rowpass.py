@@ -132,3 +132,37 @@ def test_steps_at_the_ends_of_a_replayed_sequence(itnlim):
             gsr.gsr_lsqr_solve_adjoint(h, cuda(g), mu, lam, o)
             assert rel(host(mu), S.lsqr_transposed(g, itnlim=itnlim, fixed=True)[0]) <= 1e-10
         h.close()
+
+
+@pytest.mark.parametrize("k,n_instr", [(1, 40), (2, 40), (4, 60), (8, 40), (8, 1100)])
+def test_batched_row_pass_matches_the_oracle(k, n_instr):
+    """The batched row and attitude passes at their edges: the runs of stars above as systems of
+    one batch (stars past the last slot of a round, stars without rows, rows that end inside a
+    wave step, a system of one row), attitude runs that begin and end inside a block of 32 rows
+    (n_dfa 40) and runs of thousands of rows (n_dfa 4), the unknowns of the instrumental columns
+    staged in LDS and (n_instr 1,100 with 8 right-hand sides) read from the operand."""
+    print(f"[batch row pass] k={k} n_instr={n_instr}", flush=True)
+    runs = [([1], 4), (CROWD, 40), ([10, 7], 9), (GAPS, 4), ([1] * 5003, 3000), (LONG, 40),
+            ([16] * 300 + [15], 50)]
+    systems = [_runs(c, n_dfa, n_instr, seed=180 + i) for i, (c, n_dfa) in enumerate(runs)]
+    dims = [gsr.make_dims(s["dims"]["n_rows"], s["dims"]["n_stars"], s["dims"]["n_dfa"],
+                          s["dims"]["n_instr"]) for s in systems]
+    ro = np.concatenate([[0], np.cumsum([s["dims"]["n_rows"] for s in systems])])
+    dev = {key: torch.from_numpy(np.concatenate([s[key] for s in systems])).to("cuda:0")
+           for key in ("vals", "star", "att", "instr")}
+    b = gsr.gsr_batch_setup(dims, ro.tolist(), dev["vals"], dev["star"], dev["att"], dev["instr"],
+                            k, allow_empty_cols=True)
+    rhs = np.random.default_rng(190).standard_normal((b.m, k))
+    for iters in (1, 3):
+        x = torch.empty(b.n * k, dtype=torch.float64, device="cuda")
+        gsr.gsr_batch_solve(b, cuda(rhs.ravel()), x, gsr.solve_opts(itnlim=iters, fixed_iters=True))
+        xg = host(x).reshape(b.n, k)
+        for i, sysd in enumerate(systems):
+            if iters > 1 and sysd["dims"]["n_rows"] < 100:
+                continue  # solved exactly before that
+            S = oracle_system(sysd)
+            c0, c1 = b.col_offset[i], b.col_offset[i + 1]
+            for j in range(k):
+                xo, _ = S.lsqr(rhs[ro[i]:ro[i + 1], j], itnlim=iters, fixed=True)
+                assert rel(xg[c0:c1, j], xo) <= 1e-10, (i, j, iters)
+    b.close()
