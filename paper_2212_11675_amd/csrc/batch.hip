@@ -1136,7 +1136,8 @@ namespace {
 
 // Shape of the row pass for the tuning `t`: rounds of at most t.steps wave steps per wave, as
 // many as the LDS holds beside the sums (one block of 1,024 threads or two of 512 per compute
-// unit share it); 0 rows when not even one step fits.  The instrumental unknowns are staged
+// unit share it).  Where the slots of one step do not fit beside the sums, as many as do (stars
+// past the last slot take atomics); 0 rows when the sums alone do not fit.  The instrumental unknowns are staged
 // where that leaves two steps or more (16 systems of 1.31e7 rows, 8 right-hand sides, 500 columns
 // each: 1.61 ms staged, 1.95 ms read from the operand; 64 systems of 1.76e6 rows, 2 right-hand
 // sides, 100 columns: 99 and 111 us) and read from the operand otherwise (above about 1,200
@@ -1162,9 +1163,13 @@ BRowPlan plan_brow(const gsr_batch* b, const Tuning& t) {
         while (steps > 0 && need(steps, false) > lds) --steps;
     }
     r.threads = t.threads;
-    r.rows = steps * nw * kStepRows;
-    r.nsb = (int)slots(r.rows);
-    r.lds = sizeof(double) * (size_t)need(steps, r.ldsi);
+    r.rows = std::max(1, steps) * nw * kStepRows;
+    const int64_t base =
+        brow_fixed(b->k, b->max_instr, r.ldsi) + (b->k <= 2 ? (int64_t)r.rows * b->k : 0);
+    const int64_t fit = (lds - base) / (kAstro * b->k);
+    if (fit < 1) return BRowPlan();
+    r.nsb = (int)std::min(slots(r.rows), fit);
+    r.lds = sizeof(double) * (size_t)(base + (int64_t)r.nsb * kAstro * b->k);
     return r;
 }
 

@@ -166,3 +166,28 @@ def test_batched_row_pass_matches_the_oracle(k, n_instr):
                 xo, _ = S.lsqr(rhs[ro[i]:ro[i + 1], j], itnlim=iters, fixed=True)
                 assert rel(xg[c0:c1, j], xo) <= 1e-10, (i, j, iters)
     b.close()
+
+
+def test_batched_row_pass_with_the_widest_instrumental_section():
+    """The most instrumental columns that a batch with 8 right-hand sides takes, one row per star:
+    the sums leave room for fewer star slots than one wave step of a block needs."""
+    k, n_instr = 8, 1279
+    print(f"[batch row pass, widest] k={k} n_instr={n_instr}", flush=True)
+    systems = [_runs([1] * m, 30, n_instr, seed=195 + i) for i, m in enumerate((1501, 4100))]
+    dims = [gsr.make_dims(s["dims"]["n_rows"], s["dims"]["n_stars"], s["dims"]["n_dfa"],
+                          s["dims"]["n_instr"]) for s in systems]
+    ro = np.concatenate([[0], np.cumsum([s["dims"]["n_rows"] for s in systems])])
+    dev = {key: torch.from_numpy(np.concatenate([s[key] for s in systems])).to("cuda:0")
+           for key in ("vals", "star", "att", "instr")}
+    b = gsr.gsr_batch_setup(dims, ro.tolist(), dev["vals"], dev["star"], dev["att"], dev["instr"],
+                            k, allow_empty_cols=True)
+    rhs = np.random.default_rng(197).standard_normal((b.m, k))
+    x = torch.empty(b.n * k, dtype=torch.float64, device="cuda")
+    gsr.gsr_batch_solve(b, cuda(rhs.ravel()), x, gsr.solve_opts(itnlim=2, fixed_iters=True))
+    xg = host(x).reshape(b.n, k)
+    for i, sysd in enumerate(systems):
+        S = oracle_system(sysd)
+        for j in range(k):
+            xo, _ = S.lsqr(rhs[ro[i]:ro[i + 1], j], itnlim=2, fixed=True)
+            assert rel(xg[b.col_offset[i]:b.col_offset[i + 1], j], xo) <= 1e-10, (i, j)
+    b.close()
