@@ -954,8 +954,9 @@ static __global__ __launch_bounds__(kRowBlock) void k_aprod2_star(
 // The block's sums go to part[G] (kAxes rows of lw = W + kParAxis - 1 columns), added to x by
 // k_att_reduce or taken from there by the vector step (AttSum).  Blocks from ng on add the
 // star-ordered pass's instrumental block sums to x (reduce_columns): that work waits for the same
-// kernel as this pass and fits beside it, and as a launch of its own costs 4 to 5 us.  Row k of the copy (tile k / kStepRows): attT = A[row_k, 5 + 4 a + j],
-// rowT[k] = row_k, tL[k] = att[row_k] - b W; group G is rows seg[G] .. seg[G + 1] - 1.
+// kernel as this pass and fits beside it, and as a launch of its own costs 4 to 5 us.  Row k of
+// the copy (tile k / kStepRows): attT = A[row_k, 5 + 4 a + j], rowT[k] = row_k, tL[k] = att[row_k]
+// - b W; group G is rows seg[G] .. seg[G + 1] - 1.
 constexpr int kBlockAtt = 512;
 constexpr int kAttChunkTiles = 2;  // wave steps per chunk (chunks dealt to the waves in turn)
 
