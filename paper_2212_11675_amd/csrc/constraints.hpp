@@ -23,13 +23,9 @@ namespace gsr {
 
 constexpr int kConSlots = 64;   // LDS row slots per block of k_con_dot
 constexpr int kConBlock = 256;
-constexpr int kConAhead = 4;    // entries of a thread in flight at a time
-constexpr int kConPerBlock = kConAhead * kConBlock;  // entries of a block of k_con_dot
 
 // acc[row(e)] += val[e] * x[col[e]] over all entries (acc zero before; the finishing kernel
-// clears it again).  Bound by the latency of its two dependent loads: a thread issues its
-// kConAhead entries' loads together and has no more than those (up to 1,024 blocks); 1.1e5
-// entries 15.6 -> 4.6 us against 16 entries per thread, one after the other.  check_stop: skip once the LSQR stop flag is set; gate: skip when set.
+// clears it again).  check_stop: skip once the LSQR stop flag is set; gate: skip when set.
 static __global__ __launch_bounds__(kConBlock) void k_con_dot(
     int64_t nnz, int64_t per_block, const int32_t* __restrict__ crow,
     const int64_t* __restrict__ ccol, const double* __restrict__ cval,
@@ -53,29 +49,14 @@ static __global__ __launch_bounds__(kConBlock) void k_con_dot(
         else
             atomic_add_f64(acc + cur, sum);
     };
-    for (int64_t e = e0 + threadIdx.x; e < e1; e += kConAhead * kConBlock) {
-        int32_t r[kConAhead];
-        int64_t c[kConAhead];
-        double v[kConAhead], xv[kConAhead];
-#pragma unroll
-        for (int k = 0; k < kConAhead; ++k) {
-            const int64_t i = min(e + k * kConBlock, e1 - 1);
-            r[k] = crow[i];
-            c[k] = ccol[i];
-            v[k] = cval[i];
+    for (int64_t e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
+        const int32_t r = crow[e];
+        if (r != cur) {
+            flush();
+            cur = r;
+            sum = 0.0;
         }
-#pragma unroll
-        for (int k = 0; k < kConAhead; ++k) xv[k] = x[c[k]];
-#pragma unroll
-        for (int k = 0; k < kConAhead; ++k) {
-            if (e + k * kConBlock >= e1) break;
-            if (r[k] != cur) {
-                flush();
-                cur = r[k];
-                sum = 0.0;
-            }
-            sum = fma(v[k], xv[k], sum);
-        }
+        sum = fma(cval[e], x[ccol[e]], sum);
     }
     flush();
     __syncthreads();

@@ -1057,8 +1057,7 @@ gsr_status build_constraints(gsr_handle* h, int64_t n_con, int64_t nnz, const in
         if (flags) return fail(GSR_E_LAYOUT, "constraint ptr decreases");
     }
     if (nnz == 0) return GSR_OK;
-    h->Gcon =
-        (int)std::max<int64_t>(1, std::min<int64_t>(1024, (nnz + kConPerBlock - 1) / kConPerBlock));
+    h->Gcon = (int)std::max<int64_t>(1, std::min<int64_t>(1024, (nnz + 4095) / 4096));
     h->con_per_block = (nnz + h->Gcon - 1) / h->Gcon;
     GSR_TRY(dalloc(&h->crow, nnz));
     GSR_TRY(dalloc(&h->cu_row, nnz));
