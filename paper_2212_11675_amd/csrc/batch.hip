@@ -4,16 +4,13 @@
 // Every (system, right-hand side) pair runs its own PC-LSQR recurrence (LsqrState per
 // pair); the matrix of each system is read once per product for all K right-hand sides
 // (sparse matrix times K-column block, RHS-minor storage so the K values of one row or
-// column form one contiguous 8K-byte piece).
+// column form one contiguous 8K-byte piece).  Lane layout: K lanes per row, lane j = RHS j.
 // Work is described by lists of segments that never cross a system boundary:
 //   row chunks    (one wave walks a chunk: products, row-space vector steps, partial sums),
 //   block chunks  (one block walks a chunk: star-ordered pass of aprod 2, LDS per system),
-//   rounds        (one block: the row pass of the solver),
-//   attitude chunks (one wave: runs of t-ordered rows),
 //   column tiles  (one block: unknown-space vector steps).
-// A whole fixed-iteration solve is captured in one hipGraph and launched once.  Round
-// length and block size of the row pass are picked per batch shape by timing candidates
-// (autotuner).
+// A whole fixed-iteration solve is captured in one hipGraph and launched once.  Chunk
+// length and block shape are picked per batch shape by timing candidates (autotuner).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -40,7 +37,7 @@ struct SysDesc {
     int32_t T, I;
     int32_t chunk0, nchunk;    // row chunks of the system
     int32_t tile0, ntile;      // column tiles of the system
-    int32_t round0, nround;    // rounds of the system
+    int32_t bchunk0, nbchunk;  // block chunks of the system
     int64_t btile0;            // first row tile of the system (rows padded to whole tiles)
 };
 
@@ -49,7 +46,7 @@ struct Seg {
     int32_t sys, pad;
 };
 
-constexpr int kBTileMin = 256, kBTileMax = 2048;  // columns per tile
+constexpr int kBTile = 2048;  // columns per tile
 
 // Block index renumbered so that the blocks of one die are consecutive: contiguous work
 // ranges (one or a few systems) then stay on one die and share its L2.
@@ -133,12 +130,12 @@ static __global__ __launch_bounds__(256) void k_baprod1(
 // Block chunks are walked by whole blocks; each wave takes a contiguous sub-range.  The
 // instrumental and global sums of the current system live in LDS and are added to X with
 // one atomic per (column, j) when the block moves to another system or finishes.
-template <int K>
+template <typename VT, int MODE, int K>
 static __global__ __launch_bounds__(512) void k_baprod2_star(
     const SysDesc* __restrict__ sys, const Seg* __restrict__ bchunks, int nbchunks,
-    const double* __restrict__ vals, const int32_t* __restrict__ star,
+    const VT* __restrict__ vals, const int32_t* __restrict__ star,
     const int32_t* __restrict__ instr, const double* __restrict__ Y, double* __restrict__ X,
-    int max_instr) {
+    const LsqrState* __restrict__ st, int max_instr) {
     extern __shared__ double lds[];  // [(max_instr + 1) * K]
     constexpr int RS = kWave / K;
     const int lane = threadIdx.x % kWave, rr = lane / K, j = lane % K;
@@ -177,6 +174,13 @@ static __global__ __launch_bounds__(512) void k_baprod2_star(
             cur = c.sys;
             d = sys[cur];
         }
+        bool live = true;
+        double ysc = 1.0;
+        if (MODE == A2_LSQR) {
+            const LsqrState* p = st + (int64_t)cur * K + j;
+            live = !p->stop;
+            ysc = 1.0;  // u~ unnormalized; k_bvec_v applies 1/beta
+        }
         // this wave's contiguous sub-range of the block chunk
         const int64_t len = c.e1 - c.e0;
         const int64_t sub = ((len + wpb - 1) / wpb + RS - 1) / RS * RS;
@@ -188,37 +192,41 @@ static __global__ __launch_bounds__(512) void k_baprod2_star(
             (r_beg < r_end && r_end < sys_end && star[r_end] == star[r_end - 1]) ? star[r_end - 1]
                                                                                 : -1;
         double* __restrict__ Xa = X + d.col0 * K + j;
-        // finished star: the lanes of row group 0 add it
+        // finished star: the lanes of row group 0 write it (S starts at zero in the LSQR and
+        // column-norm modes, so an owned star is stored)
         auto flush = [&](int32_t key, const double (&t)[kAstro]) {
-            if (rr != 0) return;
+            if (rr != 0 || !live) return;
             double* xa = Xa + (int64_t)kAstro * key * K;
             if (key == shared_first || key == shared_last) {
 #pragma unroll
                 for (int q = 0; q < kAstro; ++q) atomic_add_f64(xa + q * K, t[q]);
-            } else {
+            } else if (MODE == A2_ADD) {
 #pragma unroll
                 for (int q = 0; q < kAstro; ++q) xa[q * K] += t[q];
+            } else {
+#pragma unroll
+                for (int q = 0; q < kAstro; ++q) xa[q * K] = t[q];
             }
         };
         double acc[kAstro] = {0.0, 0.0, 0.0, 0.0, 0.0};
         int32_t ckey = -1;
         for (int64_t r0 = r_beg; r0 < r_end; r0 += RS) {
             const int64_t r = r0 + rr;
-            const bool valid = r < r_end;
+            const bool valid = live && r < r_end;
             int32_t key = -1;
             double v[kAstro] = {0.0, 0.0, 0.0, 0.0, 0.0};
             if (valid) {
-                const double* __restrict__ row = vals + r * kPar;
+                const VT* __restrict__ row = vals + r * kPar;
                 key = star[r];
-                const double yy = Y[r * K + j];
+                const double yy = (MODE == A2_SQ) ? 0.0 : ysc * Y[r * K + j];
 #pragma unroll
-                for (int q = 0; q < kAstro; ++q) v[q] = ld_val(row + q) * yy;
+                for (int q = 0; q < kAstro; ++q) v[q] = contrib<MODE>(ld_val(row + q), yy);
 #pragma unroll
                 for (int q = 0; q < kInstr; ++q) {
                     const int32_t ic = instr[r * kInstr + q];
-                    atomicAdd(lds + ic * K + j, ld_val(row + 17 + q) * yy);
+                    atomicAdd(lds + ic * K + j, contrib<MODE>(ld_val(row + 17 + q), yy));
                 }
-                gacc += ld_val(row + 23) * yy;
+                gacc += contrib<MODE>(ld_val(row + 23), yy);
             }
             run_step<kAstro, K>(key, v, acc, ckey, flush);
         }
@@ -227,16 +235,54 @@ static __global__ __launch_bounds__(512) void k_baprod2_star(
     if (cur >= 0) flush_lds();
 }
 
-// The t-ordered attitude copy: the 12 attitude coefficients of each t-ordered row, row after row
-// (each system's rows padded to whole tiles, as its row tiles are).
-constexpr int kAttRow = kAxes * kParAxis;
+// Batched row tiles: per system, kStepRows consecutive rows; every lane of a row needs all
+// of the row's coefficients, so a tile is [12 pairs][16 rows][2] (one 256-byte block per
+// load instruction) and the index tile [16 rows][8] = (star, att, instr0..5).
+constexpr int kBTileVals = kStepRows * kPar;  // 384 doubles
+constexpr int kBTileIdx = kStepRows * 8;      // 128 int32
 
-static __global__ void k_make_batt_rows(int64_t m, int64_t row0, const double* __restrict__ vals,
-                                        const int32_t* __restrict__ rowT,
-                                        double* __restrict__ at) {
+static __global__ void k_make_btiles(int64_t m, int64_t ntiles, const double* __restrict__ vals,
+                                     const int32_t* __restrict__ star,
+                                     const int32_t* __restrict__ att,
+                                     const int32_t* __restrict__ instr, double* __restrict__ vt,
+                                     int32_t* __restrict__ it) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m * kAttRow; e += stride)
-        at[e] = vals[(int64_t)rowT[row0 + e / kAttRow] * kPar + kAstro + e % kAttRow];
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < ntiles * kBTileVals;
+         e += stride) {
+        const int64_t tile = e / kBTileVals;
+        const int o = (int)(e - tile * kBTileVals);
+        const int pair = o / (2 * kStepRows), rg = (o / 2) % kStepRows, h = o % 2;
+        const int64_t row = tile * kStepRows + rg;
+        vt[e] = row < m ? vals[row * kPar + 2 * pair + h] : 0.0;
+    }
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < ntiles * kBTileIdx;
+         e += stride) {
+        const int64_t tile = e / kBTileIdx;
+        const int o = (int)(e - tile * kBTileIdx);
+        const int rg = o / 8, c = o % 8;
+        const int64_t row = min(tile * kStepRows + rg, m - 1);
+        it[e] = c == 0 ? star[row] : c == 1 ? att[row] : instr[row * kInstr + c - 2];
+    }
+}
+
+// Attitude tiles of the t-ordered copy, per system as the row tiles: [6 pairs][16 rows][2]
+// holding the 12 attitude coefficients of t-ordered rows row0 + 16 tile + rg (global row
+// numbers in rowT).
+constexpr int kBTileAtt = kStepRows * kAxes * kParAxis;  // 192 doubles
+
+static __global__ void k_make_batt_tiles(int64_t m, int64_t ntiles, int64_t row0,
+                                         const double* __restrict__ vals,
+                                         const int32_t* __restrict__ rowT,
+                                         double* __restrict__ at) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < ntiles * kBTileAtt;
+         e += stride) {
+        const int64_t tile = e / kBTileAtt;
+        const int o = (int)(e - tile * kBTileAtt);
+        const int pair = o / (2 * kStepRows), rg = (o / 2) % kStepRows, h = o % 2;
+        const int64_t lr = tile * kStepRows + rg;
+        at[e] = lr < m ? vals[(int64_t)rowT[row0 + lr] * kPar + kAstro + 2 * pair + h] : 0.0;
+    }
 }
 
 // R consecutive doubles (16-byte pieces when R is even; p then 16-byte aligned).
@@ -265,525 +311,409 @@ __device__ __forceinline__ void st_r(double* __restrict__ p, const double (&v)[R
     }
 }
 
-// Column of XT = p o V, the operand of the row pass (the library's own), that holds column c of
-// system d: the attitude columns lie knot by knot (the three axes of a knot together), so that a
-// row's twelve are one contiguous piece (eight right-hand sides: 768 bytes, 6 to 7 cache lines;
-// axis by axis 9, and in planes of two right-hand sides 10).
-__device__ __forceinline__ int64_t xt_col(const SysDesc& d, int64_t c) {
-    const int64_t t = c - d.att0;
-    if (t < 0 || t >= (int64_t)kAxes * d.T) return c;
-    const int ax = t >= 2 * (int64_t)d.T ? 2 : t >= d.T ? 1 : 0;
-    return d.att0 + kAxes * (t - (int64_t)ax * d.T) + ax;
-}
-
-// Batched row pass: for every (row, right-hand side j) of a round
-//   U[r, j] = sv_j (A XT)[r, j] - alpha_j su_j U[r, j]   (BR_LSQR; BR_T: U as it is, BR_SQ: the
-//   squared coefficients, no U)
-// and S += A^T U except the attitude columns, reading each row once.  Sum U^2 per (round, j) ->
-// partials.  Pairs that have stopped keep their U and contribute nothing.
-// The quad of a row holds its coefficients as in the single-system pass (TileRow).
-//   K <= 2 : as there, each lane takes its own columns of the row, for all right-hand sides, and
-//            the quad adds up;
-//   K >= 4 : each lane takes R = K / 4 right-hand sides and all columns of the row, the
-//            coefficients passed round the quad by DPP: a load instruction then reads whole
-//            pieces of 16 R bytes per column, and the row's u~ needs no sum over lanes (with the
-//            columns split and eight right-hand sides per lane: 1.82 ms against 1.61).
-// A round (one entry of `rounds`, consecutive rows of one system) keeps its stars' sums in LDS
-// and writes them at its end; with K <= 2 its U too, as the single-system pass does (with K >= 4
-// a wave step's U is one piece of 512 bytes or more and is written at once: no slower, and the
-// LDS holds longer rounds).  The instrumental sums of the current system stay in LDS until the
-// block moves to another system.
-// Star sums: a star's rows within the wave step are a contraction (coefficients x rows times
-// rows x right-hand sides), taken by the 4 x 4 x 4 binary64 matrix instruction, whose operand
-// layout is the one the row's lanes already have: lane l holds coefficient l % 4 of row l / 4,
-// in block (l / 4) % 4 and place l / 16 of it, and right-hand side l % 4 of the same row; the
-// four blocks are added over the lanes and one lane per sum adds it to the star's LDS slot
-// (with every lane adding its own product, sixteen LDS atomics fall on one address, 47 clocks
-// per instruction against 9 on separate ones).
-// What bounds it with K = 8: the vector memory path.  16 systems of 1.31e7 rows: 1.61 ms
-// (2.9 TB/s of the algorithmic bytes); without its LDS work 1.49, without the attitude columns'
-// cache misses 1.33, without any gather (BR_T) 0.63.  64 systems of 1.76e6 rows with K = 2: 127
-// (coefficients of a whole row in every lane, sums of stars over lanes) -> 98 us.  BR_T against
-// the star-ordered pass with 8 row groups per wave: 1.19 -> 0.63 ms.
-// Rounds are dealt to the blocks so that each die takes an eighth of them in system order and
-// its blocks move through the systems together, sharing each system's columns in the die's L2.
-enum { BR_LSQR = 0, BR_T = 1, BR_SQ = 2 };
-constexpr int kBRowBlock = 1024;
-
-struct BRowArgs {
-    const SysDesc* sys;
-    const Seg* rounds;
-    int nrounds;
-    const double* tiles;
-    const int32_t* star;
-    const double* XT;
-    double *U, *S;
-    const LsqrState* st;
-    double* partials;
-    int I;      // most instrumental columns of a system
-    int rows;   // most rows of a round (LDSI or not)
-    int nsb;    // stars of a round with a slot
-};
-
-// LDS doubles of a block: sums, sums of squares, staged XT, U of the round, star slots.
-__host__ __device__ constexpr int64_t brow_fixed(int k, int I, bool ldsi) {
-    return (int64_t)k * (I + 1) + k + (k * (I + 1)) % 2 + k % 2 +
-           (ldsi ? (int64_t)k * I + (k * I) % 2 : 0);
-}
-
-// The value of one lane of each quad (quad_perm [s,s,s,s] = s * 0x55), in all its lanes.
+// The three coefficient pairs m[] held by quad lane CTRL / 0x55, broadcast to the whole quad
+// as six doubles (quad_perm [s,s,s,s] = s * 0x55).
 template <int CTRL>
-__device__ __forceinline__ int32_t quad_lane(int32_t v) {
-    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
+__device__ __forceinline__ void bcast_pairs(const f64x2 (&m)[3], double* __restrict__ out) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        out[2 * i] = dpp_f64<CTRL>(m[i].x);
+        out[2 * i + 1] = dpp_f64<CTRL>(m[i].y);
+    }
 }
 
-// A value that is the same in all lanes of a wave, in scalar registers.
-__device__ __forceinline__ int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ int64_t uniform(int64_t v) {
-    return (int64_t)(uint32_t)uniform((int32_t)v) | (int64_t)uniform((int32_t)(v >> 32)) << 32;
-}
-__device__ __forceinline__ double uniform(double v) {
-    return __hiloint2double(uniform(__double2hiint(v)), uniform(__double2loint(v)));
-}
-
-template <int K, int MODE, bool LDSI>
-static __global__ __launch_bounds__(kBRowBlock) void k_browpass(BRowArgs p) {
-    constexpr int L = K >= 4 ? 4 : 1;  // lanes of a quad that share out the right-hand sides
-    constexpr int R = K / L;           // right-hand sides of a lane
-    constexpr bool kDot = MODE == BR_LSQR;
-    constexpr bool kBurst = kDot && L == 1;
+// Fused batched row pass: for every (row, rhs j) of a block chunk
+//   U[r, j] = sv_j (A XT)[r, j] - alpha_j su_j U[r, j]
+// and S += A^T U (astrometric: run accumulators; instrumental/global: LDS of the current
+// system), reading each row once.  Sum U^2 per (block chunk, j) -> partials.
+// Lane layout: L = min(K, 4) lanes per row, each lane R = K / L right-hand sides, so one row
+// costs 16-byte loads: the row's coefficients (with L = 4 each lane reads a quarter and the
+// quad exchanges them; otherwise all L lanes read the same 192 bytes), and per column the
+// lane's R consecutive values of the K-column block (RHS-minor storage).
+// Pairs that have stopped keep their U unchanged and contribute nothing.
+template <typename VT, int K>
+static __global__ __launch_bounds__(512) void k_baprod12(
+    const SysDesc* __restrict__ sys, const Seg* __restrict__ bchunks, int nbchunks,
+    const double* __restrict__ vt, const int32_t* __restrict__ it,
+    const int32_t* __restrict__ star,
+    const double* __restrict__ XT, double* __restrict__ U, double* __restrict__ S,
+    const LsqrState* __restrict__ st, double* __restrict__ partials, int max_instr) {
+    // [(max_instr + 1) * K] sums, [K] block sum U^2, [max_instr * K] instrumental part of XT
     extern __shared__ double lds[];
-    const int li = p.I + 1;
-    double* lsum = lds;                             // [I + 1][K]
-    double* lusq = lsum + K * li + (K * li) % 2;    // [K]
-    double* lxi = lusq + K + K % 2;                 // [I][K]
-    double* ubuf = lxi + (LDSI ? K * p.I + (K * p.I) % 2 : 0);  // [rows][K]
-    double* sbuf = ubuf + (kBurst ? (int64_t)p.rows * K : 0);  // [nsb][kAstro][K]
-    const int lane = threadIdx.x % kWave, rg = lane / kQuad, q = lane % kQuad;
-    const int j0 = L == 1 ? 0 : q * R;
-    const int w = threadIdx.x / kWave, nw = blockDim.x / kWave;
+    constexpr int L = K >= 4 ? 4 : K;
+    constexpr int R = K / L;
+    constexpr int RS = kWave / L;
+    const int lane = threadIdx.x % kWave, rr = lane / L, j0 = (lane % L) * R;
+    const int w = threadIdx.x / kWave, wpb = blockDim.x / kWave;
+    // Each XCD takes an eighth of the block chunks (in system order) and deals them to its
+    // blocks in turn, so that its blocks move through the systems together and share each
+    // system's attitude columns in the XCD's L2 (consecutive blocks go to consecutive XCDs).
     const int ngrp = min((int)gridDim.x, kXcd);
     const int grp = blockIdx.x % ngrp, gi = blockIdx.x / ngrp;
     const int nbg = gridDim.x / ngrp + (grp < (int)gridDim.x % ngrp ? 1 : 0);
-    const int rd_beg = (int)((int64_t)p.nrounds * grp / ngrp);
-    const int rd_end = (int)((int64_t)p.nrounds * (grp + 1) / ngrp);
-    for (int e = threadIdx.x; e < K * li + (K * li) % 2 + K; e += blockDim.x) lds[e] = 0.0;
-    for (int e = threadIdx.x; e < kAstro * K * p.nsb; e += blockDim.x) sbuf[e] = 0.0;
+    const int bc_beg = (int)((int64_t)nbchunks * grp / ngrp);
+    const int bc_end = (int)((int64_t)nbchunks * (grp + 1) / ngrp);
+    const int nl = (max_instr + 1) * K;
+    double* lusq = lds + nl;
+    double* lxi = lusq + K;
+    for (int e = threadIdx.x; e < nl + K; e += blockDim.x) lds[e] = 0.0;
     __syncthreads();
     int cur = -1;
     SysDesc d = {};
-    auto flush_sums = [&]() {  // instrumental then global columns, contiguous in S
-        double* xi = p.S + (d.col0 + d.ins0) * K;
-        for (int e = threadIdx.x; e < (d.I + 1) * K; e += blockDim.x) {
-            double* l = lsum + (e < d.I * K ? e : e + (p.I - d.I) * K);
-            const double v = *l;
+    double gacc[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) gacc[i] = 0.0;
+    auto flush_lds = [&]() {
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            double gs = gacc[i];
+#pragma unroll
+            for (int off = L; off < kWave; off <<= 1) gs += __shfl_xor(gs, off, kWave);
+            if (lane < L) atomicAdd(lds + d.I * K + j0 + i, gs);
+            gacc[i] = 0.0;
+        }
+        __syncthreads();
+        const int ne = (d.I + 1) * K;
+        double* xi = S + (d.col0 + d.ins0) * K;  // instrumental then global: contiguous
+        for (int e = threadIdx.x; e < ne; e += blockDim.x) {
+            const double v = lds[e];
             if (v != 0.0) atomic_add_f64(xi + e, v);
-            *l = 0.0;
+            lds[e] = 0.0;
         }
         __syncthreads();
     };
-    for (int rd = rd_beg + gi; rd < rd_end; rd += nbg) {
-        Seg c = p.rounds[rd];
-        c = {uniform(c.e0), uniform(c.e1), uniform(c.sys), 0};
+    for (int bc = bc_beg + gi; bc < bc_end; bc += nbg) {
+        const Seg c = bchunks[bc];
         if (c.sys != cur) {
-            if (cur >= 0) flush_sums();
+            if (cur >= 0) flush_lds();
             cur = c.sys;
-            const SysDesc t = p.sys[cur];
-            d.row0 = uniform(t.row0);
-            d.m = uniform(t.m);
-            d.col0 = uniform(t.col0);
-            d.att0 = uniform(t.att0);
-            d.ins0 = uniform(t.ins0);
-            d.glb0 = uniform(t.glb0);
-            d.I = uniform(t.I);
-            d.btile0 = uniform(t.btile0);
-            if (kDot && LDSI) {
-                const double* xs_i = p.XT + (d.col0 + d.ins0) * K;
-                for (int e = threadIdx.x; e < d.I * K; e += blockDim.x) lxi[e] = xs_i[e];
-                __syncthreads();
-            }
+            d = sys[cur];
+            // the system's instrumental columns of XT, read from LDS below
+            const double* xs_i = XT + (d.col0 + d.ins0) * K;
+            for (int e = threadIdx.x; e < d.I * K; e += blockDim.x) lxi[e] = xs_i[e];
+            __syncthreads();
         }
-        // this lane's right-hand sides j0 .. j0 + R - 1 (K <= 2: all of them)
-        const LsqrState* ps = p.st + (int64_t)cur * K;
-        bool live[R], any_live = MODE == BR_SQ;
-        double xs[R], ys[R], xglob[R];
-#pragma unroll
-        for (int j = 0; j < K; ++j) any_live = any_live || !ps[j].stop;
-        if (!any_live) continue;
+        bool live[R];
+        double xs[R], ys[R];
+        bool any_live = false;
 #pragma unroll
         for (int i = 0; i < R; ++i) {
-            live[i] = MODE == BR_SQ || !ps[j0 + i].stop;
-            if (kDot) {
-                xs[i] = ps[j0 + i].sv;
-                ys[i] = ps[j0 + i].alpha * ps[j0 + i].su;
-                xglob[i] = p.XT[(d.col0 + d.glb0) * K + j0 + i];
-            }
+            const LsqrState* ps = st + (int64_t)cur * K + j0 + i;
+            live[i] = !ps->stop;
+            xs[i] = ps->sv;
+            ys[i] = ps->alpha * ps->su;
+            any_live = any_live || live[i];
         }
-        const int64_t R0 = c.e0, R1 = c.e1;
-        const int64_t T0 = d.btile0 + (R0 - d.row0) / kStepRows;
-        const int nt = (int)((R1 - R0 + kStepRows - 1) / kStepRows);
-        const int32_t S0 = uniform(p.star[R0]), S1 = uniform(p.star[R1 - 1]);
-        const bool shf = R0 > d.row0 && p.star[R0 - 1] == S0;
-        const bool shl = R1 < d.row0 + d.m && p.star[R1] == S1;
-        const double* __restrict__ Xs = p.XT + d.col0 * K + j0;
-        double usq[R] = {};
-        const double* __restrict__ xi = (LDSI ? lxi : p.XT + (d.col0 + d.ins0) * K) + j0;
-        for (int t = w; t < nt; t += nw) {
-            TileRow a;
-            ld_tile(p.tiles, T0 + t, lane, a);
-            ld_tile_idx(p.tiles, T0 + t, lane, a);
-            const int64_t r = R0 + (int64_t)t * kStepRows + rg;
-            const bool valid = r < R1;
-            const int32_t s_first = __builtin_amdgcn_readlane(a.star, 0);
-            const int32_t s_last = __builtin_amdgcn_readlane(a.star, kWave - 1);
-            const bool two = q == 1 || q == 2;  // lanes with a second instrumental coefficient
-            const double* xa = Xs + (int64_t)kAstro * a.star * K;
-            const double* xt = Xs + (d.att0 + (int64_t)kAxes * a.att) * K;
-            double un[R], sum[R];
-            if (MODE != BR_SQ) ld_r<R>(p.U + min(r, R1 - 1) * K + j0, un);
-            // all loads without branches: a load under a lane condition would wait for the
-            // ones before it
-            if constexpr (kDot && L == 1) {
-                double x0[R], x4[R], e01[2 * R], e2[R], wx[R], wb[R];
-                ld_r<R>(xa + q * K, x0);
-                ld_r<R>(xa + 4 * K, x4);
-                if constexpr (R == 1) {
-                    typedef f64x2 __attribute__((aligned(8))) f64x2u;
-                    const f64x2 v = *reinterpret_cast<const f64x2u*>(xt + 2 * q);
-                    e01[0] = v.x;
-                    e01[1] = v.y;
-                } else {
-                    ld_r<2 * R>(xt + 2 * q * R, e01);
-                }
-                ld_r<R>(xt + (8 + q) * R, e2);
-                __builtin_amdgcn_sched_barrier(0);
-                ld_r<R>(xi + a.ia * K, wx);
-                ld_r<R>(xi + (two ? a.ib : a.ia) * K, wb);
+        if constexpr (L == 4) {
+            // the quad of a row shares its loads: it goes through the row while any pair of
+            // the system is live (a lane whose own pairs have stopped adds zeros)
 #pragma unroll
-                for (int i = 0; i < R; ++i) {
-                    double v = a.as * x0[i];
-                    v = fma(a.e0, e01[i], v);
-                    v = fma(a.e1, e01[R + i], v);
-                    v = fma(a.e2, e2[i], v);
-                    v = fma(a.wi, wx[i], v);
-                    v = fma(a.z, q == 0 ? x4[i] : two ? wb[i] : xglob[i], v);
-                    sum[i] = quad_sum(v);
-                }
-            }
-            int ic[kInstr];      // K >= 4: the row's instrumental columns and coefficients
-            double ci[kInstr];
-            if constexpr (L == 4) {
-                ic[0] = quad_lane<0x00>(a.ia);
-                ic[1] = quad_lane<0x55>(a.ia);
-                ic[2] = quad_lane<0xAA>(a.ia);
-                ic[3] = quad_lane<0xFF>(a.ia);
-                ic[4] = quad_lane<0x55>(a.ib);
-                ic[5] = quad_lane<0xAA>(a.ib);
-                ci[0] = dpp_f64<0x00>(a.wi);
-                ci[1] = dpp_f64<0x55>(a.wi);
-                ci[2] = dpp_f64<0xAA>(a.wi);
-                ci[3] = dpp_f64<0xFF>(a.wi);
-                ci[4] = dpp_f64<0x55>(a.z);
-                ci[5] = dpp_f64<0xAA>(a.z);
-            }
-            if constexpr (kDot && L == 4) {
-                double x[kAxes * kParAxis + kAstro][R];
+            for (int j = 0; j < K; ++j) any_live = any_live || !st[(int64_t)cur * K + j].stop;
+        }
+        const int64_t len = c.e1 - c.e0;
+        const int64_t sub = ((len + wpb - 1) / wpb + RS - 1) / RS * RS;
+        const int64_t r_beg = min(c.e1, c.e0 + w * sub), r_end = min(c.e1, r_beg + sub);
+        const int64_t sys_end = d.row0 + d.m;
+        const int32_t shared_first =
+            (r_beg < r_end && r_beg > d.row0 && star[r_beg - 1] == star[r_beg]) ? star[r_beg] : -1;
+        const int32_t shared_last =
+            (r_beg < r_end && r_end < sys_end && star[r_end] == star[r_end - 1]) ? star[r_end - 1]
+                                                                                : -1;
+        const double* __restrict__ Xs = XT + d.col0 * K + j0;
+        double* __restrict__ Sa = S + d.col0 * K + j0;
+        auto flush = [&](int32_t key, const double (&t)[kAstro * R]) {
+            if (rr != 0) return;
+            double* xa = Sa + (int64_t)kAstro * key * K;
+            const bool shared = key == shared_first || key == shared_last;
 #pragma unroll
-                for (int e = 0; e < kAxes * kParAxis; ++e) ld_r<R>(xt + e * K, x[e]);
+            for (int i = 0; i < R; ++i) {
+                if (!live[i]) continue;
 #pragma unroll
-                for (int e = 0; e < kAstro; ++e) ld_r<R>(xa + e * K, x[kAxes * kParAxis + e]);
-#pragma unroll
-                for (int i = 0; i < R; ++i) sum[i] = dpp_f64<0xFF>(a.z) * xglob[i];
-#pragma unroll
-                for (int k = 0; k < kInstr; ++k) {
-                    double v[R];
-                    ld_r<R>(xi + ic[k] * K, v);
-#pragma unroll
-                    for (int i = 0; i < R; ++i) sum[i] = fma(ci[k], v[i], sum[i]);
-                }
-                auto add = [&](double c, const double (&v)[R]) {
-#pragma unroll
-                    for (int i = 0; i < R; ++i) sum[i] = fma(c, v[i], sum[i]);
-                };
-                add(dpp_f64<0x00>(a.e0), x[0]);
-                add(dpp_f64<0x00>(a.e1), x[1]);
-                add(dpp_f64<0x55>(a.e0), x[2]);
-                add(dpp_f64<0x55>(a.e1), x[3]);
-                add(dpp_f64<0xAA>(a.e0), x[4]);
-                add(dpp_f64<0xAA>(a.e1), x[5]);
-                add(dpp_f64<0xFF>(a.e0), x[6]);
-                add(dpp_f64<0xFF>(a.e1), x[7]);
-                add(dpp_f64<0x00>(a.e2), x[8]);
-                add(dpp_f64<0x55>(a.e2), x[9]);
-                add(dpp_f64<0xAA>(a.e2), x[10]);
-                add(dpp_f64<0xFF>(a.e2), x[11]);
-                add(dpp_f64<0x00>(a.as), x[12]);
-                add(dpp_f64<0x55>(a.as), x[13]);
-                add(dpp_f64<0xAA>(a.as), x[14]);
-                add(dpp_f64<0xFF>(a.as), x[15]);
-                add(dpp_f64<0x00>(a.z), x[16]);
-            }
-            if (kDot) {
-#pragma unroll
-                for (int i = 0; i < R; ++i) {
-                    const double u = (ys[i] != 0.0) ? xs[i] * sum[i] - ys[i] * un[i]
-                                                    : xs[i] * sum[i];
-                    un[i] = live[i] ? u : un[i];
-                }
-                if (kBurst) {
-                    if (q == 0) st_r<R>(ubuf + (t * kStepRows + rg) * K, un);
-                } else if (valid) {
-                    double* up = p.U + r * K + j0;
-                    if constexpr (R == 2)
-                        __builtin_nontemporal_store(f64x2{un[0], un[1]}, reinterpret_cast<f64x2*>(up));
+                for (int q = 0; q < kAstro; ++q) {
+                    if (shared)
+                        atomic_add_f64(xa + q * K + i, t[i * kAstro + q]);
                     else
-                        __builtin_nontemporal_store(un[0], up);
+                        xa[q * K + i] = t[i * kAstro + q];  // S is zero here
                 }
             }
-            double ul[R];
+        };
+        // the lane's R values of column `col` of XT
+        auto xv = [&](int64_t col, double (&o)[R]) { ld_r<R>(Xs + col * K, o); };
+        double acc[kAstro * R];
 #pragma unroll
-            for (int i = 0; i < R; ++i) {
-                ul[i] = MODE == BR_SQ ? 1.0 : (live[i] && valid) ? un[i] : 0.0;
-                if (!kBurst && kDot) usq[i] = fma(ul[i], ul[i], usq[i]);
-            }
-            if (MODE == BR_SQ) {
-                a.as *= a.as;
-                a.z *= a.z;
-                a.wi *= a.wi;
-            }
-            if constexpr (L == 4) {
-                // odd rows take their right-hand sides in the other order: the lanes of an
-                // atomic then spread over all banks
-                double* lj = lsum + j0;
-                const int odd = R == 2 ? rg & 1 : 0;
-                const double u0 = odd ? ul[R - 1] : ul[0], u1 = odd ? ul[0] : ul[R - 1];
+        for (int q = 0; q < kAstro * R; ++q) acc[q] = 0.0;
+        int32_t ckey = -1;
+        double usq[R];
+#pragma unroll
+        for (int i = 0; i < R; ++i) usq[i] = 0.0;
+        for (int64_t r0 = r_beg; r0 < r_end; r0 += RS) {
+            const int64_t r = r0 + rr;
+            const bool valid = any_live && r < r_end;
+            int32_t key = -1;
+            double v[kAstro * R];
+#pragma unroll
+            for (int q = 0; q < kAstro * R; ++q) v[q] = 0.0;
+            if (valid) {
+                // the row's tile (the system's rows are padded to whole tiles)
+                const int64_t lr = r - d.row0;
+                const int64_t tile = d.btile0 + lr / kStepRows;
+                const int rgl = (int)(lr % kStepRows);
+                double a[kPar];
+                int32_t sr, tr, ins[kInstr];
+                const f64x2* vp = reinterpret_cast<const f64x2*>(vt + tile * kBTileVals) + rgl;
+                const int32_t* ip = it + tile * kBTileIdx + rgl * 8;
+                if constexpr (L == 4) {
+                    // the row's quad splits its loads (lane q: coefficient pairs 3q..3q+2 and
+                    // index slots 2q, 2q+1) and exchanges them with DPP quad broadcasts
+                    const int q = lane & 3;
+                    const f64x2 m[3] = {__builtin_nontemporal_load(vp + (3 * q) * kStepRows),
+                                        __builtin_nontemporal_load(vp + (3 * q + 1) * kStepRows),
+                                        __builtin_nontemporal_load(vp + (3 * q + 2) * kStepRows)};
+                    const i32x2 iv =
+                        __builtin_nontemporal_load(reinterpret_cast<const i32x2*>(ip) + q);
+                    bcast_pairs<0x00>(m, a + 0);
+                    bcast_pairs<0x55>(m, a + 6);
+                    bcast_pairs<0xAA>(m, a + 12);
+                    bcast_pairs<0xFF>(m, a + 18);
+                    sr = __builtin_amdgcn_update_dpp(0, iv.x, 0x00, 0xF, 0xF, false);
+                    tr = __builtin_amdgcn_update_dpp(0, iv.y, 0x00, 0xF, 0xF, false);
+                    ins[0] = __builtin_amdgcn_update_dpp(0, iv.x, 0x55, 0xF, 0xF, false);
+                    ins[1] = __builtin_amdgcn_update_dpp(0, iv.y, 0x55, 0xF, 0xF, false);
+                    ins[2] = __builtin_amdgcn_update_dpp(0, iv.x, 0xAA, 0xF, 0xF, false);
+                    ins[3] = __builtin_amdgcn_update_dpp(0, iv.y, 0xAA, 0xF, 0xF, false);
+                    ins[4] = __builtin_amdgcn_update_dpp(0, iv.x, 0xFF, 0xF, 0xF, false);
+                    ins[5] = __builtin_amdgcn_update_dpp(0, iv.y, 0xFF, 0xF, 0xF, false);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < kPar / 2; ++k) {
+                        const f64x2 t = __builtin_nontemporal_load(vp + k * kStepRows);
+                        a[2 * k] = t.x;
+                        a[2 * k + 1] = t.y;
+                    }
+                    typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+                    const i32x4* ip4 = reinterpret_cast<const i32x4*>(ip);
+                    const i32x4 i0 = __builtin_nontemporal_load(ip4);
+                    const i32x4 i1 = __builtin_nontemporal_load(ip4 + 1);
+                    sr = i0.x;
+                    tr = i0.y;
+                    ins[0] = i0.z;
+                    ins[1] = i0.w;
+                    ins[2] = i1.x;
+                    ins[3] = i1.y;
+                    ins[4] = i1.z;
+                    ins[5] = i1.w;
+                }
+                double sum[R], xv_[R];
+#pragma unroll
+                for (int i = 0; i < R; ++i) sum[i] = 0.0;
+                auto add = [&](double coef, int64_t col) {
+                    xv(col, xv_);
+#pragma unroll
+                    for (int i = 0; i < R; ++i) sum[i] = fma(coef, xv_[i], sum[i]);
+                };
+#pragma unroll
+                for (int k = 0; k < kAstro; ++k) add(a[k], (int64_t)kAstro * sr + k);
+#pragma unroll
+                for (int ax = 0; ax < kAxes; ++ax)
+#pragma unroll
+                    for (int k = 0; k < kParAxis; ++k)
+                        add(a[kAstro + ax * kParAxis + k], d.att0 + (int64_t)ax * d.T + tr + k);
 #pragma unroll
                 for (int k = 0; k < kInstr; ++k) {
-                    double* l = lj + ic[k] * K;
-                    atomicAdd(l + odd, ci[k] * u0);
-                    if (R == 2) atomicAdd(l + (1 - odd), ci[k] * u1);
+                    double xl[R];
+#pragma unroll
+                    for (int i = 0; i < R; ++i) xl[i] = lxi[ins[k] * K + j0 + i];
+#pragma unroll
+                    for (int i = 0; i < R; ++i) sum[i] = fma(a[17 + k], xl[i], sum[i]);
                 }
-            } else {
+                add(a[23], d.glb0);
+                double* up = U + r * K + j0;
+                double uo[R], un[R];
+                ld_r<R>(up, uo);
 #pragma unroll
                 for (int i = 0; i < R; ++i) {
-                    atomicAdd(lsum + a.ia * K + i, a.wi * ul[i]);
-                    if (two) atomicAdd(lsum + a.ib * K + i, a.z * ul[i]);
-                }
-            }
-            // stars and the global column; lane l of a product of the matrix instruction holds
-            // right-hand side jq of coefficient l / 16, in block (l / 4) % 4
+                    un[i] = !live[i]       ? uo[i]
+                            : (ys[i] != 0.0) ? xs[i] * sum[i] - ys[i] * uo[i]
+                                             : xs[i] * sum[i];
+                    const double ul = live[i] ? un[i] : 0.0;
+                    usq[i] = fma(ul, ul, usq[i]);
 #pragma unroll
-            for (int i = 0; i < (L == 4 ? R : 1); ++i) {
-                const double y = L == 4 ? ul[i] : R == 2 && (q & 1) ? ul[R - 1] : ul[0];
-                const int jq = L == 4 ? j0 + i : q, co = lane / 16;
-                const bool mine = (lane & 12) == 0 && jq < K;
-                for (int32_t cs = s_first;;) {  // each star of the wave step
-                    const bool in = a.star == cs;
-                    const double ym = in ? y : 0.0;
-                    double ta = __builtin_amdgcn_mfma_f64_4x4x4f64(in ? a.as : 0.0, ym, 0.0, 0, 0, 0);
-                    double tz = __builtin_amdgcn_mfma_f64_4x4x4f64(in ? a.z : 0.0, ym, 0.0, 0, 0, 0);
-                    ta += dpp_f64<0x124>(ta);
-                    ta += dpp_f64<0x128>(ta);
-                    tz += dpp_f64<0x124>(tz);
-                    tz += dpp_f64<0x128>(tz);
-                    const int o = cs - S0;
-                    if (o < p.nsb) {
-                        if (mine) {
-                            atomicAdd(sbuf + (kAstro * o + co) * K + jq, ta);
-                            if (co == 0) atomicAdd(sbuf + (kAstro * o + 4) * K + jq, tz);
-                        }
-                    } else {  // past the last slot: straight to S, which is zero there
-                        keep_apart();
-                        if (mine) {
-                            double* xo = p.S + (d.col0 + (int64_t)kAstro * cs) * K + jq;
-                            atomic_add_f64(xo + co * K, ta);
-                            if (co == 0) atomic_add_f64(xo + 4 * K, tz);
-                        }
-                        keep_apart();
-                    }
-                    if (mine && co == 3) atomicAdd(lsum + p.I * K + jq, tz);
-                    if (cs == s_last) break;
-                    const uint64_t more = __ballot(a.star > cs);
-                    cs = __builtin_amdgcn_readlane(a.star, __ffsll((unsigned long long)more) - 1);
+                    for (int q = 0; q < kAstro; ++q) v[i * kAstro + q] = a[q] * ul;
+                    gacc[i] = fma(a[23], ul, gacc[i]);
                 }
+                st_r<R>(up, un);
+                key = sr;
+#pragma unroll
+                for (int k = 0; k < kInstr; ++k)
+#pragma unroll
+                    for (int i = 0; i < R; ++i)
+                        if (live[i]) atomicAdd(lds + ins[k] * K + j0 + i, a[17 + k] * un[i]);
             }
+            run_step<kAstro * R, L>(key, v, acc, ckey, flush);
+        }
+        run_close<kAstro * R, L>(acc, ckey, flush);
+        // block sum of U^2 for this block chunk
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            double t = usq[i];
+#pragma unroll
+            for (int off = L; off < kWave; off <<= 1) t += __shfl_xor(t, off, kWave);
+            if (lane < L) atomicAdd(lusq + j0 + i, t);
         }
         __syncthreads();
-        if (kDot && !kBurst) {
-#pragma unroll
-            for (int i = 0; i < R; ++i) {
-#pragma unroll
-                for (int off = kQuad; off < kWave; off <<= 1)
-                    usq[i] += __shfl_xor(usq[i], off, kWave);
-                if (lane < kQuad) atomicAdd(lusq + j0 + i, usq[i]);
-            }
-        }
-        if (kBurst) {  // the round's U in one burst, and its sum of squares
-            constexpr int W = K >= 2 ? 2 : 1, P = K / W;
-            double acc[W] = {};
-            typedef double vec __attribute__((ext_vector_type(W)));
-            vec* dst = reinterpret_cast<vec*>(p.U + R0 * K);
-            const vec* src = reinterpret_cast<const vec*>(ubuf);
-            for (int e = threadIdx.x; e < (int)(R1 - R0) * P; e += blockDim.x) {
-                const vec v = src[e];
-                __builtin_nontemporal_store(v, dst + e);
-#pragma unroll
-                for (int i = 0; i < W; ++i) acc[i] = fma(v[i], v[i], acc[i]);
-            }
-#pragma unroll
-            for (int i = 0; i < W; ++i) {
-#pragma unroll
-                for (int off = P; off < kWave; off <<= 1) acc[i] += __shfl_xor(acc[i], off, kWave);
-                if (lane < P) atomicAdd(lusq + lane * W + i, acc[i]);
-            }
-        }
-        // finished stars: owned ones are stored (S is zero before the pass)
-        const int ns = min(S1 - S0 + 1, p.nsb);
-        const int e0 = shf ? kAstro * K : 0;
-        const int e1 = (shl ? S1 - S0 : S1 - S0 + 1) * kAstro * K;
-        double* xo = p.S + (d.col0 + (int64_t)kAstro * S0) * K;
-        for (int e = threadIdx.x; e < ns * kAstro * K; e += blockDim.x) {
-            const double v = sbuf[e];
-            sbuf[e] = 0.0;
-            if (e >= e0 && e < e1)
-                __builtin_nontemporal_store(v, xo + e);
-            else
-                atomic_add_f64(xo + e, v);
-        }
-        __syncthreads();
-        if (kDot && threadIdx.x < K) {
-            p.partials[(int64_t)rd * K + threadIdx.x] = lusq[threadIdx.x];
+        if (threadIdx.x < K) {
+            partials[(int64_t)bc * K + threadIdx.x] = lusq[threadIdx.x];
             lusq[threadIdx.x] = 0.0;
         }
+        __syncthreads();
     }
-    __syncthreads();
-    if (cur >= 0) flush_sums();
+    if (cur >= 0) flush_lds();
 }
 
-// Attitude pass over the t-ordered copy (each system's rows keep their own range): the 12
-// columns x K right-hand sides of a run of rows with one start t are a contraction over its
-// rows, 12 x rows times rows x K, and go through the binary64 matrix instruction, four rows at
-// a time: lane (i, k) = (lane % 16, lane / 16) holds coefficient i of row k and right-hand side
-// i of row k (one 8-byte load each, no value twice), and the sums of column q of axis r end in
-// register r of lane (j, q).  With the products in vector registers instead, every lane of a
-// row needed all 12 coefficients and 8 rows were in flight per wave.
-// Bound by memory: 1.31e7 rows with K = 8 0.70 -> 0.56 ms (3.9 TB/s); of these the coefficients
-// cost 0.21 ms, the order of U's rows 0.09 (against U read in order) and the atomics of the
-// finished runs 0.07.  1.76e6 rows with K = 2: 58 us before and after.
-template <int MODE, int K>
-static __global__ __launch_bounds__(256, 4) void k_baprod2_att(
+// Run accumulation as run_step (keys sorted within a wave step, -1 for rows that take no
+// part), with the step's values produced on demand by val(j) and each finished run's sum
+// passed on as soon as it is reduced, flush1(key, j, sum): neither the step's values nor the
+// reduced sums are held as arrays, which keeps the attitude pass at a few waves per SIMD.
+template <int NV, int STRIDE, typename V, typename F>
+__device__ __forceinline__ void run_step_lean(int32_t key, V&& val, double (&acc)[NV],
+                                              int32_t& ckey, F&& flush1) {
+    const uint64_t valid = __ballot(key >= 0);
+    if (valid == 0) return;
+    const int32_t kfirst =
+        __builtin_amdgcn_readlane(key, __ffsll((unsigned long long)valid) - 1);
+    const int32_t klast = __builtin_amdgcn_readlane(key, 63 - __clzll((unsigned long long)valid));
+    if (kfirst == ckey && klast == ckey) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j) acc[j] += val(j);
+        return;
+    }
+    if (ckey >= 0) {  // the open run ends in this step (or ended at its start)
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+            flush1(ckey, j, group_sum<STRIDE>(acc[j] + (key == ckey ? val(j) : 0.0)));
+    }
+    auto next_after = [&](int32_t k) {
+        const uint64_t gt = __ballot(key > k);
+        return (int32_t)__builtin_amdgcn_readlane(key, __ffsll((unsigned long long)gt) - 1);
+    };
+    int32_t k = (kfirst == ckey) ? next_after(ckey) : kfirst;
+    while (k != klast) {  // runs that start and end inside the step
+#pragma unroll
+        for (int j = 0; j < NV; ++j) flush1(k, j, group_sum<STRIDE>(key == k ? val(j) : 0.0));
+        k = next_after(k);
+    }
+#pragma unroll
+    for (int j = 0; j < NV; ++j) acc[j] = (key == klast) ? val(j) : 0.0;
+    ckey = klast;
+}
+
+template <int NV, int STRIDE, typename F>
+__device__ __forceinline__ void run_close_lean(double (&acc)[NV], int32_t& ckey, F&& flush1) {
+    if (ckey < 0) return;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) flush1(ckey, j, group_sum<STRIDE>(acc[j]));
+    ckey = -1;
+}
+
+// Attitude pass over the t-ordered copy (each system's rows keep their own range).  One lane
+// per right-hand side (L = K lanes per row, R = 1): each lane reads the row's 12 attitude
+// coefficients (16-byte loads) and its value of Y; with one right-hand side per lane the run
+// accumulators stay small enough for four waves per SIMD.
+template <typename VT, int MODE, int K>
+static __global__ __launch_bounds__(256) void k_baprod2_att(
     const SysDesc* __restrict__ sys, const Seg* __restrict__ chunks, int nchunks,
-    const double* __restrict__ attT, const int32_t* __restrict__ rowT,
+    const VT* __restrict__ attT, const int32_t* __restrict__ rowT,
     const int32_t* __restrict__ tT, const double* __restrict__ Y, double* __restrict__ X,
     const LsqrState* __restrict__ st) {
-    typedef double f64x4 __attribute__((ext_vector_type(4)));
-    constexpr int G = 8, B = 4 * G;  // groups of four rows, and rows, in flight
-    constexpr int NA = 2;            // sums a run is split over: shorter chains of additions
-    const int lane = threadIdx.x % kWave, i = lane % 16, kq = lane / 16;
-    const int ic = min(i, kAttRow - 1), j = min(i, K - 1);
+    constexpr int L = K;
+    constexpr int R = K / L;
+    constexpr int RS = kWave / L;
+    constexpr int NA = kAxes * kParAxis;
+    static_assert(sizeof(VT) == 8, "the batched attitude tiles are binary64");
+    const int lane = threadIdx.x % kWave, rr = lane / L, j0 = (lane % L) * R;
     const int wpb = blockDim.x / kWave;
     for (int ch = blockIdx.x * wpb + threadIdx.x / kWave; ch < nchunks; ch += gridDim.x * wpb) {
         const Seg c = chunks[ch];
         const SysDesc d = sys[c.sys];
-        const bool live = i < K && (MODE != A2_LSQR || !st[(int64_t)c.sys * K + j].stop);
-        if (!__any(live)) continue;
-        const double* __restrict__ A = attT + (d.btile0 * kStepRows - d.row0) * kAttRow + ic;
-        double* __restrict__ Xt = X + (d.col0 + d.att0) * K + j;
-        f64x4 acc[NA] = {};
-        int32_t ckey = -1;
-        auto flush = [&]() {
-            if (live && ckey >= 0)
+        bool live[R];
+        bool any_live = false;
 #pragma unroll
-                for (int ax = 0; ax < kAxes; ++ax)
-                    atomic_add_f64(Xt + ((int64_t)ax * d.T + ckey + kq) * K,
-                                   acc[0][ax] + acc[1][ax]);
-#pragma unroll
-            for (int h = 0; h < NA; ++h) acc[h] = {0.0, 0.0, 0.0, 0.0};
-        };
-        int64_t kn = min(c.e0 + lane % B, c.e1 - 1);
-        int32_t nkey = tT[kn], nrow = rowT[kn];
-        for (int64_t k0 = c.e0; k0 < c.e1; k0 += B) {
-            const int32_t key = k0 + lane % B < c.e1 ? nkey : -1;
-            const int32_t row = nrow;
-            double a[G], y[G];
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const int r = 4 * g + kq;
-                a[g] = __builtin_nontemporal_load(A + min(k0 + r, c.e1 - 1) * kAttRow);
-                if (MODE != A2_SQ) y[g] = Y[(int64_t)__shfl(row, r, kWave) * K + j];
-            }
-            kn = min(k0 + B + lane % B, c.e1 - 1);
-            nkey = tT[kn];
-            nrow = rowT[kn];
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                if (MODE == A2_SQ) {
-                    a[g] *= a[g];
-                    y[g] = 1.0;
-                } else {
-                    y[g] = live ? y[g] : 0.0;
-                }
-            }
-            const int32_t kf = __builtin_amdgcn_readlane(key, 0);
-            if (kf == __builtin_amdgcn_readlane(key, B - 1)) {  // one run, all rows present
-                if (kf != ckey) {
-                    flush();
-                    ckey = kf;
-                }
-#pragma unroll
-                for (int g = 0; g < G; ++g)
-                    acc[g % NA] =
-                        __builtin_amdgcn_mfma_f64_16x16x4f64(a[g], y[g], acc[g % NA], 0, 0, 0);
-                continue;
-            }
-            for (int pos = 0; pos < B;) {  // each run of the block
-                const int32_t k = __builtin_amdgcn_readlane(key, pos);
-                if (k < 0) break;
-                const uint32_t in = (uint32_t)__ballot(key == k);
-                if (k != ckey) {
-                    flush();
-                    ckey = k;
-                }
-#pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    if (((in >> (4 * g)) & 15) == 0) continue;
-                    const bool m = (in >> (4 * g + kq)) & 1;
-                    acc[g % NA] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                        m ? a[g] : 0.0, m ? y[g] : 0.0, acc[g % NA], 0, 0, 0);
-                }
-                pos = 32 - __clz(in);
-            }
+        for (int i = 0; i < R; ++i) {
+            live[i] = (MODE == A2_LSQR) ? !st[(int64_t)c.sys * K + j0 + i].stop : true;
+            any_live = any_live || live[i];
         }
-        flush();
+        // (A2_LSQR: u~ unnormalized; k_bvec_v applies 1/beta)
+        double* __restrict__ Xt = X + (d.col0 + d.att0) * K + j0;
+        // value j = i * NA + ax * kParAxis + q: right-hand side i, column t + q of axis ax
+        auto flush1 = [&](int32_t key, int j, double t) {
+            const int i = j / NA, ax = (j % NA) / kParAxis, q = j % kParAxis;
+            if (rr == 0 && live[i]) atomic_add_f64(Xt + ((int64_t)ax * d.T + key + q) * K + i, t);
+        };
+        double acc[NA * R];
+#pragma unroll
+        for (int q = 0; q < NA * R; ++q) acc[q] = 0.0;
+        int32_t ckey = -1;
+        for (int64_t k0 = c.e0; k0 < c.e1; k0 += RS) {
+            const int64_t k = k0 + rr;
+            const bool valid = any_live && k < c.e1;
+            int32_t key = -1;
+            double yy[R], a[NA];
+#pragma unroll
+            for (int i = 0; i < R; ++i) yy[i] = 0.0;
+#pragma unroll
+            for (int q = 0; q < NA; ++q) a[q] = 0.0;
+            if (valid) {
+                key = tT[k];
+                if (MODE == A2_SQ) {
+#pragma unroll
+                    for (int i = 0; i < R; ++i) yy[i] = 0.0;
+                } else {
+                    ld_r<R>(Y + (int64_t)rowT[k] * K + j0, yy);
+#pragma unroll
+                    for (int i = 0; i < R; ++i) yy[i] = live[i] ? yy[i] : 0.0;
+                }
+                {  // the row's attitude tile
+                    const int64_t lr = k - d.row0;
+                    const int64_t tile = d.btile0 + lr / kStepRows;
+                    const f64x2* ap = reinterpret_cast<const f64x2*>(attT + tile * kBTileAtt) +
+                                      (int)(lr % kStepRows);
+#pragma unroll
+                    for (int q = 0; q < NA / 2; ++q) {
+                        const f64x2 t = __builtin_nontemporal_load(ap + q * kStepRows);
+                        a[2 * q] = t.x;
+                        a[2 * q + 1] = t.y;
+                    }
+                }
+            }
+            auto val = [&](int j) { return contrib<MODE>(a[j % NA], yy[j / NA]); };
+            run_step_lean<NA * R, L>(key, val, acc, ckey, flush1);
+        }
+        run_close_lean<NA * R, L>(acc, ckey, flush1);
     }
 }
 
 // ---------------------------------------------------------------------------------------
 // vectors (one block per segment; elements e = index * K + j)
 
-// Per-segment, per-j block sums of NQ quantities -> part[(q * nseg + seg) * K + j]; a lane
-// holds W neighbouring right-hand sides, lane % (K / W) the first of them.
-template <int K, int W, int NQ>
-__device__ __forceinline__ void seg_partials(double (&acc)[NQ][W], double* sh, double* part,
+// Per-segment, per-j block sums of NQ quantities -> part[(q * nseg + seg) * K + j].
+template <int K, int NQ>
+__device__ __forceinline__ void seg_partials(double (&acc)[NQ], double* sh, double* part,
                                              int nseg, int seg) {
-    constexpr int P = K / W;
     const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
-    constexpr int NW = 256 / kWave;
+    constexpr int W = 256 / kWave;
 #pragma unroll
-    for (int q = 0; q < NQ; ++q)
+    for (int q = 0; q < NQ; ++q) {
+        double v = acc[q];
 #pragma unroll
-        for (int i = 0; i < W; ++i) {
-            double v = acc[q][i];
-#pragma unroll
-            for (int off = P; off < kWave; off <<= 1) v += __shfl_xor(v, off, kWave);
-            if (lane < P) sh[(q * NW + w) * K + lane * W + i] = v;
-        }
+        for (int off = K; off < kWave; off <<= 1) v += __shfl_xor(v, off, kWave);
+        if (lane < K) sh[(q * W + w) * K + lane] = v;
+    }
     __syncthreads();
     if (threadIdx.x < NQ * K) {
         const int q = threadIdx.x / K, j = threadIdx.x % K;
         double s = 0.0;
 #pragma unroll
-        for (int ww = 0; ww < NW; ++ww) s += sh[(q * NW + ww) * K + j];
+        for (int ww = 0; ww < W; ++ww) s += sh[(q * W + ww) * K + j];
         part[((int64_t)q * nseg + seg) * K + j] = s;
     }
     __syncthreads();
@@ -798,13 +728,13 @@ static __global__ __launch_bounds__(256) void k_bcopy_norm(const Seg* __restrict
     __shared__ double sh[4 * K * 1];
     for (int sg = blockIdx.x; sg < nseg; sg += gridDim.x) {
         const Seg c = segs[sg];
-        double acc[1][1] = {{0.0}};
+        double acc[1] = {0.0};
         for (int64_t e = c.e0 * K + threadIdx.x; e < c.e1 * K; e += blockDim.x) {
             const double v = B[e];
             U[e] = v;
-            acc[0][0] = fma(v, v, acc[0][0]);
+            acc[0] = fma(v, v, acc[0]);
         }
-        seg_partials<K, 1, 1>(acc, sh, part, nseg, sg);
+        seg_partials<K, 1>(acc, sh, part, nseg, sg);
     }
 }
 
@@ -817,69 +747,48 @@ static __global__ __launch_bounds__(256) void k_bvec_v(const Seg* __restrict__ t
                                                        double* __restrict__ Wv,
                                                        double* __restrict__ Z,
                                                        double* __restrict__ XT,
-                                                       const SysDesc* __restrict__ sys,
                                                        const LsqrState* __restrict__ st,
                                                        double* __restrict__ part) {
-    constexpr int W = K >= 2 ? 2 : 1, P = K / W;
     __shared__ double sh[4 * 4 * K];
-    const int j0 = threadIdx.x % P * W;
+    const int j = threadIdx.x % K;
     for (int sg = blockIdx.x; sg < ntile; sg += gridDim.x) {
         const Seg c = tiles[sg];
-        const SysDesc d = sys[c.sys];
-        bool live[W], pending[W], any_live = INIT;
-        double f1[W], f2[W], sv[W], c1[W], su[W];
-#pragma unroll
-        for (int i = 0; i < W; ++i) {
-            const LsqrState* ps = st + (int64_t)c.sys * K + j0 + i;
-            live[i] = INIT || !ps->stop;
-            any_live = any_live || live[i];
-            pending[i] = !INIT && live[i] && ps->pending;
-            f1[i] = ps->f1;
-            f2[i] = ps->f2;
-            sv[i] = ps->sv;
-            c1[i] = INIT ? 0.0 : ps->beta * ps->sv;
-            su[i] = ps->su;  // S holds A^T u~ unnormalized
-        }
-        double acc[4][W] = {};
-        for (int64_t e = c.e0 * P + threadIdx.x; e < c.e1 * P; e += blockDim.x) {
-            double s[W], v[W], w[W], z[W], x[W], zero[W] = {};
-            if (any_live) {
-                ld_r<W>(S + e * W, s);
-                if (!INIT) {
-                    ld_r<W>(V + e * W, v);
-                    ld_r<W>(Wv + e * W, w);
-                    ld_r<W>(Z + e * W, z);
+        const LsqrState* ps = st + (int64_t)c.sys * K + j;
+        const bool live = INIT || !ps->stop;
+        const bool pending = !INIT && ps->pending;
+        const double f1 = ps->f1, f2 = ps->f2, sv = ps->sv;
+        const double c1 = INIT ? 0.0 : ps->beta * ps->sv;
+        const double su = ps->su;  // S holds A^T u~ unnormalized
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int64_t e = c.e0 * K + threadIdx.x; e < c.e1 * K; e += blockDim.x) {
+            const double sj = S[e];
+            S[e] = 0.0;
+            if (!live) continue;
+            const double pj = p[e / K];
+            double vn;
+            if (INIT) {
+                vn = pj * (su * sj);
+                Z[e] = 0.0;
+                Wv[e] = 0.0;
+            } else {
+                const double vj = V[e];
+                if (pending) {
+                    const double wj = Wv[e];
+                    const double zj = fma(f1, wj, Z[e]);
+                    const double wn = sv * vj - f2 * wj;
+                    Z[e] = zj;
+                    Wv[e] = wn;
+                    acc[1] = fma(zj, zj, acc[1]);
+                    acc[2] = fma(zj, wn, acc[2]);
+                    acc[3] = fma(wn, wn, acc[3]);
                 }
+                vn = pj * (su * sj) - c1 * vj;
             }
-            st_r<W>(S + e * W, zero);
-            if (!any_live) continue;
-            const int64_t col = e / P;
-            const double pj = p[col];
-#pragma unroll
-            for (int i = 0; i < W; ++i) {
-                double vn = pj * (su[i] * s[i]);
-                if (INIT) {
-                    z[i] = w[i] = 0.0;
-                } else {
-                    if (pending[i]) {
-                        z[i] = fma(f1[i], w[i], z[i]);
-                        w[i] = sv[i] * v[i] - f2[i] * w[i];
-                        acc[1][i] = fma(z[i], z[i], acc[1][i]);
-                        acc[2][i] = fma(z[i], w[i], acc[2][i]);
-                        acc[3][i] = fma(w[i], w[i], acc[3][i]);
-                    }
-                    vn = live[i] ? vn - c1[i] * v[i] : v[i];  // a stopped pair keeps its vectors
-                }
-                v[i] = vn;
-                x[i] = pj * vn;
-                if (live[i]) acc[0][i] = fma(vn, vn, acc[0][i]);
-            }
-            st_r<W>(V + e * W, v);
-            st_r<W>(Wv + e * W, w);
-            st_r<W>(Z + e * W, z);
-            st_r<W>(XT + (d.col0 + xt_col(d, col - d.col0)) * K + j0, x);
+            V[e] = vn;
+            XT[e] = pj * vn;
+            acc[0] = fma(vn, vn, acc[0]);
         }
-        seg_partials<K, W, 4>(acc, sh, part, ntile, sg);
+        seg_partials<K, 4>(acc, sh, part, ntile, sg);
     }
 }
 
@@ -928,33 +837,16 @@ static __global__ void k_brecip_sqrt(int64_t n, double* __restrict__ ss, double*
 }
 
 // ---------------------------------------------------------------------------------------
-// scalars: one block per (system, rhs) pair
+// scalars: one wave per (system, rhs) pair
 
-// Sums over a pair's `count` segments of NQ quantities; every thread gets them.  One wave per
-// quantity when there are four, all waves on the one otherwise.
-template <int K, int NQ>
-__device__ __forceinline__ void pair_sums(const double* __restrict__ part, int nseg, int first,
-                                          int count, int j, double (&out)[NQ]) {
-    constexpr int NW = 256 / kWave;
-    static_assert(NQ == 1 || NQ == NW, "quantities");
-    __shared__ double sh[NW];
-    const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const int q = NQ == 1 ? 0 : w;
-    const double* __restrict__ x = part + ((int64_t)q * nseg + first) * K + j;
+template <int K>
+__device__ __forceinline__ double pair_sum(const double* __restrict__ part, int q, int nseg,
+                                           int first, int count, int j) {
+    const int lane = threadIdx.x % kWave;
     double a = 0.0;
-#pragma unroll 4
-    for (int s = NQ == 1 ? (int)threadIdx.x : lane; s < count; s += NQ == 1 ? 256 : kWave)
-        a += x[(int64_t)s * K];
-    a = wave_sum(a);
-    if (lane == 0) sh[w] = a;
-    __syncthreads();
-    if (NQ == 1) {
-        out[0] = 0.0;
-        for (int k = 0; k < NW; ++k) out[0] += sh[k];
-    } else {
-#pragma unroll
-        for (int k = 0; k < NQ; ++k) out[k] = sh[k];
-    }
+    for (int s = first + lane; s < first + count; s += kWave)
+        a += part[((int64_t)q * nseg + s) * K + j];
+    return wave_sum(a);
 }
 
 enum { BS_INIT1 = 0, BS_INIT2 = 1, BS_BETA = 2, BS_ALPHA = 3 };
@@ -965,14 +857,19 @@ static __global__ __launch_bounds__(256) void k_bscal(LsqrState* __restrict__ st
                                                       const double* __restrict__ part, int nseg,
                                                       int32_t itnlim, int32_t fixed, double atol,
                                                       double btol, double conlim, int32_t k_used) {
-    const int pair = blockIdx.x, sidx = pair / K, j = pair % K;
+    const int pair = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
+    if (pair >= n_sys * K) return;
+    const int sidx = pair / K, j = pair % K;
     const SysDesc d = sys[sidx];
+    const bool by_rows = (STEP == BS_INIT1);
+    const bool by_bchunks = (STEP == BS_BETA);
+    const int first = by_bchunks ? d.bchunk0 : (by_rows ? d.chunk0 : d.tile0);
+    const int count = by_bchunks ? d.nbchunk : (by_rows ? d.nchunk : d.ntile);
     LsqrState* ps = st + pair;
     if (STEP == BS_INIT1) {
-        double ss[1];
-        pair_sums<K, 1>(part, nseg, d.chunk0, d.nchunk, j, ss);
-        if (threadIdx.x == 0) {
-            scal_init1(ps, ss[0], itnlim, fixed, atol, btol, conlim);
+        const double ss = pair_sum<K>(part, 0, nseg, first, count, j);
+        if (threadIdx.x % kWave == 0) {
+            scal_init1(ps, ss, itnlim, fixed, atol, btol, conlim);
             if (j >= k_used) {  // padding right-hand side: never iterates
                 ps->stop = 1;
                 ps->istop = 4;
@@ -982,17 +879,17 @@ static __global__ __launch_bounds__(256) void k_bscal(LsqrState* __restrict__ st
     }
     if (ps->stop) return;
     if (STEP == BS_INIT2) {
-        double ss[1];
-        pair_sums<K, 1>(part, nseg, d.tile0, d.ntile, j, ss);
-        if (threadIdx.x == 0) scal_init2(ps, ss[0]);
+        const double ss = pair_sum<K>(part, 0, nseg, first, count, j);
+        if (threadIdx.x % kWave == 0) scal_init2(ps, ss);
     } else if (STEP == BS_BETA) {
-        double ss[1];
-        pair_sums<K, 1>(part, nseg, d.round0, d.nround, j, ss);
-        if (threadIdx.x == 0) scal_beta(ps, ss[0]);
+        const double ss = pair_sum<K>(part, 0, nseg, first, count, j);
+        if (threadIdx.x % kWave == 0) scal_beta(ps, ss);
     } else {
-        double ss[4];
-        pair_sums<K, 4>(part, nseg, d.tile0, d.ntile, j, ss);
-        if (threadIdx.x == 0) scal_alpha(ps, ss[0], ss[1], ss[2], ss[3]);
+        const double vv = pair_sum<K>(part, 0, nseg, first, count, j);
+        const double zz = pair_sum<K>(part, 1, nseg, first, count, j);
+        const double zw = pair_sum<K>(part, 2, nseg, first, count, j);
+        const double ww = pair_sum<K>(part, 3, nseg, first, count, j);
+        if (threadIdx.x % kWave == 0) scal_alpha(ps, vv, zz, zw, ww);
     }
 }
 
@@ -1059,28 +956,18 @@ using namespace gsr;
 
 namespace {
 
-constexpr int kChunkRows = 256;  // rows per wave chunk
-constexpr int kStarBlock = 512;  // threads of the star-ordered aprod 2 blocks
-
 struct Tuning {
-    int threads = kBRowBlock;  // of a block of the row pass
-    int steps = 8;             // most wave steps per wave and round
-};
-
-// Launch shape of the row pass.
-struct BRowPlan {
-    int threads = 0, rows = 0, nsb = 0, grid = 0;
-    bool ldsi = true;
-    size_t lds = 0;
+    int chunk_rows = 256;  // rows per wave chunk
+    int star_block = 512;  // threads of the star-ordered aprod 2 blocks
 };
 
 std::mutex g_tune_mu;
 std::map<std::tuple<int, int64_t, int>, Tuning> g_tune_cache;
 
 template <typename T>
-gsr_status balloc(T** p, size_t count, size_t contiguous_from = kContiguous) {
+gsr_status balloc(T** p, size_t count) {
     if (count == 0) count = 1;
-    hipError_t e = device_alloc((void**)p, count * sizeof(T), contiguous_from);
+    hipError_t e = device_alloc((void**)p, count * sizeof(T));
     if (e != hipSuccess) {
         *p = nullptr;
         return fail(GSR_E_NOMEM, "hipMalloc of %zu bytes failed", count * sizeof(T));
@@ -1105,13 +992,12 @@ struct gsr_batch {
     const int32_t *star = nullptr, *att = nullptr, *instr = nullptr;
     SysDesc* d_sys = nullptr;
     // segment lists (device) and their counts
-    Seg *chunks = nullptr, *bchunks = nullptr, *tiles = nullptr, *rounds = nullptr,
-        *achunks = nullptr;
-    int nchunks = 0, nbchunks = 0, ntiles = 0, nrounds = 0, nachunks = 0;
-    BRowPlan row;
-    int64_t stars = 0;  // of all systems
-    // row tiles of the row pass, as in the single-system form
-    double* btiles = nullptr;
+    Seg *chunks = nullptr, *bchunks = nullptr, *tiles = nullptr;
+    int nchunks = 0, nbchunks = 0, ntiles = 0;
+    Tuning tune;
+    // row tiles (coefficients, indices) of the fused pass
+    double* bvt = nullptr;
+    int32_t* bit = nullptr;
     int64_t nbtiles = 0;
     // t-ordered attitude copy
     int32_t *rowT = nullptr, *tT = nullptr;
@@ -1134,100 +1020,52 @@ struct gsr_batch {
 
 namespace {
 
-// Shape of the row pass for the tuning `t`: rounds of at most t.steps wave steps per wave, as
-// many as the LDS holds beside the sums (one block of 1,024 threads or two of 512 per compute
-// unit share it).  Where the slots of one step do not fit beside the sums, as many as do (stars
-// past the last slot take atomics); 0 rows when the sums alone do not fit.  The instrumental unknowns are staged
-// where that leaves two steps or more (16 systems of 1.31e7 rows, 8 right-hand sides, 500 columns
-// each: 1.61 ms staged, 1.95 ms read from the operand; 64 systems of 1.76e6 rows, 2 right-hand
-// sides, 100 columns: 99 and 111 us) and read from the operand otherwise (above about 1,200
-// columns with 8 right-hand sides).
-BRowPlan plan_brow(const gsr_batch* b, const Tuning& t) {
-    BRowPlan r;
-    const int nw = t.threads / kWave;
-    const int64_t lds = 160 * 1024 / (kBRowBlock / t.threads) / 8 - 16;  // doubles per block
-    const double rows_per_star =
-        std::max(1.0, (double)b->M / (double)std::max<int64_t>(1, b->stars));
-    auto slots = [&](int64_t rows) {
-        return std::min<int64_t>(rows, (int64_t)(1.25 * rows / rows_per_star) + 8);
-    };
-    auto need = [&](int64_t steps, bool ldsi) {
-        const int64_t rows = steps * nw * kStepRows;
-        return brow_fixed(b->k, b->max_instr, ldsi) + (b->k <= 2 ? rows * b->k : 0) + slots(rows) * kAstro * b->k;
-    };
-    int steps = t.steps;
-    while (steps > 0 && need(steps, true) > lds) --steps;
-    r.ldsi = steps >= std::min(2, t.steps);
-    if (!r.ldsi) {
-        steps = t.steps;
-        while (steps > 0 && need(steps, false) > lds) --steps;
-    }
-    r.threads = t.threads;
-    r.rows = std::max(1, steps) * nw * kStepRows;
-    const int64_t base =
-        brow_fixed(b->k, b->max_instr, r.ldsi) + (b->k <= 2 ? (int64_t)r.rows * b->k : 0);
-    const int64_t fit = (lds - base) / (kAstro * b->k);
-    if (fit < 1) return BRowPlan();
-    r.nsb = (int)std::min(slots(r.rows), fit);
-    r.lds = sizeof(double) * (size_t)(base + (int64_t)r.nsb * kAstro * b->k);
-    return r;
-}
-
-// (Re)build the work lists for the row pass shape `r`; device copies replaced.
-gsr_status build_lists(gsr_batch* b, const BRowPlan& r, hipStream_t s) {
-    std::vector<Seg> ch, bch, tl, rd, ach;
-    // attitude chunks: two per wave at eight blocks per compute unit, whole blocks of 32 rows
-    // (longer ones are no faster: one chunk per wave 59 and 594 us for 1.76e6 and 1.31e7 rows,
-    // two 57 and 565)
-    const int64_t al =
-        std::min<int64_t>(2048, std::max<int64_t>(128, b->M / (64 * b->n_cu) / 32 * 32));
-    // column tiles: eight blocks per compute unit (64 systems of 3.3e5 columns in all: a vector
-    // step of 2,048-column tiles, 164 blocks, takes 16 us)
-    const int64_t cl = std::min<int64_t>(
-        kBTileMax, std::max<int64_t>(kBTileMin, b->N / (8 * b->n_cu) / 64 * 64));
+// (Re)build the row-chunk and block-chunk lists for the tuning `t`; device copies replaced.
+gsr_status build_lists(gsr_batch* b, const Tuning& t, hipStream_t s) {
+    std::vector<Seg> ch, bch, tl;
+    const int wpb = t.star_block / kWave;
     for (int i = 0; i < b->n_sys; ++i) {
         SysDesc& d = b->h_sys[i];
-        auto split = [&](std::vector<Seg>& v, int64_t at, int64_t n, int64_t len) {
-            const size_t first = v.size();
-            for (int64_t e = 0; e < n; e += len)
-                v.push_back({at + e, at + std::min<int64_t>(n, e + len), i, 0});
-            return std::make_pair((int)first, (int)(v.size() - first));
-        };
-        std::tie(d.chunk0, d.nchunk) = split(ch, d.row0, d.m, kChunkRows);
-        split(bch, d.row0, d.m, (int64_t)kChunkRows * (kStarBlock / kWave));
-        split(ach, d.row0, d.m, al);
-        std::tie(d.tile0, d.ntile) = split(tl, d.col0, d.n, cl);
-        // rounds of equal length, whole row tiles
-        const int64_t nt = (d.m + kStepRows - 1) / kStepRows, cap = r.rows / kStepRows;
-        const int64_t nr = std::max<int64_t>(1, (nt + cap - 1) / cap);
-        std::tie(d.round0, d.nround) = split(rd, d.row0, d.m, (nt + nr - 1) / nr * kStepRows);
+        d.chunk0 = (int)ch.size();
+        for (int64_t r = 0; r < d.m; r += t.chunk_rows)
+            ch.push_back({d.row0 + r, d.row0 + std::min<int64_t>(d.m, r + t.chunk_rows), i, 0});
+        d.nchunk = (int)ch.size() - d.chunk0;
+        const int64_t bl = (int64_t)t.chunk_rows * wpb;
+        d.bchunk0 = (int)bch.size();
+        for (int64_t r = 0; r < d.m; r += bl)
+            bch.push_back({d.row0 + r, d.row0 + std::min<int64_t>(d.m, r + bl), i, 0});
+        d.nbchunk = (int)bch.size() - d.bchunk0;
+        d.tile0 = (int)tl.size();
+        for (int64_t c = 0; c < d.n; c += kBTile)
+            tl.push_back({d.col0 + c, d.col0 + std::min<int64_t>(d.n, c + kBTile), i, 0});
+        d.ntile = (int)tl.size() - d.tile0;
     }
-    auto put = [&](Seg** p, int* n, const std::vector<Seg>& v) -> gsr_status {
-        bfree(*p);
-        *p = nullptr;
-        *n = (int)v.size();
-        GSR_TRY(balloc(p, v.size()));
-        HIP_TRY(hipMemcpyAsync(*p, v.data(), v.size() * sizeof(Seg), hipMemcpyHostToDevice, s));
-        return GSR_OK;
-    };
-    GSR_TRY(put(&b->chunks, &b->nchunks, ch));
-    GSR_TRY(put(&b->bchunks, &b->nbchunks, bch));
-    GSR_TRY(put(&b->tiles, &b->ntiles, tl));
-    GSR_TRY(put(&b->rounds, &b->nrounds, rd));
-    GSR_TRY(put(&b->achunks, &b->nachunks, ach));
+    bfree(b->chunks);
+    bfree(b->bchunks);
+    bfree(b->tiles);
+    b->chunks = b->bchunks = b->tiles = nullptr;
+    b->nchunks = (int)ch.size();
+    b->nbchunks = (int)bch.size();
+    b->ntiles = (int)tl.size();
+    GSR_TRY(balloc(&b->chunks, ch.size()));
+    GSR_TRY(balloc(&b->bchunks, bch.size()));
+    GSR_TRY(balloc(&b->tiles, tl.size()));
     if (!b->d_sys) GSR_TRY(balloc(&b->d_sys, b->n_sys));
+    HIP_TRY(hipMemcpyAsync(b->chunks, ch.data(), ch.size() * sizeof(Seg), hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemcpyAsync(b->bchunks, bch.data(), bch.size() * sizeof(Seg), hipMemcpyHostToDevice,
+                           s));
+    HIP_TRY(hipMemcpyAsync(b->tiles, tl.data(), tl.size() * sizeof(Seg), hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(b->d_sys, b->h_sys.data(), b->n_sys * sizeof(SysDesc),
                            hipMemcpyHostToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));
     // persistent grids
-    auto cap_grid = [&](int64_t items, int per_cu) {
-        return (int)std::max<int64_t>(1, std::min<int64_t>(items, (int64_t)b->n_cu * per_cu));
+    auto cap_grid = [&](int64_t items) {
+        return (int)std::max<int64_t>(1, std::min<int64_t>(items, (int64_t)b->n_cu * 8));
     };
-    b->G1 = cap_grid((b->nchunks + 3) / 4, 8);
-    b->G2t = cap_grid((b->nachunks + 3) / 4, 8);
-    b->G2s = cap_grid(b->nbchunks, 2);
-    b->row = r;
-    b->row.grid = cap_grid(b->nrounds, kBRowBlock / r.threads);
+    b->G1 = cap_grid((b->nchunks + 3) / 4);
+    b->G2t = cap_grid((b->nchunks + 3) / 4);
+    b->G2s = (int)std::max<int64_t>(1, std::min<int64_t>(b->nbchunks, (int64_t)b->n_cu * 2));
+    b->tune = t;
     return GSR_OK;
 }
 
@@ -1249,38 +1087,19 @@ void blaunch_aprod1(gsr_batch* b, const double* X, double* Y, const double* B, h
 }
 
 template <int MODE, int K>
-void blaunch_att(gsr_batch* b, const double* Y, double* X, hipStream_t s) {
-    hipLaunchKernelGGL((k_baprod2_att<MODE, K>), dim3(b->G2t), dim3(256), 0, s, b->d_sys,
-                       b->achunks, b->nachunks, b->attT, b->rowT, b->tT, Y, X, b->st);
-}
-
-// The row pass and the attitude columns of S.
-template <int MODE, int K>
-void blaunch_row(gsr_batch* b, hipStream_t s) {
-    const BRowPlan& r = b->row;
-    const BRowArgs a = {b->d_sys, b->rounds, b->nrounds, b->btiles, b->star,      b->XT,  b->U,
-                        b->S,     b->st,     b->part,    b->max_instr, r.rows, r.nsb};
-    auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(r.grid), dim3(r.threads), r.lds, s, a);
-    };
-    if (r.ldsi)
-        go(k_browpass<K, MODE, true>);
-    else
-        go(k_browpass<K, MODE, false>);
-    blaunch_att<MODE == BR_SQ ? A2_SQ : A2_LSQR, K>(b, b->U, b->S, s);
-}
-
-template <int K>
 void blaunch_aprod2(gsr_batch* b, const double* Y, double* X, hipStream_t s) {
     const size_t lds = sizeof(double) * (size_t)(b->max_instr + 1) * K;
-    hipLaunchKernelGGL((k_baprod2_star<K>), dim3(b->G2s), dim3(kStarBlock), lds, s, b->d_sys,
-                       b->bchunks, b->nbchunks, b->vals, b->star, b->instr, Y, X, b->max_instr);
-    blaunch_att<A2_ADD, K>(b, Y, X, s);
+    hipLaunchKernelGGL((k_baprod2_star<double, MODE, K>), dim3(b->G2s), dim3(b->tune.star_block),
+                       lds, s, b->d_sys, b->bchunks, b->nbchunks, b->vals, b->star, b->instr, Y,
+                       X, b->st, b->max_instr);
+    hipLaunchKernelGGL((k_baprod2_att<double, MODE, K>), dim3(b->G2t), dim3(256), 0, s, b->d_sys,
+                       b->chunks, b->nchunks, b->attT, b->rowT, b->tT, Y, X, b->st);
 }
 
 template <int K>
 void bscal(gsr_batch* b, int step, int nseg, const gsr_solve_opts& o, hipStream_t s) {
-    const dim3 grid(b->n_sys * K), block(256);
+    const int pairs = b->n_sys * K;
+    const dim3 grid((pairs + 3) / 4), block(256);
     switch (step) {
         case BS_INIT1:
             hipLaunchKernelGGL((k_bscal<BS_INIT1, K>), grid, block, 0, s, b->st, b->d_sys,
@@ -1304,11 +1123,17 @@ void bscal(gsr_batch* b, int step, int nseg, const gsr_solve_opts& o, hipStream_
 template <int K>
 void b_iteration(gsr_batch* b, hipStream_t s) {
     const dim3 tgrid((unsigned)std::min(b->ntiles, b->n_cu * 8));
-    // one read of every row: U = sv A XT - alpha su U and S = A^T U
-    blaunch_row<BR_LSQR, K>(b, s);
-    bscal<K>(b, BS_BETA, b->nrounds, gsr_solve_opts{}, s);
+    // one read of every row: U = sv A XT - alpha su U and S = A^T U (star-ordered part)
+    const size_t lds = sizeof(double) * ((size_t)(2 * b->max_instr + 1) * K + K);
+    hipLaunchKernelGGL((k_baprod12<double, K>), dim3(b->G2s), dim3(b->tune.star_block), lds, s,
+                       b->d_sys, b->bchunks, b->nbchunks, b->bvt, b->bit, b->star, b->XT, b->U,
+                       b->S, b->st, b->part, b->max_instr);
+    hipLaunchKernelGGL((k_baprod2_att<double, A2_LSQR, K>), dim3(b->G2t), dim3(256), 0, s,
+                       b->d_sys, b->chunks, b->nchunks, b->attT, b->rowT, b->tT, b->U, b->S,
+                       b->st);
+    bscal<K>(b, BS_BETA, b->nbchunks, gsr_solve_opts{}, s);
     hipLaunchKernelGGL((k_bvec_v<false, K>), tgrid, dim3(256), 0, s, b->tiles, b->ntiles, b->S,
-                       b->p, b->V, b->W, b->Z, b->XT, b->d_sys, b->st, b->part);
+                       b->p, b->V, b->W, b->Z, b->XT, b->st, b->part);
     bscal<K>(b, BS_ALPHA, b->ntiles, gsr_solve_opts{}, s);
 }
 
@@ -1322,9 +1147,9 @@ void b_solve_body(gsr_batch* b, const double* B, double* X, const gsr_solve_opts
     bscal<K>(b, BS_INIT1, b->nchunks, o, s);
     hipLaunchKernelGGL(k_fill, dim3(grid_for(b->N * K, 256, 2048)), dim3(256), 0, s, b->S,
                        b->N * K, 0.0);
-    blaunch_row<BR_T, K>(b, s);
+    blaunch_aprod2<A2_LSQR, K>(b, b->U, b->S, s);
     hipLaunchKernelGGL((k_bvec_v<true, K>), tgrid, dim3(256), 0, s, b->tiles, b->ntiles, b->S,
-                       b->p, b->V, b->W, b->Z, b->XT, b->d_sys, b->st, b->part);
+                       b->p, b->V, b->W, b->Z, b->XT, b->st, b->part);
     bscal<K>(b, BS_INIT2, b->ntiles, o, s);
     for (int it = 0; it < iters; ++it) b_iteration<K>(b, s);
     if (X)
@@ -1332,40 +1157,38 @@ void b_solve_body(gsr_batch* b, const double* B, double* X, const gsr_solve_opts
                            b->W, b->V, X, b->st);
 }
 
-// Time the row pass for each candidate tuning; keep the fastest.  Synchronizes.
+// Time the two products for each candidate tuning; keep the fastest.  Synchronizes.
 gsr_status autotune(gsr_batch* b, hipStream_t s) {
     const auto key = std::make_tuple(b->n_sys, b->M, b->k);
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tune_cache.find(key);
-        if (it != g_tune_cache.end()) {
-            const BRowPlan r = plan_brow(b, it->second);
-            if (r.rows > 0) return build_lists(b, r, s);
-        }
+        if (it != g_tune_cache.end()) return build_lists(b, it->second, s);
     }
-    const Tuning cands[] = {{1024, 48}, {1024, 16}, {1024, 6}, {1024, 2}, {512, 16}, {512, 6}};
-    Tuning best;
+    const Tuning cands[] = {{128, 512}, {256, 512}, {512, 512}, {256, 256}, {1024, 512}};
+    Tuning best = cands[1];
     float best_ms = 1e30f;
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0));
     HIP_TRY(hipEventCreate(&e1));
-    int last_rows = 0, last_threads = 0;
     for (const Tuning& t : cands) {
-        const BRowPlan r = plan_brow(b, t);
-        if (r.rows == 0 || (r.rows == last_rows && r.threads == last_threads)) continue;
-        last_rows = r.rows;
-        last_threads = r.threads;
-        GSR_TRY(build_lists(b, r, s));
+        GSR_TRY(build_lists(b, t, s));
         float ms = 0.f;
         with_k(b->k, [&](auto kc) {
             constexpr int K = decltype(kc)::value;
-            // on scratch contents (every pair's state is still zero here, so the values are
-            // zeros); the partial sums need room for this candidate's rounds
+            // the two product passes of one iteration, on scratch contents (every pair's
+            // state is still zero here, so the values are zeros)
             HIP_TRY_VOID(hipMemsetAsync(b->XT, 0, sizeof(double) * b->N * K, s));
             HIP_TRY_VOID(hipMemsetAsync(b->U, 0, sizeof(double) * b->M * K, s));
+            const size_t lds = sizeof(double) * ((size_t)(2 * b->max_instr + 1) * K + K);
             for (int rep = 0; rep < 3; ++rep) {
                 if (rep == 1) (void)hipEventRecord(e0, s);
-                blaunch_row<BR_LSQR, K>(b, s);
+                hipLaunchKernelGGL((k_baprod12<double, K>), dim3(b->G2s), dim3(t.star_block), lds,
+                                   s, b->d_sys, b->bchunks, b->nbchunks, b->bvt, b->bit,
+                                   b->star, b->XT, b->U, b->S, b->st, b->part, b->max_instr);
+                hipLaunchKernelGGL((k_baprod2_att<double, A2_LSQR, K>), dim3(b->G2t), dim3(256),
+                                   0, s, b->d_sys, b->chunks, b->nchunks, b->attT, b->rowT,
+                                   b->tT, b->U, b->S, b->st);
             }
             (void)hipEventRecord(e1, s);
             (void)hipEventSynchronize(e1);
@@ -1383,17 +1206,20 @@ gsr_status autotune(gsr_batch* b, hipStream_t s) {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         g_tune_cache[key] = best;
     }
-    return build_lists(b, plan_brow(b, best), s);
+    return build_lists(b, best, s);
 }
 
 gsr_status b_colnorm(gsr_batch* b, hipStream_t s, unsigned long long* n_empty) {
-    // column sums of squares (stride-1 vectors)
+    // column sums of squares with K = 1 lists (stride-1 vectors)
+    const int k_saved = b->k;
     double* ss = b->S;  // N x k >= N doubles
     unsigned long long* d_cnt = nullptr;
     GSR_TRY(balloc(&d_cnt, 1));
     HIP_TRY(hipMemsetAsync(d_cnt, 0, sizeof(*d_cnt), s));
     HIP_TRY(hipMemsetAsync(ss, 0, sizeof(double) * b->N, s));
-    blaunch_row<BR_SQ, 1>(b, s);
+    b->k = 1;
+    blaunch_aprod2<A2_SQ, 1>(b, nullptr, ss, s);
+    b->k = k_saved;
     hipLaunchKernelGGL(k_brecip_sqrt, dim3(grid_for(b->N, 256, 2048)), dim3(256), 0, s, b->N, ss,
                        b->p, d_cnt);
     HIP_TRY(hipMemsetAsync(ss, 0, sizeof(double) * b->N * b->k, s));
@@ -1470,7 +1296,6 @@ gsr_status gsr_batch_setup(int32_t n_sys, const gsr_dims* dims, const int64_t* r
         d.n_stars = dims[i].n_stars;
         d.T = g.T;
         d.I = g.I;
-        b->stars += d.n_stars;
         d.btile0 = b->nbtiles;
         b->nbtiles += (d.m + kStepRows - 1) / kStepRows;
         b->col_off[i] = col;
@@ -1480,28 +1305,26 @@ gsr_status gsr_batch_setup(int32_t n_sys, const gsr_dims* dims, const int64_t* r
     b->col_off[n_sys] = col;
     b->N = col;
     gsr_status st;
-    if ((st = build_lists(b, plan_brow(b, Tuning()), s)) != GSR_OK) return bail(st);
+    if ((st = build_lists(b, Tuning(), s)) != GSR_OK) return bail(st);
     const size_t NK = (size_t)b->N * k, MK = (size_t)M * k;
     if ((st = balloc(&b->p, b->N)) != GSR_OK) return bail(st);
     if ((st = balloc(&b->S, NK)) != GSR_OK) return bail(st);
     if ((st = balloc(&b->V, NK)) != GSR_OK) return bail(st);
     if ((st = balloc(&b->W, NK)) != GSR_OK) return bail(st);
     if ((st = balloc(&b->Z, NK)) != GSR_OK) return bail(st);
-    if ((st = balloc(&b->XT, NK, kGathered)) != GSR_OK) return bail(st);
-    if ((st = balloc(&b->U, MK, kGathered)) != GSR_OK) return bail(st);
+    if ((st = balloc(&b->XT, NK)) != GSR_OK) return bail(st);
+    if ((st = balloc(&b->U, MK)) != GSR_OK) return bail(st);
     if ((st = balloc(&b->st, (size_t)n_sys * k)) != GSR_OK) return bail(st);
-    if ((st = balloc(&b->btiles, (size_t)b->nbtiles * tile_elems<double>())) != GSR_OK)
-        return bail(st);
+    if ((st = balloc(&b->bvt, (size_t)b->nbtiles * kBTileVals)) != GSR_OK) return bail(st);
+    if ((st = balloc(&b->bit, (size_t)b->nbtiles * kBTileIdx)) != GSR_OK) return bail(st);
     for (int i = 0; i < n_sys; ++i) {
         const SysDesc& d = b->h_sys[i];
         const int64_t nt = (d.m + kStepRows - 1) / kStepRows;
         if (nt == 0) continue;
-        double* tiles = b->btiles + d.btile0 * tile_elems<double>();
-        hipLaunchKernelGGL(k_make_tiles<double>, dim3(grid_for(nt * kTileVals, 256, 4096)),
-                           dim3(256), 0, s, d.m, nt, vals + d.row0 * kPar, tiles);
-        hipLaunchKernelGGL(k_make_itiles<double>, dim3(grid_for(nt * kTileIdx, 256, 4096)),
-                           dim3(256), 0, s, d.m, nt, star + d.row0, att + d.row0,
-                           instr + d.row0 * kInstr, tiles);
+        hipLaunchKernelGGL(k_make_btiles, dim3(grid_for(nt * kBTileVals, 256, 4096)), dim3(256), 0,
+                           s, d.m, nt, vals + d.row0 * kPar, star + d.row0, att + d.row0,
+                           instr + d.row0 * kInstr, b->bvt + d.btile0 * kBTileVals,
+                           b->bit + d.btile0 * kBTileIdx);
     }
     b->st_host.resize((size_t)n_sys * k);
     {
@@ -1533,7 +1356,7 @@ gsr_status gsr_batch_setup(int32_t n_sys, const gsr_dims* dims, const int64_t* r
     // attitude coefficients in (system, t) order
     if ((st = balloc(&b->rowT, M)) != GSR_OK) return bail(st);
     if ((st = balloc(&b->tT, M)) != GSR_OK) return bail(st);
-    if ((st = balloc(&b->attT, (size_t)b->nbtiles * kStepRows * kAttRow)) != GSR_OK) return bail(st);
+    if ((st = balloc(&b->attT, (size_t)b->nbtiles * kBTileAtt)) != GSR_OK) return bail(st);
     if (M > 0) {
         int tbits = 1;
         while (tbits < 31 && (1LL << tbits) <= max_T) ++tbits;
@@ -1561,10 +1384,11 @@ gsr_status gsr_batch_setup(int32_t n_sys, const gsr_dims* dims, const int64_t* r
                                keys_out, tbits, b->tT);
             for (int i = 0; i < n_sys; ++i) {
                 const SysDesc& d = b->h_sys[i];
-                if (d.m == 0) continue;
-                hipLaunchKernelGGL(k_make_batt_rows, dim3(grid_for(d.m * kAttRow, 256, 4096)),
-                                   dim3(256), 0, s, d.m, d.row0, vals, b->rowT,
-                                   b->attT + d.btile0 * kStepRows * kAttRow);
+                const int64_t nt = (d.m + kStepRows - 1) / kStepRows;
+                if (nt == 0) continue;
+                hipLaunchKernelGGL(k_make_batt_tiles, dim3(grid_for(nt * kBTileAtt, 256, 4096)),
+                                   dim3(256), 0, s, d.m, nt, d.row0, vals, b->rowT,
+                                   b->attT + d.btile0 * kBTileAtt);
             }
             e = hipStreamSynchronize(s);
         }
@@ -1574,16 +1398,21 @@ gsr_status gsr_batch_setup(int32_t n_sys, const gsr_dims* dims, const int64_t* r
         bfree(temp);
         if (e != hipSuccess) return bail(hip_fail(e, "batched attitude ordering"));
     }
-    // partial sums: 4 quantities per (column tile, rhs), one per (row chunk or round, rhs); at
-    // most one round per 8 row tiles of a system, and one more
-    b->part_len = (size_t)k * std::max({(size_t)4 * b->ntiles, (size_t)b->nchunks,
-                                        (size_t)(b->nbtiles / 8 + n_sys), (size_t)1});
+    // partial-sum buffer: 4 quantities per (segment, rhs)
+    b->part_len = (size_t)4 * std::max(std::max(b->nchunks, b->ntiles), 1) * k * 4;
     if ((st = balloc(&b->part, b->part_len)) != GSR_OK) return bail(st);
     unsigned long long n_empty = 0;
     if ((st = b_colnorm(b, s, &n_empty)) != GSR_OK) return bail(st);
     if (n_empty && !so.allow_empty_cols)
         return bail(fail(GSR_E_LAYOUT, "%llu all-zero column(s); set allow_empty_cols", n_empty));
     if ((st = autotune(b, s)) != GSR_OK) return bail(st);
+    // the tuned lists may have more segments than the default ones
+    const size_t need = (size_t)4 * std::max(std::max(b->nchunks, b->ntiles), 1) * k;
+    if (need > b->part_len) {
+        bfree(b->part);
+        b->part_len = need;
+        if ((st = balloc(&b->part, b->part_len)) != GSR_OK) return bail(st);
+    }
     *out = b;
     return GSR_OK;
 }
@@ -1596,8 +1425,7 @@ gsr_status gsr_batch_destroy(gsr_batch* b) {
     for (void* p : {(void*)b->d_sys, (void*)b->chunks, (void*)b->bchunks, (void*)b->tiles,
                     (void*)b->rowT, (void*)b->tT, (void*)b->attT, (void*)b->p, (void*)b->st,
                     (void*)b->U, (void*)b->V, (void*)b->W, (void*)b->Z, (void*)b->XT,
-                    (void*)b->S, (void*)b->part, (void*)b->btiles, (void*)b->rounds,
-                    (void*)b->achunks})
+                    (void*)b->S, (void*)b->part, (void*)b->bvt, (void*)b->bit})
         bfree(p);
     if (b->cap) (void)hipStreamDestroy(b->cap);
     delete b;
@@ -1625,7 +1453,7 @@ gsr_status gsr_batch_aprod2(gsr_batch* b, const double* Y, double* X, void* stre
     if (((uintptr_t)X | (uintptr_t)Y) & 15) return fail(GSR_E_INVAL, "X and Y must be 16-byte aligned");
     HIP_TRY(hipSetDevice(b->device));
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    with_k(b->k, [&](auto kc) { blaunch_aprod2<decltype(kc)::value>(b, Y, X, s); });
+    with_k(b->k, [&](auto kc) { blaunch_aprod2<A2_ADD, decltype(kc)::value>(b, Y, X, s); });
     HIP_TRY(hipGetLastError());
     return GSR_OK;
 }

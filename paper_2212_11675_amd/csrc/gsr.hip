@@ -222,6 +222,13 @@ void dfree(void* p) {
     if (p) (void)hipFree(p);
 }
 
+// Vectors of n doubles each, in one allocation.  The vectors that the row pass and the attitude
+// pass gather from and scatter to (u~, s, xt) are asked for as contiguous memory from 16 MiB
+// on: those passes' times depend on how the pages lie (2e7 rows: 0.98 -> 0.93 ms and 0.51 ->
+// 0.49 ms).  Not v, w, z, which the vector step streams side by side with s, xt and p: all of
+// them contiguous, it took 114 us instead of 72.
+constexpr size_t kGathered = size_t(16) << 20;
+
 gsr_status dalloc_vecs(void** slab, std::initializer_list<double**> vecs, int64_t n,
                        size_t contiguous_from) {
     const size_t step = ((size_t)std::max<int64_t>(n, 1) * sizeof(double) + 255) / 256 * 256;

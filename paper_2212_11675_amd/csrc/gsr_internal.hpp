@@ -25,11 +25,5 @@ int grid_for(int64_t items, int per_block, int max_blocks);
 // Device memory for the library's arrays (hipMalloc semantics; free with hipFree).
 constexpr size_t kContiguous = size_t(1) << 30;
 hipError_t device_alloc(void** p, size_t bytes, size_t contiguous_from = kContiguous);
-// Vectors of n doubles each, in one allocation.  The vectors that the row pass and the attitude
-// pass gather from and scatter to (u~, s, xt) are asked for as contiguous memory from 16 MiB
-// on: those passes' times depend on how the pages lie (2e7 rows: 0.98 -> 0.93 ms and 0.51 ->
-// 0.49 ms).  Not v, w, z, which the vector step streams side by side with s, xt and p: all of
-// them contiguous, it took 114 us instead of 72.
-constexpr size_t kGathered = size_t(16) << 20;
 
 }  // namespace gsr

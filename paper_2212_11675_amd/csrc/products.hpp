@@ -100,9 +100,9 @@ __device__ __forceinline__ void ld_tile_idx(const VT* __restrict__ tiles, int64_
     const int32_t* itile =
         reinterpret_cast<const int32_t*>(tiles + tile * tile_elems<VT>() + kTileVals);
     const i32x2 v = __builtin_nontemporal_load(reinterpret_cast<const i32x2*>(itile) + lane);
-    r.star = __builtin_amdgcn_mov_dpp(v.x, 0x00, 0xF, 0xF, true);  // quad_perm [0,0,0,0]
-    r.att = __builtin_amdgcn_mov_dpp(v.y, 0x00, 0xF, 0xF, true);
-    const int32_t i3 = __builtin_amdgcn_mov_dpp(v.y, 0xFF, 0xF, 0xF, true);  // [3,3,3,3]
+    r.star = __builtin_amdgcn_update_dpp(0, v.x, 0x00, 0xF, 0xF, false);  // quad_perm [0,0,0,0]
+    r.att = __builtin_amdgcn_update_dpp(0, v.y, 0x00, 0xF, 0xF, false);
+    const int32_t i3 = __builtin_amdgcn_update_dpp(0, v.y, 0xFF, 0xF, 0xF, false);  // [3,3,3,3]
     r.ia = ((lane & 3) == 0) ? i3 : v.x;
     r.ib = v.y;
 }
@@ -183,8 +183,8 @@ __device__ __forceinline__ void ld_att_tile(const float* __restrict__ t, int64_t
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
     const int lo = __double2loint(v), hi = __double2hiint(v);
-    const int lo2 = __builtin_amdgcn_mov_dpp(lo, CTRL, 0xF, 0xF, true);
-    const int hi2 = __builtin_amdgcn_mov_dpp(hi, CTRL, 0xF, 0xF, true);
+    const int lo2 = __builtin_amdgcn_update_dpp(0, lo, CTRL, 0xF, 0xF, false);
+    const int hi2 = __builtin_amdgcn_update_dpp(0, hi, CTRL, 0xF, 0xF, false);
     return __hiloint2double(hi2, lo2);
 }
 
