@@ -163,10 +163,8 @@ struct gsr_handle {
     double* part_ig = nullptr;  // [blocks][n_instr + 1] block sums of the star-ordered pass
     double *partA = nullptr, *partB = nullptr;
     LsqrState* st = nullptr;   // device scalars
-    LsqrState* st2 = nullptr;  // the same after the step a row pass or vector step begins with
     LsqrState* st_host = nullptr;  // pinned mirror
-    int Gv = 1;          // blocks of the vector steps
-    int Gn = 1, Gm = 1;  // blocks of the small kernels over n and m
+    int Gn = 1, Gm = 1;
     // launch shapes: aprod 1 and star-ordered aprod 2 by themselves, the fused row pass (used
     // when its instrumental columns fit in LDS)
     RowPlan dot, star_pass, row12;
@@ -202,8 +200,7 @@ struct gsr_handle {
 
 namespace {
 
-constexpr int kVecBlocksMax = 2048;  // of the small kernels
-constexpr int kVecBlocks = 1024;     // of the solver's vector steps (four per compute unit)
+constexpr int kVecBlocksMax = 2048;
 constexpr int kGraphIters = 16;  // even: u~ is back in its first array after a graph
 
 template <typename T>
@@ -285,7 +282,7 @@ void deal_rounds(const Geo& g, int n_cu, int64_t cap, RowPlan* r) {
 // tw = 0 when not even one wave step fits.
 RowPlan plan_rows(const Geo& g, int n_cu, int64_t fixed, bool with_u, bool with_stars) {
     RowPlan r;
-    const int64_t budget = (160 * 1024 - 1024) / 8 - fixed;  // doubles; 1 KiB static
+    const int64_t budget = (160 * 1024 - 256) / 8 - fixed;  // doubles
     const double rows_per_star = std::max(1.0, (double)g.m / (double)g.n_stars);
     auto slots = [&](int64_t tw) {
         const int64_t rows = with_stars ? tw * kRoundRows : 0;
@@ -354,26 +351,26 @@ const float* tiles_of<float>(const gsr_handle* h) { return h->tiles32; }
 // Constraint rows.  y_c (op)= C x with the operation of k_con_fin (LSQR modes write their
 // partial sums to part[0] (and part[stride], ... with PENDING)).
 template <int MODE, bool TRANS = false, bool PENDING = false>
-void launch_con_a1(const gsr_handle* h, const LsqrState* st, const double* x, const double* yin,
-                   double* yc, const double* bc, double* part, int stride, double* wc, double* zc,
+void launch_con_a1(const gsr_handle* h, const double* x, const double* yin, double* yc,
+                   const double* bc, double* part, int stride, double* wc, double* zc,
                    hipStream_t s, const int32_t* gate = nullptr) {
     if (!h->n_con) return;
     if (h->nnz_c > 0)
         hipLaunchKernelGGL(k_con_dot, dim3(h->Gcon), dim3(kConBlock), 0, s, h->nnz_c,
-                           h->con_per_block, h->crow, h->ccol, h->cval, x, h->cacc, st,
+                           h->con_per_block, h->crow, h->ccol, h->cval, x, h->cacc, h->st,
                            (int)(MODE == CON_LSQR), gate);
     hipLaunchKernelGGL((k_con_fin<MODE, TRANS, PENDING>), dim3(1), dim3(kConBlock), 0, s,
-                       h->n_con, h->cacc, yin, yc, bc, st, part, stride, wc, zc, gate);
+                       h->n_con, h->cacc, yin, yc, bc, h->st, part, stride, wc, zc, gate);
 }
 
 // x += C^T y_c (SQ: the squared coefficients, for the column norms; y_c unused)
 template <bool SQ>
-void launch_con_a2(const gsr_handle* h, const LsqrState* st, const double* yc, double* x,
-                   int check_stop, hipStream_t s) {
+void launch_con_a2(const gsr_handle* h, const double* yc, double* x, int check_stop,
+                   hipStream_t s) {
     if (!h->n_con || !h->ncu) return;
     hipLaunchKernelGGL((k_con_a2<SQ>), dim3(grid_for(h->ncu, kConBlock, kVecBlocksMax)),
                        dim3(kConBlock), 0, s, h->ncu, h->cu_col, h->cu_ptr, h->cu_row, h->cu_val,
-                       yc, x, st, check_stop);
+                       yc, x, h->st, check_stop);
 }
 
 AttCopy att_copy(const gsr_handle* h) { return {h->xa, h->g.att0, h->g.T}; }
@@ -386,14 +383,14 @@ AttCopy att_copy(const gsr_handle* h) { return {h->xa, h->g.att0, h->g.T}; }
 constexpr int64_t kAttCopyRows = 250000;
 
 template <typename VT, int MODE>
-void launch_aprod1(const gsr_handle* h, const StepArgs& step, const double* xx, double* y,
-                   const double* b, hipStream_t s, const int32_t* gate = nullptr) {
+void launch_aprod1(const gsr_handle* h, const double* xx, double* y, const double* b,
+                   hipStream_t s, const int32_t* gate = nullptr) {
     constexpr bool kLsqr = (MODE == A1_LSQR || MODE == A1_LSQR_T);
     const RowPlan& rp = h->dot;
     const int64_t m = h->g.m;
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3(rp.grid), dim3(kRowBlock), rp.lds, s, h->g, tiles_of<VT>(h),
-                           h->star, xx, h->xa, y, b, step, h->partA, rp.tw, gate);
+                           h->star, xx, h->xa, y, b, h->st, h->partA, rp.tw, gate);
     };
     if (kLsqr || m >= kAttCopyRows) {
         if (!kLsqr)
@@ -409,56 +406,56 @@ void launch_aprod1(const gsr_handle* h, const StepArgs& step, const double* xx, 
         go(k_aprod1<VT, MODE, false, false>);
     }
     if (MODE == A1_ADD)
-        launch_con_a1<CON_ADD>(h, h->st, xx, y + m, y + m, nullptr, nullptr, 0, nullptr, nullptr, s);
+        launch_con_a1<CON_ADD>(h, xx, y + m, y + m, nullptr, nullptr, 0, nullptr, nullptr, s);
     else if (MODE == A1_RESID)
-        launch_con_a1<CON_RESID>(h, h->st, xx, y + m, y + m, b + m, nullptr, 0, nullptr, nullptr,
-                                 s, gate);
+        launch_con_a1<CON_RESID>(h, xx, y + m, y + m, b + m, nullptr, 0, nullptr, nullptr, s,
+                                 gate);
     else  // the u-step's (or transposed v-step's) sum of squares continues in slot rp.grid
-        launch_con_a1<CON_LSQR, MODE == A1_LSQR_T>(h, step.out ? step.out : step.in, xx, y + m,
-                                                   y + m, nullptr, h->partA + rp.grid, 0, nullptr,
-                                                   nullptr, s);
+        launch_con_a1<CON_LSQR, MODE == A1_LSQR_T>(h, xx, y + m, y + m, nullptr,
+                                                   h->partA + rp.grid, 0, nullptr, nullptr, s);
 }
 
-// The attitude pass over the library's copy (its sums in groups, h->att_part), and beside it
-// x[ins0 .. glb0] += the instrumental/global sums of nblocks blocks in part_ig (0: none).  Then,
-// outside the solver (whose vector step reads the groups itself), x += the attitude sums.
+// x[ins0 .. glb0] += the blocks' instrumental/global sums in part_ig
+void launch_reduce(const gsr_handle* h, int nblocks, double* x, int check_stop, hipStream_t s) {
+    const int ncols = h->g.I + 1;
+    const int slices = std::max(1, std::min(32, nblocks / 8));
+    hipLaunchKernelGGL(k_reduce_partials, dim3((ncols + 255) / 256, slices), dim3(256), 0, s,
+                       ncols, nblocks, h->part_ig, x + h->g.ins0, h->st, check_stop);
+}
+
+// x += A^T y over the attitude columns: the attitude pass over the library's copy, then the
+// sums of its groups added to x.
 template <typename VT, int MODE>
-void launch_att(const gsr_handle* h, const LsqrState* st, const VT* attT, const double* y,
-                double* x, int nblocks, hipStream_t s) {
+void launch_att(const gsr_handle* h, const VT* attT, const double* y, double* x, hipStream_t s) {
     const Geo& g = h->g;
-    ReduceArgs red = {0, 0, 0, nullptr, nullptr};
-    int nred = 0;
-    if (nblocks > 0) {
-        red = {g.I + 1, nblocks, std::max(1, std::min(32, nblocks / 8)), h->part_ig, x + g.ins0};
-        nred = (red.ncols + kBlockAtt - 1) / kBlockAtt * red.slices;
-    }
-    hipLaunchKernelGGL((k_aprod2_att<VT, MODE>), dim3(h->att_ng + nred), dim3(kBlockAtt),
+    if (g.m == 0) return;
+    hipLaunchKernelGGL((k_aprod2_att<VT, MODE>), dim3(h->att_ng), dim3(kBlockAtt),
                        sizeof(double) * kAxes * h->att_lw, s, g, attT, h->rowT, h->tT,
-                       h->att_seg, h->att_ng, h->att_lw, y, h->att_part, st, red);
-    if (MODE == A2_ADD || MODE == A2_SQ)
-        hipLaunchKernelGGL(k_att_reduce,
-                           dim3(grid_for((int64_t)kAxes * g.T, kBlock, kVecBlocksMax)),
-                           dim3(kBlock), 0, s, g, AttSum{h->att_part, h->att_w, h->att_lw}, x);
+                       h->att_seg, h->att_lw, y, h->att_part, h->st);
+    const int64_t n = (int64_t)kAxes * g.T;
+    hipLaunchKernelGGL(k_att_reduce, dim3(grid_for(n, kBlock, kVecBlocksMax)), dim3(kBlock), 0,
+                       s, g, h->att_w, h->att_lw, h->att_part, x, h->st,
+                       (int)(MODE == A2_LSQR || MODE == A2_LSQR_T));
 }
 
-// x += A^T y: star-ordered pass (astrometric, instrumental, global), then the attitude pass with
-// the reduction of the instrumental/global block sums.  LSQR modes: skipped once st->stop is set,
-// the attitude columns stay in h->att_part.
+// x += A^T y: star-ordered pass (astrometric, instrumental, global), reduction of the
+// instrumental/global block sums, attitude pass over the library's copy.
 template <typename VT, int MODE>
-void launch_aprod2(const gsr_handle* h, const LsqrState* st, const VT* attT, const double* y,
-                   double* x, hipStream_t s) {
+void launch_aprod2(const gsr_handle* h, const VT* attT, const double* y, double* x,
+                   hipStream_t s) {
     const Geo& g = h->g;
     const RowPlan& rp = h->star_pass;
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3(rp.grid), dim3(kRowBlock), rp.lds, s, g, tiles_of<VT>(h),
-                           h->star, y, x, st, h->part_ig, rp.tw, rp.nsb);
+                           h->star, y, x, h->st, h->part_ig, rp.tw, rp.nsb);
     };
     if (rp.ldsi)
         go(k_aprod2_star<VT, MODE, true>);
     else
         go(k_aprod2_star<VT, MODE, false>);
-    launch_att<VT, MODE>(h, st, attT, y, x, rp.ldsi ? rp.grid : 0, s);
-    launch_con_a2<MODE == A2_SQ>(h, st, MODE == A2_SQ ? nullptr : y + g.m, x,
+    if (rp.ldsi) launch_reduce(h, rp.grid, x, (int)(MODE == A2_LSQR || MODE == A2_LSQR_T), s);
+    launch_att<VT, MODE>(h, attT, y, x, s);
+    launch_con_a2<MODE == A2_SQ>(h, MODE == A2_SQ ? nullptr : y + g.m, x,
                                  (int)(MODE == A2_LSQR || MODE == A2_LSQR_T), s);
 }
 
@@ -470,7 +467,7 @@ gsr_status colnorm(gsr_handle* h, const VT* attT, double* p, hipStream_t s,
     GSR_TRY(dalloc(&d_cnt, 1));
     HIP_TRY(hipMemsetAsync(d_cnt, 0, sizeof(*d_cnt), s));
     fill(h->s, h->g.n, 0.0, s);
-    launch_aprod2<VT, A2_SQ>(h, h->st, attT, nullptr, h->s, s);
+    launch_aprod2<VT, A2_SQ>(h, attT, nullptr, h->s, s);
     hipLaunchKernelGGL(k_recip_sqrt, dim3(grid_for(h->g.n, kBlock, kVecBlocksMax)), dim3(kBlock),
                        0, s, h->g.n, h->s, p, d_cnt);
     hipError_t e = hipMemcpyAsync(n_empty, d_cnt, sizeof(*d_cnt), hipMemcpyDeviceToHost, s);
@@ -518,12 +515,7 @@ gsr_status build_att_order(gsr_handle* h, hipStream_t s) {
     h->att_ng = (int)(nb * kXcd);
     GSR_TRY(dalloc(&h->att_seg, (size_t)h->att_ng + 1));
     GSR_TRY(dalloc(&h->att_part, (size_t)h->att_ng * kAxes * h->att_lw));
-    // the vector step reads the groups' sums even when the pass that writes them was skipped
-    fill(h->att_part, (int64_t)h->att_ng * kAxes * h->att_lw, 0.0, s);
-    if (m == 0) {  // every group empty
-        HIP_TRY(hipMemsetAsync(h->att_seg, 0, sizeof(int64_t) * ((size_t)h->att_ng + 1), s));
-        return GSR_OK;
-    }
+    if (m == 0) return GSR_OK;
     int shift = 16;
     while (shift > 8 && (m >> shift) < 64) --shift;
     const int sbits = bits_for(((m - 1) >> shift) / kXcd);
@@ -582,127 +574,100 @@ void mark(hipEvent_t e, hipStream_t s) {
 }
 
 // The fused row pass (u-step of the forward solve from uin to uout, or with TRANS the v-step
-// of the adjoint solve, uin == uout, with its pending z/w update in ww/zz), which begins with the
-// scalar step `step`; then the instrumental/global block sums and the attitude columns (the latter
-// into h->att_part).  Sum-of-squares partials go to `parts`.
+// of the adjoint solve, uin == uout, with its pending z/w update in ww/zz), then the
+// instrumental/global block sums and the attitude columns of s from the attitude copy.
+// Sum-of-squares partials go to `parts`.
 template <typename VT, bool TRANS = false>
-void launch_fused(const gsr_handle* h, const StepArgs& step, const VT* attT, const double* uin,
-                  double* uout, double* s_acc, double* parts, hipStream_t s,
+void launch_fused(const gsr_handle* h, const VT* attT, const double* uin, double* uout,
+                  double* s_acc, double* parts, hipStream_t s,
                   const IterEvents* ev, double* ww = nullptr, double* zz = nullptr) {
     const Geo& g = h->g;
     const RowPlan& rp = h->row12;
-    const LsqrState* st = step.out ? step.out : step.in;  // the state after the step
     const int pstride = rp.grid + h->nc1;  // partial sums: the blocks, then the constraint rows
     if (ev) mark(TRANS ? ev->a2_begin : ev->a1_begin, s);
-    const RowArgs<VT> a = {g,    tiles_of<VT>(h), h->star,    h->xt, h->xa, uin,     uout,  s_acc,
-                           step, parts,           h->part_ig, ww,    zz,    pstride, rp.tw, rp.nsb};
+    // constraint rows of the same step (with the transposed operator, their pending z/w update
+    // too)
+    launch_con_a1<CON_LSQR, TRANS, TRANS>(h, h->xt, uin + g.m, uout + g.m, nullptr,
+                                          parts + rp.grid, pstride, TRANS ? ww + g.m : nullptr,
+                                          TRANS ? zz + g.m : nullptr, s);
+    const RowArgs<VT> a = {g,     tiles_of<VT>(h), h->star,    h->xt, h->xa, uin,     uout,  s_acc,
+                           h->st, parts,           h->part_ig, ww,    zz,    pstride, rp.tw, rp.nsb};
     if (rp.reg)
         hipLaunchKernelGGL((k_aprod12_reg<VT, TRANS>), dim3(rp.grid), dim3(kRowBlock), rp.lds, s,
                            a);
     else
         hipLaunchKernelGGL((k_aprod12<VT, TRANS>), dim3(rp.grid), dim3(kRowBlock), rp.lds, s, a);
-    // constraint rows of the same step (with the transposed operator, their pending z/w update
-    // too)
-    launch_con_a1<CON_LSQR, TRANS, TRANS>(h, st, h->xt, uin + g.m, uout + g.m, nullptr,
-                                          parts + rp.grid, pstride, TRANS ? ww + g.m : nullptr,
-                                          TRANS ? zz + g.m : nullptr, s);
     if (ev) mark(TRANS ? ev->a2_end : ev->a1_end, s);
     if (ev) mark(TRANS ? ev->a1_begin : ev->a2_begin, s);
-    launch_att<VT, A2_LSQR>(h, st, attT, uout, s_acc, rp.grid, s);
-    launch_con_a2<false>(h, st, uout + g.m, s_acc, 1, s);
+    launch_reduce(h, rp.grid, s_acc, 1, s);
+    launch_att<VT, A2_LSQR>(h, attT, uout, s_acc, s);
+    launch_con_a2<false>(h, uout + g.m, s_acc, 1, s);
     if (ev) mark(TRANS ? ev->a1_end : ev->a2_end, s);
 }
 
-// Arguments of a vector step that begins with the scalar step `step`.
-VecArgs vec_args(const gsr_handle* h, const LsqrWork& w, const double* p, double* v,
-                 const StepArgs& step, double* partials) {
-    return {h->g.n, h->s,        p,
-            v,      w.w,         w.z,
-            h->xt,  w.var,       att_copy(h),
-            AttSum{h->att_part, h->att_w, h->att_lw}, step, partials};
-}
-
-StepArgs no_step(const gsr_handle* h) { return {h->st, nullptr, nullptr, 0, 0, STEP_NONE}; }
-
-// alpha step in place, at the end of a sequence of iterations (the last one's; within the
-// sequence the next iteration's first kernel takes it)
-void finish_alpha(const gsr_handle* h, hipStream_t s, const double* pv, int Gv, const double* pz,
-                  int Gz) {
-    hipLaunchKernelGGL(k_scal_alpha, dim3(1), dim3(kBlock), 0, s, h->st, pv, Gv, pz, Gz);
-}
-
-// One forward iteration.  `it` counts from the start of the solve or graph (even there): u~ goes
-// from u to u2 or back.  alpha_due: the previous iteration's alpha step has not been taken yet.
-// Afterwards this one's is due.  The state passes from h->st (before the alpha step) through
-// h->st2 (after it) back to h->st (after the beta step).
 template <typename VT, bool VAR = false>
 void fwd_iteration(const gsr_handle* h, LsqrWork& w, const VT* attT, const double* p,
-                   hipStream_t s, int it, bool alpha_due, const IterEvents* ev = nullptr) {
-    const StepArgs alpha = {h->st, h->st2, h->partB, h->Gv, h->Gv,
-                            alpha_due ? STEP_ALPHA : STEP_NONE};
-    int n_part;
+                   hipStream_t s, int it, const IterEvents* ev = nullptr) {
+    const Geo& g = h->g;
     if (h->fused) {
-        // one read of every row: beta u = A (p o v) - alpha u and s = A^T u~ (unnormalized)
-        launch_fused<VT>(h, alpha, attT, it % 2 ? w.u2 : w.u, it % 2 ? w.u : w.u2, h->s, h->partA,
+        // one read of every row: beta u = A (p o v) - alpha u and s = A^T u~ (unnormalized);
+        // iteration `it` of the solve reads u~ from u or u2 and writes it to the other
+        launch_fused<VT>(h, attT, it % 2 ? w.u2 : w.u, it % 2 ? w.u : w.u2, h->s, h->partA,
                          s, ev);
-        n_part = h->row12.grid + h->nc1;
+        hipLaunchKernelGGL(k_scal_beta, dim3(1), dim3(kBlock), 0, s, h->st, h->partA,
+                           h->row12.grid + h->nc1);
     } else {
         // beta u = A (p o v) - alpha u        (xt = p o v~ from the previous vector step)
         if (ev) mark(ev->a1_begin, s);
-        launch_aprod1<VT, A1_LSQR>(h, alpha, h->xt, w.u, nullptr, s);
+        launch_aprod1<VT, A1_LSQR>(h, h->xt, w.u, nullptr, s);
         if (ev) mark(ev->a1_end, s);
+        hipLaunchKernelGGL(k_scal_beta, dim3(1), dim3(kBlock), 0, s, h->st, h->partA,
+                           h->dot.grid + h->nc1);
         // s = A^T u~ (unnormalized)
         if (ev) mark(ev->a2_begin, s);
-        launch_aprod2<VT, A2_LSQR>(h, h->st2, attT, w.u, h->s, s);
+        launch_aprod2<VT, A2_LSQR>(h, attT, w.u, h->s, s);
         if (ev) mark(ev->a2_end, s);
-        n_part = h->dot.grid + h->nc1;
     }
     // alpha v = p o (s / beta) - beta v, with the pending z/w update of the previous iteration
-    const StepArgs beta = {h->st2, h->st, h->partA, n_part, 0, STEP_BETA};
-    hipLaunchKernelGGL((k_vec_v<false, VAR>), dim3(h->Gv), dim3(kVecBlock), 0, s,
-                       vec_args(h, w, p, w.v, beta, h->partB));
-}
-
-void fwd_finish(const gsr_handle* h, hipStream_t s) {
-    finish_alpha(h, s, h->partB, h->Gv, h->partB + h->Gv, h->Gv);
+    hipLaunchKernelGGL((k_vec_v<false, VAR>), dim3(h->Gn), dim3(kBlock), 0, s, g.n, h->s, p, w.v,
+                       w.w, w.z, h->xt, att_copy(h), h->st, h->partB, w.var);
+    hipLaunchKernelGGL(k_scal_alpha, dim3(1), dim3(kBlock), 0, s, h->st, h->partB, h->Gn,
+                       h->partB + h->Gn, h->Gn);
 }
 
 // Transposed operator B = D A^T (rows = n_cols, cols = n_rows): u lives in the unknowns'
-// space, v / w / z in the observations' space.  alpha_due as above (fused form; the state passes
-// from h->st through h->st2, after the alpha step, back to h->st, after the beta step); the
-// unfused form takes its steps in kernels of their own.
-void trans_iteration(const gsr_handle* h, LsqrWork& w, hipStream_t s, bool alpha_due,
+// space, v / w / z in the observations' space.
+void trans_iteration(const gsr_handle* h, LsqrWork& w, hipStream_t s,
                      const IterEvents* ev = nullptr) {
+    const Geo& g = h->g;
     if (h->fused) {
-        const int P = h->row12.grid + h->nc1;
-        const StepArgs alpha = {h->st, h->st2, h->partB, P, P, alpha_due ? STEP_ALPHA : STEP_NONE};
         // beta u = D A^T v - alpha u  (s = A^T v~ left by the previous row pass)
-        hipLaunchKernelGGL(k_vec_tu, dim3(h->Gv), dim3(kVecBlock), 0, s,
-                           vec_args(h, w, h->p64, w.u, alpha, h->partA));
+        hipLaunchKernelGGL(k_vec_tu, dim3(h->Gn), dim3(kBlock), 0, s, g.n, h->s, h->p64, w.u,
+                           h->xt, att_copy(h), h->st, h->partA);
+        hipLaunchKernelGGL(k_scal_beta, dim3(1), dim3(kBlock), 0, s, h->st, h->partA, h->Gn);
         // one read of every row: pending z/w update, alpha v = A D u - beta v, s = A^T v~
-        const StepArgs beta = {h->st2, h->st, h->partA, h->Gv, 0, STEP_BETA};
-        launch_fused<double, true>(h, beta, h->attT64, w.v, w.v, h->s, h->partB, s, ev, w.w, w.z);
+        launch_fused<double, true>(h, h->attT64, w.v, w.v, h->s, h->partB, s, ev, w.w,
+                                   w.z);
+        const int P = h->row12.grid + h->nc1;
+        hipLaunchKernelGGL(k_scal_alpha, dim3(1), dim3(kBlock), 0, s, h->st, h->partB, P,
+                           h->partB + P, P);
         return;
     }
     // beta u = D A^T v - alpha u
     if (ev) mark(ev->a2_begin, s);
-    launch_aprod2<double, A2_LSQR_T>(h, h->st, h->attT64, w.v, h->s, s);
+    launch_aprod2<double, A2_LSQR_T>(h, h->attT64, w.v, h->s, s);
     if (ev) mark(ev->a2_end, s);
-    hipLaunchKernelGGL(k_vec_tu, dim3(h->Gv), dim3(kVecBlock), 0, s,
-                       vec_args(h, w, h->p64, w.u, no_step(h), h->partA));
-    hipLaunchKernelGGL(k_scal_beta, dim3(1), dim3(kBlock), 0, s, h->st, h->partA, h->Gv);
+    hipLaunchKernelGGL(k_vec_tu, dim3(h->Gn), dim3(kBlock), 0, s, g.n, h->s, h->p64, w.u, h->xt,
+                       att_copy(h), h->st, h->partA);
+    hipLaunchKernelGGL(k_scal_beta, dim3(1), dim3(kBlock), 0, s, h->st, h->partA, h->Gn);
     // pending z/w update, then alpha v = A D u - beta v
     hipLaunchKernelGGL(k_vec_zw, dim3(h->Gm), dim3(kBlock), 0, s, h->rows(), w.v, w.w, w.z,
                        h->st, h->partB);
     if (ev) mark(ev->a1_begin, s);
-    launch_aprod1<double, A1_LSQR_T>(h, no_step(h), h->xt, w.v, nullptr, s);
+    launch_aprod1<double, A1_LSQR_T>(h, h->xt, w.v, nullptr, s);
     if (ev) mark(ev->a1_end, s);
-    finish_alpha(h, s, h->partA, h->dot.grid + h->nc1, h->partB, h->Gm);
-}
-
-void trans_finish(const gsr_handle* h, hipStream_t s) {
-    const int P = h->row12.grid + h->nc1;
-    if (h->fused) finish_alpha(h, s, h->partB, P, h->partB + P, P);
+    hipLaunchKernelGGL(k_scal_alpha, dim3(1), dim3(kBlock), 0, s, h->st, h->partA,
+                       h->dot.grid + h->nc1, h->partB, h->Gm);
 }
 
 // Profile mode: the iterations are launched one by one with events around the products;
@@ -721,7 +686,7 @@ gsr_status run_profiled(gsr_handle* h, const gsr_solve_opts& o, hipStream_t s, F
     int launched = 0;
     gsr_status rc = GSR_OK;
     for (int it = 0; it < o.itnlim; ++it) {
-        iteration(s, it, &ev[(size_t)it]);  // takes its alpha step itself
+        iteration(s, it, &ev[(size_t)it]);
         ++launched;
         if (!o.fixed_iters && (it + 1) % every == 0) {
             hipError_t e = hipMemcpyAsync(&h->st_host->stop, &h->st->stop, sizeof(int32_t),
@@ -763,7 +728,7 @@ gsr_status capture_graph(gsr_handle* h, LsqrWork& w, F&& body) {
     if (w.graph) return GSR_OK;
     hipGraph_t graph = nullptr;
     HIP_TRY(hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal));
-    body(h->cap);
+    for (int k = 0; k < kGraphIters; ++k) body(h->cap, k);
     hipError_t e = hipStreamEndCapture(h->cap, &graph);
     if (e != hipSuccess) return hip_fail(e, "hipStreamEndCapture");
     e = hipGraphInstantiate(&w.graph, graph, nullptr, nullptr, 0);
@@ -834,11 +799,8 @@ gsr_status fwd_solve(gsr_handle* h, LsqrWork& w, const VT* attT, const double* p
     const Geo& g = h->g;
     GSR_TRY(ensure_work(w, h->rows(), g.n, VAR));
     GSR_TRY(capture_graph(
-        h, w, [&](hipStream_t cs) {
-            for (int it = 0; it < kGraphIters; ++it)
-                fwd_iteration<VT, VAR>(h, w, attT, p, cs, it, it > 0);
-            fwd_finish(h, cs);
-        }));
+        h, w,
+        [&](hipStream_t cs, int it) { fwd_iteration<VT, VAR>(h, w, attT, p, cs, it); }));
     // beta_1 u_1 = b
     hipLaunchKernelGGL(k_copy_norm<false>, dim3(h->Gm), dim3(kBlock), 0, s, h->rows(), b, nullptr,
                        w.u, nullptr, AttCopy{}, h->partA);
@@ -846,17 +808,16 @@ gsr_status fwd_solve(gsr_handle* h, LsqrWork& w, const VT* attT, const double* p
                        o.itnlim, o.fixed_iters, o.atol, o.btol, o.conlim);
     // alpha_1 v_1 = p o A^T u_1  (the initial aprod 2)
     fill(h->s, g.n, 0.0, s);
-    launch_aprod2<VT, A2_LSQR>(h, h->st, attT, w.u, h->s, s);
-    hipLaunchKernelGGL((k_vec_v<true, VAR>), dim3(h->Gv), dim3(kVecBlock), 0, s,
-                       vec_args(h, w, p, w.v, no_step(h), h->partB));
-    hipLaunchKernelGGL(k_scal_init2, dim3(1), dim3(kBlock), 0, s, h->st, h->partB, h->Gv);
+    launch_aprod2<VT, A2_LSQR>(h, attT, w.u, h->s, s);
+    hipLaunchKernelGGL((k_vec_v<true, VAR>), dim3(h->Gn), dim3(kBlock), 0, s, g.n, h->s, p, w.v,
+                       w.w, w.z, h->xt, att_copy(h), h->st, h->partB, w.var);
+    hipLaunchKernelGGL(k_scal_init2, dim3(1), dim3(kBlock), 0, s, h->st, h->partB, h->Gn);
     ProfileOut prof;
     if (o.profile)
         GSR_TRY(run_profiled(
             h, o, s,
             [&](hipStream_t cs, int it, const IterEvents* ev) {
-                fwd_iteration<VT, VAR>(h, w, attT, p, cs, it, false, ev);
-                fwd_finish(h, cs);
+                fwd_iteration<VT, VAR>(h, w, attT, p, cs, it, ev);
             },
             &prof.ms1, &prof.ms2, &prof.n));
     else
@@ -907,12 +868,11 @@ void fwd_enqueue(const gsr_handle* h, LsqrWork& w, const VT* attT, const double*
     hipLaunchKernelGGL(k_scal_init1, dim3(1), dim3(kBlock), 0, s, h->st, h->partA, h->Gm,
                        o.itnlim, o.fixed_iters, o.atol, o.btol, o.conlim, gate);
     fill(h->s, g.n, 0.0, s);
-    launch_aprod2<VT, A2_LSQR>(h, h->st, attT, w.u, h->s, s);
-    hipLaunchKernelGGL((k_vec_v<true>), dim3(h->Gv), dim3(kVecBlock), 0, s,
-                       vec_args(h, w, p, w.v, no_step(h), h->partB));
-    hipLaunchKernelGGL(k_scal_init2, dim3(1), dim3(kBlock), 0, s, h->st, h->partB, h->Gv);
-    for (int it = 0; it < o.itnlim; ++it) fwd_iteration<VT>(h, w, attT, p, s, it, it > 0);
-    if (o.itnlim > 0) fwd_finish(h, s);
+    launch_aprod2<VT, A2_LSQR>(h, attT, w.u, h->s, s);
+    hipLaunchKernelGGL((k_vec_v<true>), dim3(h->Gn), dim3(kBlock), 0, s, g.n, h->s, p, w.v,
+                       w.w, w.z, h->xt, att_copy(h), h->st, h->partB, nullptr);
+    hipLaunchKernelGGL(k_scal_init2, dim3(1), dim3(kBlock), 0, s, h->st, h->partB, h->Gn);
+    for (int it = 0; it < o.itnlim; ++it) fwd_iteration<VT>(h, w, attT, p, s, it);
     hipLaunchKernelGGL((k_final<true>), dim3(h->Gn), dim3(kBlock), 0, s, g.n, p, w.z, w.w, w.v,
                        x, h->st);
 }
@@ -965,7 +925,7 @@ gsr_status f32v_solve_async(gsr_handle* h, const double* b, double* x, const gsr
                            inner_opts(o, k), s, gate);
         ref_step(h, x, o, s);
         if (k + 1 < o.max_refine)
-            launch_aprod1<double, A1_RESID>(h, StepArgs{}, x, h->r, b, s, gate);
+            launch_aprod1<double, A1_RESID>(h, x, h->r, b, s, gate);
     }
     hipLaunchKernelGGL(k_write_info, dim3(1), dim3(64), 0, s, h->st, info_dev, (int32_t)h->fused,
                        h->ref);
@@ -978,10 +938,7 @@ gsr_status trans_solve(gsr_handle* h, const double* gvec, double* mu, const gsr_
     const Geo& g = h->g;
     LsqrWork& w = h->trans;
     GSR_TRY(ensure_work(w, g.n, h->rows(), false, false));
-    GSR_TRY(capture_graph(h, w, [&](hipStream_t cs) {
-        for (int it = 0; it < kGraphIters; ++it) trans_iteration(h, w, cs, it > 0);
-        trans_finish(h, cs);
-    }));
+    GSR_TRY(capture_graph(h, w, [&](hipStream_t cs, int) { trans_iteration(h, w, cs); }));
     // beta_1 u_1 = D g
     hipLaunchKernelGGL(k_copy_norm<true>, dim3(h->Gn), dim3(kBlock), 0, s, g.n, gvec, h->p64,
                        w.u, h->xt, att_copy(h), h->partA);
@@ -992,12 +949,12 @@ gsr_status trans_solve(gsr_handle* h, const double* gvec, double* mu, const gsr_
     // alpha_1 v_1 = A D u_1 (and, fused, s = A^T v~_1 for the first u-step)
     if (h->fused) {
         fill(h->s, g.n, 0.0, s);
-        launch_fused<double, true>(h, no_step(h), h->attT64, w.v, w.v, h->s, h->partB, s, nullptr,
+        launch_fused<double, true>(h, h->attT64, w.v, w.v, h->s, h->partB, s, nullptr,
                                    w.w, w.z);
         hipLaunchKernelGGL(k_scal_init2, dim3(1), dim3(kBlock), 0, s, h->st, h->partB,
                            h->row12.grid + h->nc1);
     } else {
-        launch_aprod1<double, A1_LSQR_T>(h, no_step(h), h->xt, w.v, nullptr, s);
+        launch_aprod1<double, A1_LSQR_T>(h, h->xt, w.v, nullptr, s);
         hipLaunchKernelGGL(k_scal_init2, dim3(1), dim3(kBlock), 0, s, h->st, h->partA,
                            h->dot.grid + h->nc1);
     }
@@ -1005,10 +962,7 @@ gsr_status trans_solve(gsr_handle* h, const double* gvec, double* mu, const gsr_
     if (o.profile)
         GSR_TRY(run_profiled(
             h, o, s,
-            [&](hipStream_t cs, int, const IterEvents* ev) {
-                trans_iteration(h, w, cs, false, ev);
-                trans_finish(h, cs);
-            },
+            [&](hipStream_t cs, int, const IterEvents* ev) { trans_iteration(h, w, cs, ev); },
             &prof.ms1, &prof.ms2, &prof.n));
     else
         GSR_TRY(run_iterations(h, w, o, s));
@@ -1235,7 +1189,6 @@ gsr_status gsr_lsqr_setup(const gsr_dims* dims, const double* vals, const int32_
         return st;
     };
 
-    h->Gv = grid_for(g.n, kVecBlock, kVecBlocks);
     h->Gn = grid_for(g.n, kBlock, kVecBlocksMax);
     h->Gm = grid_for(g.m, kBlock, kVecBlocksMax);
     h->dot = plan_dot(g, n_cu);
@@ -1259,7 +1212,6 @@ gsr_status gsr_lsqr_setup(const gsr_dims* dims, const double* vals, const int32_
                                       (g.I + 1))) != GSR_OK)
         return bail(st);
     if ((st = dalloc(&h->st, 1)) != GSR_OK) return bail(st);
-    if ((st = dalloc(&h->st2, 1)) != GSR_OK) return bail(st);
     // the binary64 solve's vectors: allocated here so that a stream-ordered solve allocates
     // nothing
     if ((st = ensure_work(h->fwd64, g.m, g.n)) != GSR_OK) return bail(st);
@@ -1362,7 +1314,6 @@ gsr_status gsr_destroy(gsr_handle* h) {
     dfree(h->partA);
     dfree(h->partB);
     dfree(h->st);
-    dfree(h->st2);
     dfree(h->r);
     dfree(h->ref_part);
     dfree(h->ref);
@@ -1472,7 +1423,7 @@ gsr_status gsr_set_constraints(gsr_handle* h, int64_t n_con, const int64_t* ptr,
 gsr_status gsr_aprod1(gsr_handle* h, const double* x, double* y, void* stream) {
     if (!h || !x || !y) return fail(GSR_E_INVAL, "null argument");
     GSR_TRY(set_device(h));
-    launch_aprod1<double, A1_ADD>(h, StepArgs{}, x, y, nullptr, as_stream(stream));
+    launch_aprod1<double, A1_ADD>(h, x, y, nullptr, as_stream(stream));
     HIP_TRY(hipGetLastError());
     return GSR_OK;
 }
@@ -1480,7 +1431,7 @@ gsr_status gsr_aprod1(gsr_handle* h, const double* x, double* y, void* stream) {
 gsr_status gsr_aprod2(gsr_handle* h, const double* y, double* x, void* stream) {
     if (!h || !x || !y) return fail(GSR_E_INVAL, "null argument");
     GSR_TRY(set_device(h));
-    launch_aprod2<double, A2_ADD>(h, h->st, h->attT64, y, x, as_stream(stream));
+    launch_aprod2<double, A2_ADD>(h, h->attT64, y, x, as_stream(stream));
     HIP_TRY(hipGetLastError());
     return GSR_OK;
 }
@@ -1489,7 +1440,7 @@ gsr_status gsr_aprod1_f32v(gsr_handle* h, const double* x, double* y, void* stre
     if (!h || !x || !y) return fail(GSR_E_INVAL, "null argument");
     if (!h->has_f32) return fail(GSR_E_UNSUPPORTED, "binary32 copy not built (build_f32 = 0)");
     GSR_TRY(set_device(h));
-    launch_aprod1<float, A1_ADD>(h, StepArgs{}, x, y, nullptr, as_stream(stream));
+    launch_aprod1<float, A1_ADD>(h, x, y, nullptr, as_stream(stream));
     HIP_TRY(hipGetLastError());
     return GSR_OK;
 }
@@ -1498,7 +1449,7 @@ gsr_status gsr_aprod2_f32v(gsr_handle* h, const double* y, double* x, void* stre
     if (!h || !x || !y) return fail(GSR_E_INVAL, "null argument");
     if (!h->has_f32) return fail(GSR_E_UNSUPPORTED, "binary32 copy not built (build_f32 = 0)");
     GSR_TRY(set_device(h));
-    launch_aprod2<float, A2_ADD>(h, h->st, h->attT32, y, x, as_stream(stream));
+    launch_aprod2<float, A2_ADD>(h, h->attT32, y, x, as_stream(stream));
     HIP_TRY(hipGetLastError());
     return GSR_OK;
 }
@@ -1517,7 +1468,7 @@ gsr_status gsr_residual(gsr_handle* h, const double* b, const double* x, double*
                         void* stream) {
     if (!h || !b || !x || !r) return fail(GSR_E_INVAL, "null argument");
     GSR_TRY(set_device(h));
-    launch_aprod1<double, A1_RESID>(h, StepArgs{}, x, r, b, as_stream(stream));
+    launch_aprod1<double, A1_RESID>(h, x, r, b, as_stream(stream));
     HIP_TRY(hipGetLastError());
     return GSR_OK;
 }
@@ -1547,7 +1498,7 @@ gsr_status gsr_lsqr_solve(gsr_handle* h, const double* b, double* x, const gsr_s
         HIP_TRY(hipMemcpyAsync(h->ref_host, h->ref, sizeof(RefState), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         if (h->ref_host->stop) break;
-        launch_aprod1<double, A1_RESID>(h, StepArgs{}, x, h->r, b, s);
+        launch_aprod1<double, A1_RESID>(h, x, h->r, b, s);
     }
     HIP_TRY(hipGetLastError());
     if (info) {

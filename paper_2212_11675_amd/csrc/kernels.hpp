@@ -23,9 +23,7 @@ constexpr int kAxes = 3;     // attitude axes
 constexpr int kParAxis = 4;  // attitude coefficients per axis
 constexpr int kInstr = 6;    // instrumental coefficients per row
 constexpr int kWave = 64;    // gfx950 wavefront
-constexpr int kBlock = 256;  // threads per block of the small kernels
-constexpr int kVecBlock = 512;   // threads per block of the solver's vector steps
-constexpr int kXcd = 8;  // accelerator dies; the dispatcher places block i on die i % 8
+constexpr int kBlock = 256;  // threads per block of the row kernels
 constexpr int kInstrLdsMax = 10240;  // instrumental columns privatized in LDS (80 KiB)
 
 // Column geometry of one system.
@@ -142,26 +140,6 @@ __device__ __forceinline__ void put_att(const AttCopy& a, int64_t j, double v) {
     a.xa[kAxes * (c - ax * a.T) + ax] = v;
 }
 
-// The attitude columns of A^T u~ as the attitude pass leaves them: sums of the groups (bucket b,
-// die d), kAxes rows of lw columns each, buckets w knots apart.  The sum of column c of one axis
-// over the groups whose bucket covers it: bucket c / w of every die and the buckets before it
-// whose columns reach c (the previous one for the first kParAxis - 1 columns of a bucket when
-// w >= kParAxis - 1, more when w is smaller).
-struct AttSum {
-    const double* part;
-    int w, lw;
-};
-__device__ __forceinline__ double att_sum(const AttSum& a, int ax, int c) {
-    double sum = 0.0;
-    for (int b = c / a.w; b >= 0 && c - (int64_t)b * a.w < a.lw; --b) {
-        const double* __restrict__ p =
-            a.part + ((int64_t)b * kXcd * kAxes + ax) * a.lw + (c - (int64_t)b * a.w);
-#pragma unroll
-        for (int d = 0; d < kXcd; ++d) sum += p[(int64_t)d * kAxes * a.lw];
-    }
-    return sum;
-}
-
 // u = src (o p if PRE); block partial of sum u^2
 // (PRE: also xt = p o u, the operand of the next aprod 1, and its attitude copy)
 template <bool PRE>
@@ -181,6 +159,102 @@ static __global__ __launch_bounds__(kBlock) void k_copy_norm(int64_t n, const do
             put_att(ac, j, p[j] * v);
         }
         acc = fma(v, v, acc);
+    }
+    const double tot = block_sum<kBlock>(acc, sh);
+    if (threadIdx.x == 0) partials[blockIdx.x] = tot;
+}
+
+// Forward operator, after aprod 2 accumulated s = A^T (su u~):
+//   INIT : v~ = p o s;                 z = 0, w = 0
+//   else : apply the pending update  z += f1 w; w = sv v~ - f2 w  (old v~), then
+//          v~ = p o s - beta sv v~
+// s is reset to 0 and xt = p o v~ (the operand of the next aprod 1) and its attitude copy are
+// written.
+// Partials (4 rows of G): sum v~^2, sum z^2, sum z w, sum w^2.
+// VAR: also the variance estimate var += (w / rho)^2 with the w of the pending update.
+template <bool INIT, bool VAR = false>
+static __global__ __launch_bounds__(kBlock) void k_vec_v(int64_t n, double* __restrict__ s,
+                                                  const double* __restrict__ p,
+                                                  double* __restrict__ v, double* __restrict__ w,
+                                                  double* __restrict__ z, double* __restrict__ xt,
+                                                  AttCopy ac, const LsqrState* __restrict__ st,
+                                                  double* __restrict__ partials,
+                                                  double* __restrict__ var = nullptr) {
+    __shared__ double sh[kBlock / kWave];
+    if (!INIT && st->stop) return;
+    const bool pending = !INIT && st->pending;
+    const double f1 = st->f1, f2 = st->f2, sv = st->sv;
+    const double c1 = INIT ? 0.0 : st->beta * st->sv;
+    const double su = st->su;  // s holds A^T u~ unnormalized
+    const double rinv = st->rinv;
+    double avv = 0.0, azz = 0.0, azw = 0.0, aww = 0.0;
+    const int64_t stride = (int64_t)gridDim.x * kBlock;
+    for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < n; j += stride) {
+        const double sj = s[j];
+        s[j] = 0.0;
+        double vn;
+        if (INIT) {
+            vn = p[j] * (su * sj);
+            z[j] = 0.0;
+            w[j] = 0.0;
+            if (VAR) var[j] = 0.0;
+        } else {
+            const double vj = v[j];
+            if (pending) {
+                const double wj = w[j];
+                if (VAR) {
+                    const double d = wj * rinv;
+                    var[j] = fma(d, d, var[j]);
+                }
+                const double zj = fma(f1, wj, z[j]);
+                const double wn = sv * vj - f2 * wj;
+                z[j] = zj;
+                w[j] = wn;
+                azz = fma(zj, zj, azz);
+                azw = fma(zj, wn, azw);
+                aww = fma(wn, wn, aww);
+            }
+            vn = p[j] * (su * sj) - c1 * vj;
+        }
+        v[j] = vn;
+        xt[j] = p[j] * vn;
+        put_att(ac, j, p[j] * vn);
+        avv = fma(vn, vn, avv);
+    }
+    const int G = gridDim.x;
+    double tot = block_sum<kBlock>(avv, sh);
+    if (threadIdx.x == 0) partials[blockIdx.x] = tot;
+    if (!INIT) {
+        tot = block_sum<kBlock>(azz, sh);
+        if (threadIdx.x == 0) partials[G + blockIdx.x] = tot;
+        tot = block_sum<kBlock>(azw, sh);
+        if (threadIdx.x == 0) partials[2 * G + blockIdx.x] = tot;
+        tot = block_sum<kBlock>(aww, sh);
+        if (threadIdx.x == 0) partials[3 * G + blockIdx.x] = tot;
+    }
+}
+
+// Transposed operator, u-step after aprod 2 accumulated s = A^T v~ (unnormalized):
+//   u~ = p o (sv s) - alpha su u~ ; s = 0 ; xt = p o u~ ; partial sum u~^2.
+static __global__ __launch_bounds__(kBlock) void k_vec_tu(int64_t n, double* __restrict__ s,
+                                                   const double* __restrict__ p,
+                                                   double* __restrict__ u, double* __restrict__ xt,
+                                                   AttCopy ac, const LsqrState* __restrict__ st,
+                                                   double* __restrict__ partials) {
+    __shared__ double sh[kBlock / kWave];
+    if (st->stop) return;
+    const double c1 = st->alpha * st->su;
+    const double sv = st->sv;  // s holds A^T v~ unnormalized
+    double acc = 0.0;
+    const int64_t stride = (int64_t)gridDim.x * kBlock;
+    for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < n; j += stride) {
+        const double sj = s[j];
+        s[j] = 0.0;
+        const double un = p[j] * (sv * sj) - c1 * u[j];
+        u[j] = un;
+        xt[j] = p[j] * un;
+        put_att(ac, j, p[j] * un);
+        acc = fma(un, un, acc);
     }
     const double tot = block_sum<kBlock>(acc, sh);
     if (threadIdx.x == 0) partials[blockIdx.x] = tot;
@@ -446,220 +520,6 @@ __device__ __forceinline__ void scal_alpha(LsqrState* st, double vv, double zz, 
         }
     }
     if (st->itn >= st->itnlim) st->stop = 1;
-}
-
-// The scalar step between two kernels of an iteration, taken by every block of the second one
-// for itself: a kernel of its own is a launch and a gap of 4 to 5 us for a chain of some 30
-// dependent operations.  The loads of that chain run beside the kernel's own first loads (the
-// elements of a vector step, the unknowns a row pass stages), so the step adds less than 1 us to
-// k_aprod12 and 2 us to k_vec_v (an iteration of 6e4 rows 28.9 -> 21.3 us, of 3.15e5 rows 49 ->
-// 39.5, of 1.1e6 rows 99.6 -> 90.7, with the attitude sums below and the instrumental reduction
-// moved into their neighbours too).  The block reads the state `in`, sums all of the first
-// kernel's partials (at most 4 x 1,024 of them) in the same order as every other block, applies
-// the step to its own copy, and block 0 writes the new state to `out`, which is not `in`: other
-// blocks may still be reading that.  Returns the new state, in `sh` (kStepScratch doubles); two
-// barriers inside.  A stopped state is passed on unchanged.
-//   STEP_NONE  : the state as it is (out may be NULL)
-//   STEP_BETA  : beta_{i+1} from `part` (G entries)
-//   STEP_ALPHA : alpha_{i+1}, Givens rotation, stopping tests from the four rows of `part`
-//                (stride apart, G entries each)
-enum { STEP_NONE = 0, STEP_BETA = 1, STEP_ALPHA = 2 };
-struct StepArgs {
-    const LsqrState* in;
-    LsqrState* out;
-    const double* part;
-    int G, stride, step;
-};
-constexpr int kStateWords = sizeof(LsqrState) / sizeof(int32_t);
-constexpr int kStepScratch = 4 + sizeof(LsqrState) / sizeof(double);
-
-__device__ __forceinline__ const LsqrState* block_step(const StepArgs& a, double* sh) {
-    LsqrState* s = reinterpret_cast<LsqrState*>(sh + 4);
-    const int w = threadIdx.x / kWave, l = threadIdx.x % kWave;
-    const int rows = a.step == STEP_ALPHA ? 4 : a.step == STEP_BETA ? 1 : 0;
-    if (threadIdx.x < kStateWords)
-        reinterpret_cast<int32_t*>(s)[threadIdx.x] =
-            reinterpret_cast<const int32_t*>(a.in)[threadIdx.x];
-    if (w < rows) {  // one wave per row of partials
-        const double* __restrict__ part = a.part + (int64_t)w * a.stride;
-        double acc = 0.0;
-#pragma unroll 4
-        for (int k = l; k < a.G; k += kWave) acc += part[k];
-        acc = wave_sum(acc);
-        if (l == 0) sh[w] = acc;
-    }
-    __syncthreads();
-    if (rows && threadIdx.x == 0 && !s->stop) {
-        if (a.step == STEP_ALPHA)
-            scal_alpha(s, sh[0], sh[1], sh[2], sh[3]);
-        else
-            scal_beta(s, sh[0]);
-    }
-    __syncthreads();
-    if (a.out && blockIdx.x == 0 && threadIdx.x < kStateWords)
-        reinterpret_cast<int32_t*>(a.out)[threadIdx.x] =
-            reinterpret_cast<const int32_t*>(s)[threadIdx.x];
-    return s;
-}
-
-// Block sums of NQ quantities -> out[q * stride + blockIdx.x], with one barrier (sh: NQ * NT /
-// kWave doubles).
-template <int NT, int NQ>
-__device__ __forceinline__ void block_partials(double (&acc)[NQ], double* sh, double* out,
-                                               int stride) {
-    constexpr int W = NT / kWave;
-    const int w = threadIdx.x / kWave, l = threadIdx.x % kWave;
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        const double t = wave_sum(acc[q]);
-        if (l == 0) sh[q * W + w] = t;
-    }
-    __syncthreads();
-    if (threadIdx.x < NQ) {
-        double t = 0.0;
-#pragma unroll
-        for (int k = 0; k < W; ++k) t += sh[threadIdx.x * W + k];
-        out[(int64_t)threadIdx.x * stride + blockIdx.x] = t;
-    }
-}
-
-// Forward operator, after aprod 2 accumulated s = A^T (su u~) (its attitude columns still in
-// groups, AttSum):
-//   INIT : v~ = p o s;                 z = 0, w = 0
-//   else : the beta step (block_step), apply the pending update  z += f1 w; w = sv v~ - f2 w
-//          (old v~), then  v~ = p o s - beta sv v~
-// s is reset to 0 and xt = p o v~ (the operand of the next aprod 1) and its attitude copy are
-// written.
-// Partials (4 rows of G): sum v~^2, sum z^2, sum z w, sum w^2.
-// VAR: also the variance estimate var += (w / rho)^2 with the w of the pending update.
-// At most kVecBlocks (1,024) blocks, since every block of the next kernel sums all partials.
-// Bound by memory: 9 vectors of 8 bytes per unknown (2e7 rows, 5.2e6 unknowns: 71 us, 5.3 TB/s).
-// The first element's loads come before the scalar step, later ones together at the loop's end
-// (loads issued as the expression needs them, the sums' branch between them: 153 us).
-struct VecArgs {
-    int64_t n;
-    double* s;
-    const double* p;
-    double *v, *w, *z, *xt, *var;
-    AttCopy ac;
-    AttSum as;
-    StepArgs step;
-    double* partials;
-};
-
-// One element's operands, all loaded before the first use (the attitude sums' loads sit under a
-// branch: behind them the others would wait a round trip more).
-template <bool FWD>
-struct VecElem {
-    double s, p, v, w, z;
-    int64_t at;  // place in the attitude copy, -1 outside the attitude columns
-    __device__ __forceinline__ void load(const VecArgs& a, int64_t j) {
-        s = a.s[j];
-        p = a.p[j];
-        v = a.v[j];
-        if (FWD) {
-            w = a.w[j];
-            z = a.z[j];
-        }
-        const int64_t c = j - a.ac.att0;
-        at = -1;
-        if (c >= 0 && c < kAxes * a.ac.T) {
-            const int ax = c >= 2 * a.ac.T ? 2 : c >= a.ac.T ? 1 : 0;
-            const int k = (int)(c - ax * a.ac.T);
-            at = (int64_t)kAxes * k + ax;
-            s += att_sum(a.as, ax, k);
-        }
-    }
-};
-
-template <bool INIT, bool VAR = false>
-static __global__ __launch_bounds__(kVecBlock) void k_vec_v(VecArgs a) {
-    __shared__ double sh[kStepScratch];
-    __shared__ double red[4 * kVecBlock / kWave];
-    const int64_t stride = (int64_t)gridDim.x * kVecBlock;
-    int64_t j = (int64_t)blockIdx.x * kVecBlock + threadIdx.x;
-    VecElem<!INIT> e;
-    if (j < a.n) e.load(a, j);  // on its way during the scalar step
-    const LsqrState* st = block_step(a.step, sh);
-    if (!INIT && st->stop) return;
-    double* __restrict__ s = a.s;
-    double* __restrict__ v = a.v;
-    double* __restrict__ w = a.w;
-    double* __restrict__ z = a.z;
-    double* __restrict__ xt = a.xt;
-    double* __restrict__ var = a.var;
-    const bool pending = !INIT && st->pending;
-    const double f1 = st->f1, f2 = st->f2, sv = st->sv;
-    const double c1 = INIT ? 0.0 : st->beta * st->sv;
-    const double su = st->su;  // s holds A^T u~ unnormalized
-    const double rinv = st->rinv;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    while (j < a.n) {
-        double vn = e.p * (su * e.s);
-        s[j] = 0.0;
-        if (INIT) {
-            z[j] = 0.0;
-            w[j] = 0.0;
-            if (VAR) var[j] = 0.0;
-        } else {
-            if (pending) {
-                if (VAR) {
-                    const double d = e.w * rinv;
-                    var[j] = fma(d, d, var[j]);
-                }
-                const double zj = fma(f1, e.w, e.z);
-                const double wn = sv * e.v - f2 * e.w;
-                z[j] = zj;
-                w[j] = wn;
-                acc[1] = fma(zj, zj, acc[1]);
-                acc[2] = fma(zj, wn, acc[2]);
-                acc[3] = fma(wn, wn, acc[3]);
-            }
-            vn -= c1 * e.v;
-        }
-        const double x = e.p * vn;
-        v[j] = vn;
-        xt[j] = x;
-        if (e.at >= 0) a.ac.xa[e.at] = x;
-        acc[0] = fma(vn, vn, acc[0]);
-        j += stride;
-        if (j < a.n) e.load(a, j);
-    }
-    if (INIT) {
-        double one[1] = {acc[0]};
-        block_partials<kVecBlock, 1>(one, red, a.partials, gridDim.x);
-    } else {
-        block_partials<kVecBlock, 4>(acc, red, a.partials, gridDim.x);
-    }
-}
-
-// Transposed operator, u-step after aprod 2 accumulated s = A^T v~ (unnormalized): the alpha
-// step (block_step), then  u~ = p o (sv s) - alpha su u~ (in v) ; s = 0 ; xt = p o u~ ; partial
-// sum u~^2.
-static __global__ __launch_bounds__(kVecBlock) void k_vec_tu(VecArgs a) {
-    __shared__ double sh[kStepScratch];
-    __shared__ double red[kVecBlock / kWave];
-    const int64_t stride = (int64_t)gridDim.x * kVecBlock;
-    int64_t j = (int64_t)blockIdx.x * kVecBlock + threadIdx.x;
-    VecElem<false> e;
-    if (j < a.n) e.load(a, j);
-    const LsqrState* st = block_step(a.step, sh);
-    if (st->stop) return;
-    const double c1 = st->alpha * st->su;
-    const double sv = st->sv;  // s holds A^T v~ unnormalized
-    double acc[1] = {0.0};
-    while (j < a.n) {
-        const double un = e.p * (sv * e.s) - c1 * e.v;
-        const double x = e.p * un;
-        a.s[j] = 0.0;
-        a.v[j] = un;
-        a.xt[j] = x;
-        if (e.at >= 0) a.ac.xa[e.at] = x;
-        acc[0] = fma(un, un, acc[0]);
-        j += stride;
-        if (j < a.n) e.load(a, j);
-    }
-    block_partials<kVecBlock, 1>(acc, red, a.partials, gridDim.x);
 }
 
 // gate (may be NULL): when *gate is set the solve is not started (st keeps the stopped state

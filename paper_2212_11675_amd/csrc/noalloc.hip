@@ -176,9 +176,8 @@ extern "C" gsr_status gsr_aprod2_noalloc(const gsr_dims* dims, const double* val
     hipLaunchKernelGGL(k_aprod2_star_rows, dim3(blocks), dim3(kThreads), lds_bytes, s, g, vals,
                        star, instr, y, x, part, (int)chunk);
     const int slices = std::max(1, std::min(32, blocks / 8));
-    hipLaunchKernelGGL(k_reduce_partials, dim3((unsigned)((ncols + kBlock - 1) / kBlock * slices)),
-                       dim3(kBlock), 0, s,
-                       ReduceArgs{(int)ncols, blocks, slices, part, x + g.ins0});
+    hipLaunchKernelGGL(k_reduce_partials, dim3((unsigned)((ncols + 255) / 256), slices),
+                       dim3(256), 0, s, (int)ncols, blocks, part, x + g.ins0, nullptr, 0);
     const int64_t att_blocks = std::min<int64_t>((g.m * kQuad + 255) / 256, 8 * (int64_t)n_cu);
     hipLaunchKernelGGL(k_aprod2_att_rows, dim3((unsigned)att_blocks), dim3(256), 0, s, g, vals,
                        att, y, x);

@@ -279,32 +279,23 @@ __device__ __forceinline__ void run_close(double (&acc)[NV], int32_t& ckey, F&& 
     ckey = -1;
 }
 
-// x[c] += sum_b part[b][c] for the n_instr + 1 instrumental and global columns (x at the first):
-// `slices` slices of the blocks, meeting in one atomic add per column.  Block number `blk` of NT
-// threads takes columns (blk % nx) NT .. and slice blk / nx, nx = ceil(ncols / NT).
-struct ReduceArgs {
-    int ncols, nblocks, slices;  // ncols = 0: nothing to do
-    const double* part;
-    double* x;
-};
-template <int NT>
-__device__ __forceinline__ void reduce_columns(const ReduceArgs& a, int blk) {
-    const int nx = (a.ncols + NT - 1) / NT;
-    const int c = blk % nx * NT + threadIdx.x, y = blk / nx;
-    if (c >= a.ncols) return;
-    const int per = (a.nblocks + a.slices - 1) / a.slices;
-    const int b0 = y * per, b1 = min(a.nblocks, b0 + per);
+// x[ins0 + c] += sum_b part[b][c] for the n_instr + 1 instrumental and global columns.
+// blockIdx.y takes a slice of the blocks; slices meet in one atomic add per column.
+static __global__ void k_reduce_partials(int ncols, int nblocks, const double* __restrict__ part,
+                                         double* __restrict__ x, const LsqrState* __restrict__ st,
+                                         int check_stop) {
+    if (check_stop && st->stop) return;
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= ncols) return;
+    const int per = (nblocks + gridDim.y - 1) / gridDim.y;
+    const int b0 = blockIdx.y * per, b1 = min(nblocks, b0 + per);
     double s = 0.0;
-    for (int b = b0; b < b1; ++b) s += a.part[(int64_t)b * a.ncols + c];
-    if (a.slices == 1) {
-        a.x[c] += s;
+    for (int b = b0; b < b1; ++b) s += part[(int64_t)b * ncols + c];
+    if (gridDim.y == 1) {
+        x[c] += s;
     } else if (b0 < b1) {
-        atomic_add_f64(a.x + c, s);
+        atomic_add_f64(x + c, s);
     }
-}
-
-static __global__ __launch_bounds__(kBlock) void k_reduce_partials(ReduceArgs a) {
-    reduce_columns<kBlock>(a, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -365,7 +356,7 @@ struct RowArgs {
     const double* uin;    // old u~ (TRANS: old v~)
     double* uout;
     double* s;
-    StepArgs step;        // scalar step before the pass (alpha; TRANS: beta)
+    const LsqrState* st;
     double* partials;
     double* part;
     double *ww, *zz;      // TRANS: w and z of the row space
@@ -433,8 +424,9 @@ template <typename VT, bool TRANS = false>
 static __global__ __launch_bounds__(kRowBlock) void k_aprod12(RowArgs<VT> p) {
     // [n_instr + 1] sums, [n_instr] staged xt, [tw][kRoundRows] u~, [nsb][5] star sums
     extern __shared__ double lds[];
-    __shared__ double sh[4 * kRowWaves];  // kStepScratch for the step, then partial sums
-    static_assert(kStepScratch <= 4 * kRowWaves, "scratch of the scalar step");
+    __shared__ double sh[kRowWaves];
+    const LsqrState* __restrict__ st = p.st;
+    if (st->stop) return;
     const Geo g = p.g;
     const VT* __restrict__ tiles = p.tiles;
     const int32_t* __restrict__ star = p.star;
@@ -443,7 +435,12 @@ static __global__ __launch_bounds__(kRowBlock) void k_aprod12(RowArgs<VT> p) {
     const double* uin = p.uin;
     double* uout = p.uout;
     double* __restrict__ s = p.s;
+    const double xs = TRANS ? st->su : st->sv;
+    const double ys = TRANS ? st->beta * st->sv : st->alpha * st->su;
+    const bool pending = TRANS && st->pending;
+    const double f1 = st->f1, f2 = st->f2, svo = st->sv;
     const int tw = p.tw, nsb = p.nsb;
+    double zsq = 0.0, zw = 0.0, wsq = 0.0;
     double* lsum = lds;  // instrumental and global sums of the block
     double* lxi = lds + g.I + 1;
     double* ubuf = lds + 2 * (int64_t)g.I + 2;  // 16-byte aligned
@@ -451,13 +448,7 @@ static __global__ __launch_bounds__(kRowBlock) void k_aprod12(RowArgs<VT> p) {
     for (int k = threadIdx.x; k <= g.I; k += kRowBlock) lsum[k] = 0.0;
     for (int k = threadIdx.x; k < g.I; k += kRowBlock) lxi[k] = xx[g.ins0 + k];
     for (int k = threadIdx.x; k < kAstro * nsb; k += kRowBlock) sbuf[k] = 0.0;
-    const LsqrState* st = block_step(p.step, sh);  // its barriers serve the stores above too
-    if (st->stop) return;
-    const double xs = TRANS ? st->su : st->sv;
-    const double ys = TRANS ? st->beta * st->sv : st->alpha * st->su;
-    const bool pending = TRANS && st->pending;
-    const double f1 = st->f1, f2 = st->f2, svo = st->sv;
-    double zsq = 0.0, zw = 0.0, wsq = 0.0;
+    __syncthreads();
     const double* __restrict__ xi = lxi;  // LDS reads (not flat loads tied to vmcnt)
     const int lane = threadIdx.x % kWave, rg = lane / kQuad, q = lane % kQuad;
     const int w = threadIdx.x / kWave;
@@ -540,14 +531,17 @@ static __global__ __launch_bounds__(kRowBlock) void k_aprod12(RowArgs<VT> p) {
     }
     const double gs = wave_sum(gacc);
     if (lane == 0) atomicAdd(lsum + g.I, gs);
-    __syncthreads();  // the state lay in sh (a block without a round comes here at once)
+    const double tot = block_sum<kRowBlock>(usq, sh);
+    if (threadIdx.x == 0) p.partials[blockIdx.x] = tot;
     if (TRANS) {
-        double sums[4] = {usq, zsq, zw, wsq};
-        block_partials<kRowBlock, 4>(sums, sh, p.partials, p.pstride);
-    } else {
-        double sums[1] = {usq};
-        block_partials<kRowBlock, 1>(sums, sh, p.partials, p.pstride);
+        double t2 = block_sum<kRowBlock>(zsq, sh);
+        if (threadIdx.x == 0) p.partials[p.pstride + blockIdx.x] = t2;
+        t2 = block_sum<kRowBlock>(zw, sh);
+        if (threadIdx.x == 0) p.partials[2 * p.pstride + blockIdx.x] = t2;
+        t2 = block_sum<kRowBlock>(wsq, sh);
+        if (threadIdx.x == 0) p.partials[3 * p.pstride + blockIdx.x] = t2;
     }
+    __syncthreads();
     double* dst = p.part + (int64_t)blockIdx.x * (g.I + 1);
     for (int k = threadIdx.x; k <= g.I; k += kRowBlock) dst[k] = lsum[k];
 }
@@ -562,6 +556,8 @@ static __global__ __launch_bounds__(kRowBlock) void k_aprod12(RowArgs<VT> p) {
 template <typename VT, bool TRANS = false>
 static __global__ __launch_bounds__(kRowBlock) void k_aprod12_reg(RowArgs<VT> p) {
     extern __shared__ double lds[];  // [n_instr + 1] sums, [n_instr] staged xt, exchange area
+    const LsqrState* __restrict__ st = p.st;
+    if (st->stop) return;
     const Geo g = p.g;
     const VT* __restrict__ tiles = p.tiles;
     const int32_t* __restrict__ star = p.star;
@@ -570,24 +566,19 @@ static __global__ __launch_bounds__(kRowBlock) void k_aprod12_reg(RowArgs<VT> p)
     const double* uin = p.uin;
     double* uout = p.uout;
     double* __restrict__ s = p.s;
-    double* lsum = lds;
-    double* lxi = lds + g.I + 1;
-    for (int k = threadIdx.x; k < g.I; k += kRowBlock) lxi[k] = xx[g.ins0 + k];
-    const LsqrState* st = block_step(p.step, lsum);  // n_instr is far above kStepScratch here
-    if (st->stop) return;
     const double xs = TRANS ? st->su : st->sv;
     const double ys = TRANS ? st->beta * st->sv : st->alpha * st->su;
-    const bool pending = TRANS && st->pending;
-    const double f1 = TRANS ? st->f1 : 0.0, f2 = TRANS ? st->f2 : 0.0, svo = TRANS ? st->sv : 0.0;
     const int tw = p.tw;
     const bool xb = p.nsb != 0;
     double zsq = 0.0, zw = 0.0, wsq = 0.0;
+    double* lsum = lds;
+    double* lxi = lds + g.I + 1;
     double* xw = lds + 2 * (int64_t)g.I + 1;
     double* xch = xw + kAstro * kRowWaves;
     int32_t* bkey = reinterpret_cast<int32_t*>(xch + kAstro * (kRowWaves + 1));
     constexpr int kXch = kAstro * (kRowWaves + 1);
-    __syncthreads();  // the state lay in lsum
     for (int k = threadIdx.x; k <= g.I; k += kRowBlock) lsum[k] = 0.0;
+    for (int k = threadIdx.x; k < g.I; k += kRowBlock) lxi[k] = xx[g.ins0 + k];
     if (xb && threadIdx.x < kXch) xch[threadIdx.x] = 0.0;
     __syncthreads();
     const double* __restrict__ xi = lxi;
@@ -706,10 +697,10 @@ static __global__ __launch_bounds__(kRowBlock) void k_aprod12_reg(RowArgs<VT> p)
             const int64_t r = (tb + 4 * gi) * kStepRows + kStepRows * q + rg;
             if (r >= r_end) continue;
             if (TRANS) {
-                if (pending) {  // z, w updated with the old v~ of this row
+                if (st->pending) {  // z, w updated with the old v~ of this row
                     const double wo = p.ww[r];
-                    const double zn = fma(f1, wo, p.zz[r]);
-                    const double wn = svo * uin[r] - f2 * wo;
+                    const double zn = fma(st->f1, wo, p.zz[r]);
+                    const double wn = st->sv * uin[r] - st->f2 * wo;
                     p.zz[r] = zn;
                     p.ww[r] = wn;
                     zsq = fma(zn, zn, zsq);
@@ -748,13 +739,17 @@ static __global__ __launch_bounds__(kRowBlock) void k_aprod12_reg(RowArgs<VT> p)
     if (lane == 0) atomicAdd(lsum + g.I, gs);
     __syncthreads();
     double* sh = lxi;  // the staged unknowns are no longer needed
+    const double tot = block_sum<kRowBlock>(usq, sh);
+    if (threadIdx.x == 0) p.partials[blockIdx.x] = tot;
     if (TRANS) {
-        double sums[4] = {usq, zsq, zw, wsq};
-        block_partials<kRowBlock, 4>(sums, sh, p.partials, p.pstride);
-    } else {
-        double sums[1] = {usq};
-        block_partials<kRowBlock, 1>(sums, sh, p.partials, p.pstride);
+        double t2 = block_sum<kRowBlock>(zsq, sh);
+        if (threadIdx.x == 0) p.partials[p.pstride + blockIdx.x] = t2;
+        t2 = block_sum<kRowBlock>(zw, sh);
+        if (threadIdx.x == 0) p.partials[2 * p.pstride + blockIdx.x] = t2;
+        t2 = block_sum<kRowBlock>(wsq, sh);
+        if (threadIdx.x == 0) p.partials[3 * p.pstride + blockIdx.x] = t2;
     }
+    __syncthreads();
     double* dst = p.part + (int64_t)blockIdx.x * (g.I + 1);
     for (int k = threadIdx.x; k <= g.I; k += kRowBlock) dst[k] = lsum[k];
 }
@@ -765,8 +760,7 @@ static __global__ __launch_bounds__(kRowBlock) void k_aprod12_reg(RowArgs<VT> p)
 //   A1_LSQR  : y[i] = xs sum_i - ys y[i]  with (xs, ys) = (sv, alpha su)   [forward operator]
 //   A1_LSQR_T: same with (xs, ys) = (su, beta sv)                           [transposed]
 //   A1_RESID : y[i] = b[i] - sum_i
-// LSQR modes take the scalar step `step` first (block_step) and write the block partial of
-// sum y[i]^2.  gate (may be NULL): nothing is done
+// LSQR modes also write the block partial of sum y[i]^2.  gate (may be NULL): nothing is done
 // when *gate is set (a residual of a correction step that will not be taken).
 // Rounds as in the fused pass: the round's sums wait in LDS and y is read and written in one
 // go at its end (2e7 rows, n_instr 6,000: 1.12 ms with a load and a store of y per wave step,
@@ -779,23 +773,22 @@ template <typename VT, int MODE, bool IL, bool LDSI>
 static __global__ __launch_bounds__(kRowBlock) void k_aprod1(
     Geo g, const VT* __restrict__ tiles, const int32_t* __restrict__ star,
     const double* __restrict__ xx, const double* __restrict__ xa, double* y,
-    const double* __restrict__ b, StepArgs step,
+    const double* __restrict__ b, const LsqrState* __restrict__ st,
     double* __restrict__ partials, int tw, const int32_t* __restrict__ gate) {
     extern __shared__ double lds[];  // [n_instr] staged unknowns (LDSI), [tw][kRoundRows] sums
-    __shared__ double sh[4 * kRowWaves];  // kStepScratch for the step, then partial sums
+    __shared__ double sh[kRowWaves];
     if (gate && *gate) return;
     constexpr bool kLsqr = (MODE == A1_LSQR || MODE == A1_LSQR_T);
-    double* lxi = lds;
-    double* ubuf = lds + (LDSI ? (g.I + 1) / 2 * 2 : 0);
-    if (LDSI)
-        for (int k = threadIdx.x; k < g.I; k += kRowBlock) lxi[k] = xx[g.ins0 + k];
     double xs = 1.0, ys = 0.0;
     if (kLsqr) {
-        const LsqrState* st = block_step(step, sh);  // its barriers serve the staging too
         if (st->stop) return;
         xs = MODE == A1_LSQR ? st->sv : st->su;
         ys = MODE == A1_LSQR ? st->alpha * st->su : st->beta * st->sv;
-    } else if (LDSI) {
+    }
+    double* lxi = lds;
+    double* ubuf = lds + (LDSI ? (g.I + 1) / 2 * 2 : 0);
+    if (LDSI) {
+        for (int k = threadIdx.x; k < g.I; k += kRowBlock) lxi[k] = xx[g.ins0 + k];
         __syncthreads();
     }
     const double* __restrict__ xi = LDSI ? lxi : xx + g.ins0;
@@ -835,9 +828,8 @@ static __global__ __launch_bounds__(kRowBlock) void k_aprod1(
         __syncthreads();
     }
     if (kLsqr) {
-        __syncthreads();  // the state lay in sh
-        double sums[1] = {acc};
-        block_partials<kRowBlock, 1>(sums, sh, partials, 0);
+        const double tot = block_sum<kRowBlock>(acc, sh);
+        if (threadIdx.x == 0) partials[blockIdx.x] = tot;
     }
 }
 
@@ -952,25 +944,18 @@ static __global__ __launch_bounds__(kRowBlock) void k_aprod2_star(
 // axes, in LDS; its waves move through the die's slices in step with the die's other blocks,
 // so the u~ values they gather at any time come from one slice, which the die's L2 holds.
 // The block's sums go to part[G] (kAxes rows of lw = W + kParAxis - 1 columns), added to x by
-// k_att_reduce or taken from there by the vector step (AttSum).  Blocks from ng on add the
-// star-ordered pass's instrumental block sums to x (reduce_columns): that work waits for the same
-// kernel as this pass and fits beside it, and as a launch of its own costs 4 to 5 us.  Row k of
-// the copy (tile k / kStepRows): attT = A[row_k, 5 + 4 a + j], rowT[k] = row_k, tL[k] = att[row_k]
-// - b W; group G is rows seg[G] .. seg[G + 1] - 1.
+// k_att_reduce.  Row k of the copy (tile k / kStepRows): attT = A[row_k, 5 + 4 a + j],
+// rowT[k] = row_k, tL[k] = att[row_k] - b W; group G is rows seg[G] .. seg[G + 1] - 1.
+constexpr int kXcd = 8;  // accelerator dies; the dispatcher places block i on die i % 8
 constexpr int kBlockAtt = 512;
 constexpr int kAttChunkTiles = 2;  // wave steps per chunk (chunks dealt to the waves in turn)
 
 template <typename VT, int MODE>
 static __global__ __launch_bounds__(kBlockAtt) void k_aprod2_att(
     Geo g, const VT* __restrict__ attT, const int32_t* __restrict__ rowT,
-    const int32_t* __restrict__ tL, const int64_t* __restrict__ seg, int ng, int lw,
-    const double* __restrict__ y, double* __restrict__ part, const LsqrState* __restrict__ st,
-    ReduceArgs red) {
+    const int32_t* __restrict__ tL, const int64_t* __restrict__ seg, int lw,
+    const double* __restrict__ y, double* __restrict__ part, const LsqrState* __restrict__ st) {
     if ((MODE == A2_LSQR || MODE == A2_LSQR_T) && st->stop) return;
-    if ((int)blockIdx.x >= ng) {
-        reduce_columns<kBlockAtt>(red, blockIdx.x - ng);
-        return;
-    }
     extern __shared__ double acc[];  // [kAxes][lw]
     for (int i = threadIdx.x; i < kAxes * lw; i += blockDim.x) acc[i] = 0.0;
     __syncthreads();
@@ -1012,13 +997,25 @@ static __global__ __launch_bounds__(kBlockAtt) void k_aprod2_att(
     for (int i = threadIdx.x; i < kAxes * lw; i += blockDim.x) dst[i] = acc[i];
 }
 
-// x[att0 + a T + c] += the attitude pass's sums of column c (att_sum).
-static __global__ void k_att_reduce(Geo g, AttSum as, double* __restrict__ x) {
+// x[att0 + a T + c] += the sums of column c over the groups whose bucket covers it: bucket
+// c / W of every die and the buckets before it whose columns reach c (the previous one for
+// the first kParAxis - 1 columns of a bucket when W >= kParAxis - 1, more when W is smaller).
+// check_stop: nothing is done once the LSQR stop flag is set.
+static __global__ void k_att_reduce(Geo g, int w, int lw, const double* __restrict__ part,
+                                    double* __restrict__ x, const LsqrState* __restrict__ st,
+                                    int check_stop) {
+    if (check_stop && st->stop) return;
     const int64_t n = (int64_t)kAxes * g.T;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
-        const int64_t ax = e / g.T;
-        x[g.att0 + e] += att_sum(as, (int)ax, (int)(e - ax * g.T));
+        const int64_t ax = e / g.T, c = e - ax * g.T;
+        double sum = 0.0;
+        for (int64_t b = c / w; b >= 0 && c - b * w < lw; --b) {
+            const double* __restrict__ p = part + (b * kXcd * kAxes + ax) * lw + (c - b * w);
+#pragma unroll
+            for (int d = 0; d < kXcd; ++d) sum += p[(int64_t)d * kAxes * lw];
+        }
+        x[g.att0 + e] += sum;
     }
 }
 
