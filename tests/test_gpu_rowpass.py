@@ -48,6 +48,9 @@ CASES = {
     "reg_exchange_gaps": (GAPS * 2, 40, 10100),
     "reg_no_exchange": (LONG + [25] * 2000 + GAPS, 40, 10200),
     "reg_two_rounds": ([37] * 57000 + [3, 41], 300, 10100),
+    # so many stars that two rounds of the LDS form would be short ones: the register form with a
+    # narrow instrumental section
+    "reg_narrow": ([1] * 1000000, 50, 12),
     "wide": (LONG + [25] * 2000 + GAPS, 40, 11000),
     "beyond_lds": (LONG + [25] * 2000 + GAPS, 40, 21000),
 }
