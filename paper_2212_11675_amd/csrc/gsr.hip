@@ -1037,7 +1037,7 @@ gsr_status build_constraints(gsr_handle* h, int64_t n_con, int64_t nnz, const in
         dfree(d_misc);
         dfree(temp);
     };
-    if ((rc = dalloc(&seq, nnz)) != GSR_OK || (rc = dalloc(&perm, nnz)) != GSR_OK ||
+    if ((rc = dalloc(&seq, nnz + 1)) != GSR_OK || (rc = dalloc(&perm, nnz)) != GSR_OK ||
         (rc = dalloc(&counts, nnz + 1)) != GSR_OK || (rc = dalloc(&ksorted, nnz)) != GSR_OK ||
         (rc = dalloc(&d_misc, 2)) != GSR_OK) {
         cleanup();
@@ -1086,7 +1086,9 @@ gsr_status build_constraints(gsr_handle* h, int64_t n_con, int64_t nnz, const in
     // offsets of the column groups: exclusive scan of the counts with a zero appended
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, counts + h->ncu, (int64_t)1, 0);
     rc = dalloc(&h->cu_ptr, h->ncu + 1);
-    int32_t* offs = seq;  // seq is no longer needed: the offsets as int32 (nnz < 2^31)
+    // seq is no longer needed: the offsets as int32, ncu + 1 of them (nnz + 1 when every column
+    // is there once)
+    int32_t* offs = seq;
     if (rc == GSR_OK) {
         e = hipcub::DeviceScan::ExclusiveSum(temp, b3, counts, offs, (int)h->ncu + 1, s);
         if (e == hipSuccess) {

@@ -268,3 +268,24 @@ def test_full_size_with_frame_constraints():
         xo, _ = S.lsqr(b, itnlim=k, fixed=True)
         assert rel(host(xg), xo) <= 1e-10
     h.close()
+
+
+@pytest.mark.parametrize("nnz", [1, 1023, 1024])
+def test_constraint_columns_all_distinct(nnz):
+    """Every entry in a column of its own: as many column groups as entries, so the group offsets
+    are one more than the entries (1,024 of them fill a 4 KiB page as int32)."""
+    print(f"[con distinct] nnz={nnz}", flush=True)
+    rng = np.random.default_rng(nnz)
+    n_con = min(4, nnz)
+    con = dict(ptr=np.linspace(0, nnz, n_con + 1).astype(np.int64),
+               col=rng.permutation(FUSED.n_cols)[:nnz].astype(np.int64),
+               val=rng.standard_normal(nnz))
+    sysd, S, h, keep = setup(FUSED, con)
+    y, x0 = rng.standard_normal(S.m), rng.standard_normal(S.n)
+    xd = cuda(x0)
+    gsr.gsr_aprod2(h, cuda(y), xd)
+    assert_close_scaled(host(xd), S.aprod2(y, x0), 1e-13)
+    p = torch.empty(S.n, dtype=torch.float64, device="cuda")
+    gsr.gsr_precond(h, p)
+    np.testing.assert_allclose(host(p), S.colnorm(), rtol=1e-12, atol=0)
+    h.close()
