@@ -90,12 +90,12 @@ int grid_for(int64_t items, int per_block, int max_blocks) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(b, max_blocks));
 }
 
-// Arrays of `contiguous_from` bytes and more are asked for as physically contiguous memory
-// first, plain hipMalloc when that fails.  From 1 GiB on by default: with ordinary allocations
-// the fused row pass over tens of GB of row tiles ran up to 10% slower in a process started
-// right after another one had used and freed most of the device memory.
-hipError_t device_alloc(void** p, size_t bytes, size_t contiguous_from) {
-    if (bytes >= contiguous_from) {
+// Arrays of 1 GiB and more are asked for as physically contiguous memory first, plain
+// hipMalloc when that fails.  Measured: with ordinary allocations the fused row pass over
+// tens of GB of row tiles ran up to 10% slower in a process started right after another one
+// had used and freed most of the device memory, and at full speed with contiguous ones.
+hipError_t device_alloc(void** p, size_t bytes) {
+    if (bytes >= (size_t(1) << 30)) {
         if (hipExtMallocWithFlags(p, bytes, hipDeviceMallocContiguous) == hipSuccess)
             return hipSuccess;
         (void)hipGetLastError();
@@ -124,7 +124,6 @@ struct LsqrWork {
     int64_t rows = 0, cols = 0;
     double *u = nullptr, *v = nullptr, *w = nullptr, *z = nullptr;
     double* u2 = nullptr;   // forward recurrences: u~ alternates between u and u2
-    void *slab_u = nullptr, *slab_v = nullptr;  // allocations behind u, u2 and v, w, z, var
     double* var = nullptr;  // [cols] variance estimate (solves that return it)
     hipGraphExec_t graph = nullptr;
     int graph_iters = 0;
@@ -147,7 +146,6 @@ struct gsr_handle {
     const double* vals = nullptr;
     const int32_t *star = nullptr, *att = nullptr, *instr = nullptr;
     bool has_f32 = false;  // binary32 copies built
-    void* slab = nullptr;  // allocation behind p64, s, xt (and p32, dx)
     double *p64 = nullptr, *p32 = nullptr;
     double* s = nullptr;       // [n] aprod 2 accumulator (kept zero between uses)
     double* xt = nullptr;      // [n] operand of the next aprod 1 (p o v)
@@ -204,9 +202,9 @@ constexpr int kVecBlocksMax = 2048;
 constexpr int kGraphIters = 16;  // even: u~ is back in its first array after a graph
 
 template <typename T>
-gsr_status dalloc(T** p, size_t count, size_t contiguous_from = kContiguous) {
+gsr_status dalloc(T** p, size_t count) {
     if (count == 0) count = 1;
-    hipError_t e = device_alloc((void**)p, count * sizeof(T), contiguous_from);
+    hipError_t e = device_alloc((void**)p, count * sizeof(T));
     if (e != hipSuccess) {
         *p = nullptr;
         return fail(GSR_E_NOMEM, "hipMalloc of %zu bytes failed: %s", count * sizeof(T),
@@ -219,42 +217,25 @@ void dfree(void* p) {
     if (p) (void)hipFree(p);
 }
 
-// Vectors of n doubles each, in one allocation.  The vectors that the row pass and the attitude
-// pass gather from and scatter to (u~, s, xt) are asked for as contiguous memory from 16 MiB
-// on: those passes' times depend on how the pages lie (2e7 rows: 0.98 -> 0.93 ms and 0.51 ->
-// 0.49 ms).  Not v, w, z, which the vector step streams side by side with s, xt and p: all of
-// them contiguous, it took 114 us instead of 72.
-constexpr size_t kGathered = size_t(16) << 20;
-
-gsr_status dalloc_vecs(void** slab, std::initializer_list<double**> vecs, int64_t n,
-                       size_t contiguous_from) {
-    const size_t step = ((size_t)std::max<int64_t>(n, 1) * sizeof(double) + 255) / 256 * 256;
-    char* base = nullptr;
-    GSR_TRY(dalloc(&base, step * vecs.size(), contiguous_from));
-    *slab = base;
-    for (double** v : vecs) {
-        *v = reinterpret_cast<double*>(base);
-        base += step;
-    }
-    return GSR_OK;
-}
-
 void free_work(LsqrWork& w) {
     if (w.graph) (void)hipGraphExecDestroy(w.graph);
-    dfree(w.slab_u);
-    dfree(w.slab_v);
+    for (double* v : {w.u, w.u2, w.v, w.w, w.z, w.var}) dfree(v);
     w = LsqrWork();
 }
 
+// Allocates what the recurrence does not have yet: a call that failed half way is taken up
+// where it ended.
 gsr_status ensure_work(LsqrWork& w, int64_t rows, int64_t cols, bool with_var = false,
                        bool alternating = true) {
-    if (w.slab_v) return GSR_OK;
     w.rows = rows;
     w.cols = cols;
-    GSR_TRY(alternating ? dalloc_vecs(&w.slab_u, {&w.u, &w.u2}, rows, kGathered)
-                        : dalloc_vecs(&w.slab_u, {&w.u}, rows, kContiguous));
-    return with_var ? dalloc_vecs(&w.slab_v, {&w.v, &w.w, &w.z, &w.var}, cols, kContiguous)
-                    : dalloc_vecs(&w.slab_v, {&w.v, &w.w, &w.z}, cols, kContiguous);
+    auto need = [](double** v, int64_t n) { return *v ? GSR_OK : dalloc(v, n); };
+    GSR_TRY(need(&w.u, rows));
+    if (alternating) GSR_TRY(need(&w.u2, rows));
+    GSR_TRY(need(&w.v, cols));
+    GSR_TRY(need(&w.w, cols));
+    GSR_TRY(need(&w.z, cols));
+    return with_var ? need(&w.var, cols) : GSR_OK;
 }
 
 hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
@@ -1199,11 +1180,10 @@ gsr_status gsr_lsqr_setup(const gsr_dims* dims, const double* vals, const int32_
     // (160 KiB per compute unit)
     h->fused = g.I <= kInstrLdsMax && sizeof(double) * (2 * (size_t)g.I + 1) <= 160 * 1024;
     if (h->fused) h->row12 = plan_fused(g, n_cu);
-    gsr_status st =
-        so.build_f32
-            ? dalloc_vecs(&h->slab, {&h->p64, &h->s, &h->xt, &h->p32, &h->dx}, g.n, kGathered)
-            : dalloc_vecs(&h->slab, {&h->p64, &h->s, &h->xt}, g.n, kGathered);
-    if (st != GSR_OK) return bail(st);
+    gsr_status st;
+    if ((st = dalloc(&h->p64, g.n)) != GSR_OK) return bail(st);
+    if ((st = dalloc(&h->s, g.n)) != GSR_OK) return bail(st);
+    if ((st = dalloc(&h->xt, g.n)) != GSR_OK) return bail(st);
     if ((st = dalloc(&h->xa, (size_t)kAxes * g.T)) != GSR_OK) return bail(st);
     // one more slot than the largest grid: the constraint rows' partial sum
     const int part_len = std::max({h->dot.grid, h->Gm, h->Gn, h->row12.grid}) + 1;
@@ -1276,6 +1256,7 @@ gsr_status gsr_lsqr_setup(const gsr_dims* dims, const double* vals, const int32_
         const int64_t natt = (g.m + kStepRows - 1) / kStepRows * kTileAtt;
         h->has_f32 = true;
         if ((st = dalloc(&h->attT32, natt)) != GSR_OK) return bail(st);
+        if ((st = dalloc(&h->p32, g.n)) != GSR_OK) return bail(st);
         hipLaunchKernelGGL(k_to_f32, dim3(grid_for(natt, kBlock, 8192)), dim3(kBlock), 0, s,
                            natt, h->attT64, h->attT32);
         unsigned long long n_empty32 = 0;
@@ -1284,6 +1265,7 @@ gsr_status gsr_lsqr_setup(const gsr_dims* dims, const double* vals, const int32_
         // the precision form's workspaces, so that its stream-ordered solve allocates nothing
         if ((st = ensure_work(h->fwd32, g.m, g.n)) != GSR_OK) return bail(st);
         if ((st = dalloc(&h->r, g.m)) != GSR_OK) return bail(st);
+        if ((st = dalloc(&h->dx, g.n)) != GSR_OK) return bail(st);
         if ((st = dalloc(&h->ref_part, 2 * (size_t)h->Gn)) != GSR_OK) return bail(st);
         if ((st = dalloc(&h->ref, 1)) != GSR_OK) return bail(st);
         hipError_t e = hipHostMalloc((void**)&h->ref_host, sizeof(RefState), hipHostMallocDefault);
@@ -1302,7 +1284,11 @@ gsr_status gsr_destroy(gsr_handle* h) {
     free_work(h->fwd64v);
     free_work(h->fwd32);
     free_work(h->trans);
-    dfree(h->slab);
+    dfree(h->p64);
+    dfree(h->p32);
+    dfree(h->s);
+    dfree(h->xt);
+    dfree(h->dx);
     dfree(h->tiles64);
     dfree(h->tiles32);
     dfree(h->attT32);

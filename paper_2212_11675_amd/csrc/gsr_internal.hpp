@@ -23,7 +23,6 @@ gsr_status check_dims(const gsr_dims* d);
 Geo make_geo(const gsr_dims* d);
 int grid_for(int64_t items, int per_block, int max_blocks);
 // Device memory for the library's arrays (hipMalloc semantics; free with hipFree).
-constexpr size_t kContiguous = size_t(1) << 30;
-hipError_t device_alloc(void** p, size_t bytes, size_t contiguous_from = kContiguous);
+hipError_t device_alloc(void** p, size_t bytes);
 
 }  // namespace gsr
