@@ -583,7 +583,9 @@ static __global__ __launch_bounds__(kRowBlock) void k_aprod12_reg(RowArgs<VT> p)
     __syncthreads();
     const double* __restrict__ xi = lxi;
     const int lane = threadIdx.x % kWave, rg = lane / kQuad, q = lane % kQuad;
-    const int w = threadIdx.x / kWave;
+    // in scalar registers, and with it the bounds of the wave's rows and their shared stars: in
+    // vector registers they were spilled (12 to 28 bytes per lane)
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const double xglob = xx[g.glb0];
     const int64_t ntiles = (g.m + kStepRows - 1) / kStepRows;
     const int64_t bt = (int64_t)tw * kRowWaves, nch = (ntiles + bt - 1) / bt;
