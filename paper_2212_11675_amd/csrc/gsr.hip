@@ -1226,6 +1226,8 @@ gsr_status gsr_lsqr_setup(const gsr_dims* dims, const double* vals, const int32_
                              (flags & 4) ? " attitude start out of [0, n_dfa-4]" : "",
                              (flags & 8) ? " instrumental index out of range" : ""));
     }
+    // before the row tiles: the sort's keys and buffers (about 40 bytes a row) are freed by then
+    if ((st = build_att_order(h, s)) != GSR_OK) return bail(st);
     if (g.m > 0) {
         h->ntiles = (g.m + kStepRows - 1) / kStepRows;
         const int64_t nv = h->ntiles * kTileVals, ni = h->ntiles * kTileIdx;
@@ -1245,7 +1247,6 @@ gsr_status gsr_lsqr_setup(const gsr_dims* dims, const double* vals, const int32_
                                h->tiles32);
         }
     }
-    if ((st = build_att_order(h, s)) != GSR_OK) return bail(st);
     unsigned long long n_empty = 0;
     if ((st = colnorm<double>(h, h->attT64, h->p64, s, &n_empty)) != GSR_OK)
         return bail(st);

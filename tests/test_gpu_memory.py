@@ -1,0 +1,110 @@
+"""Systems near the limit of the device memory: what setup needs at its peak and what it can do
+without.  The rest of the memory is held by one allocation meanwhile; results are compared with
+those of a handle opened with all of it free (products to 1e-12 of the largest entry, iterates to
+1e-10: other orders of summation)."""
+import contextlib
+
+import pytest
+import torch
+
+from gpu_util import assert_close_scaled, host, rel
+from paper_2212_11675_amd import gsr
+
+pytestmark = pytest.mark.gpu
+
+MIB = 1 << 20
+
+
+def _system(stars, per, n_dfa, n_instr, seed):
+    """`stars` stars of `per` rows each, made on the GPU."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    m = stars * per
+    star = torch.arange(stars, dtype=torch.int32, device="cuda").repeat_interleave(per)
+    att = torch.randint(0, n_dfa - 3, (m,), dtype=torch.int32, device="cuda", generator=g)
+    step = n_instr // 6
+    instr = torch.randint(0, step, (m, 6), dtype=torch.int32, device="cuda", generator=g)
+    instr += step * torch.arange(6, dtype=torch.int32, device="cuda")
+    vals = torch.randn(24 * m, dtype=torch.float64, device="cuda", generator=g)
+    dims = gsr.make_dims(m, stars, n_dfa, n_instr)
+    return dims, (vals, star, att, instr.reshape(-1).contiguous())
+
+
+def _free():
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    return torch.cuda.mem_get_info()[0]
+
+
+@contextlib.contextmanager
+def _room(nbytes):
+    """All free device memory but `nbytes` held."""
+    held = torch.empty(_free() - nbytes, dtype=torch.uint8, device="cuda")
+    try:
+        yield
+    finally:
+        del held
+        torch.cuda.empty_cache()
+
+
+def _compare(h, ref, with_f32):
+    """Products, solves and the adjoint solve of two handles on the same system."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+
+    def vec(n):
+        return torch.randn(n, dtype=torch.float64, device="cuda", generator=g)
+
+    x, y = vec(h.n), vec(h.m)
+    forms = [(gsr.gsr_aprod1, gsr.gsr_aprod2)]
+    if with_f32:
+        forms.append((gsr.gsr_aprod1_f32v, gsr.gsr_aprod2_f32v))
+    for a1, a2 in forms:
+        out = []
+        for k in (h, ref):
+            ax, aty = torch.zeros_like(y), torch.zeros_like(x)
+            a1(k, x, ax)
+            a2(k, y, aty)
+            out.append((host(ax), host(aty)))
+        assert_close_scaled(out[0][0], out[1][0], 1e-12)
+        assert_close_scaled(out[0][1], out[1][1], 1e-12)
+    res, pre = [], []
+    for k in (h, ref):
+        r, p = torch.empty_like(y), torch.empty_like(x)
+        gsr.gsr_residual(k, y, x, r)
+        gsr.gsr_precond(k, p)
+        res.append(host(r))
+        pre.append(host(p))
+    assert_close_scaled(res[0], res[1], 1e-12)
+    assert_close_scaled(pre[0], pre[1], 1e-12)
+    precisions = [gsr.GSR_F64] + ([gsr.GSR_F32V] if with_f32 else [])
+    for precision in precisions:
+        o = gsr.solve_opts(itnlim=17, fixed_iters=True, precision=precision, max_refine=2)
+        xs = []
+        for k in (h, ref):
+            xk = torch.empty_like(x)
+            gsr.gsr_lsqr_solve(k, y, xk, o)
+            xs.append(host(xk))
+        assert rel(xs[0], xs[1]) <= 1e-10
+    o = gsr.solve_opts(itnlim=3, fixed_iters=True)
+    mus = []
+    for k in (h, ref):
+        mu, lam = torch.empty_like(y), torch.empty_like(x)
+        gsr.gsr_lsqr_solve_adjoint(k, x, mu, lam, o)
+        mus.append(host(mu))
+    assert rel(mus[0], mus[1]) <= 1e-10
+
+
+def test_setup_needs_no_more_than_the_handle_keeps():
+    """The sort of the attitude copy (240 MB of keys and buffers for 6e6 rows) is over before the
+    row tiles (1.3 GB) are allocated: setup fits where the finished handle does."""
+    dims, arrays = _system(300_000, 20, 3000, 1200, seed=301)
+    before = _free()
+    h = gsr.gsr_lsqr_setup(dims, *arrays, allow_empty_cols=True)
+    kept = before - _free()
+    h.close()
+    print(f"[memory] handle {kept / MIB:.0f} MiB", flush=True)
+    with _room(kept + 64 * MIB):
+        h = gsr.gsr_lsqr_setup(dims, *arrays, allow_empty_cols=True)
+    ref = gsr.gsr_lsqr_setup(dims, *arrays, allow_empty_cols=True)
+    _compare(h, ref, with_f32=False)
+    h.close()
+    ref.close()
