@@ -123,7 +123,8 @@ namespace {
 struct LsqrWork {
     int64_t rows = 0, cols = 0;
     double *u = nullptr, *v = nullptr, *w = nullptr, *z = nullptr;
-    double* u2 = nullptr;   // forward recurrences: u~ alternates between u and u2
+    double* u2 = nullptr;   // forward recurrences: u~ alternates between u and u2 (u itself
+                            // where a second vector does not fit)
     double* var = nullptr;  // [cols] variance estimate (solves that return it)
     hipGraphExec_t graph = nullptr;
     int graph_iters = 0;
@@ -219,23 +220,34 @@ void dfree(void* p) {
 
 void free_work(LsqrWork& w) {
     if (w.graph) (void)hipGraphExecDestroy(w.graph);
-    for (double* v : {w.u, w.u2, w.v, w.w, w.z, w.var}) dfree(v);
+    if (w.u2 != w.u) dfree(w.u2);
+    for (double* v : {w.u, w.v, w.w, w.z, w.var}) dfree(v);
     w = LsqrWork();
 }
 
 // Allocates what the recurrence does not have yet: a call that failed half way is taken up
 // where it ended.
-gsr_status ensure_work(LsqrWork& w, int64_t rows, int64_t cols, bool with_var = false,
-                       bool alternating = true) {
+gsr_status ensure_work(LsqrWork& w, int64_t rows, int64_t cols, bool with_var = false) {
     w.rows = rows;
     w.cols = cols;
     auto need = [](double** v, int64_t n) { return *v ? GSR_OK : dalloc(v, n); };
     GSR_TRY(need(&w.u, rows));
-    if (alternating) GSR_TRY(need(&w.u2, rows));
     GSR_TRY(need(&w.v, cols));
     GSR_TRY(need(&w.w, cols));
     GSR_TRY(need(&w.z, cols));
     return with_var ? need(&w.var, cols) : GSR_OK;
+}
+
+// The second u~ of a forward recurrence, taken last: where it does not fit, the row pass
+// rewrites u~ in place (a block has read a round's rows before it writes them; a read stream of
+// 2e7 rows' tiles with such writes takes 0.815 ms, with writes to the other array 0.75).
+void second_u(LsqrWork& w) {
+    if (w.u2) return;
+    if (dalloc(&w.u2, w.rows) != GSR_OK) {
+        w.u2 = w.u;
+        g_last_error.clear();
+        (void)hipGetLastError();
+    }
 }
 
 hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
@@ -779,6 +791,7 @@ gsr_status fwd_solve(gsr_handle* h, LsqrWork& w, const VT* attT, const double* p
                      gsr_solve_info* info, hipStream_t s, double* var_out = nullptr) {
     const Geo& g = h->g;
     GSR_TRY(ensure_work(w, h->rows(), g.n, VAR));
+    second_u(w);
     GSR_TRY(capture_graph(
         h, w,
         [&](hipStream_t cs, int it) { fwd_iteration<VT, VAR>(h, w, attT, p, cs, it); }));
@@ -918,7 +931,7 @@ gsr_status trans_solve(gsr_handle* h, const double* gvec, double* mu, const gsr_
                        gsr_solve_info* info, hipStream_t s) {
     const Geo& g = h->g;
     LsqrWork& w = h->trans;
-    GSR_TRY(ensure_work(w, g.n, h->rows(), false, false));
+    GSR_TRY(ensure_work(w, g.n, h->rows()));
     GSR_TRY(capture_graph(h, w, [&](hipStream_t cs, int) { trans_iteration(h, w, cs); }));
     // beta_1 u_1 = D g
     hipLaunchKernelGGL(k_copy_norm<true>, dim3(h->Gn), dim3(kBlock), 0, s, g.n, gvec, h->p64,
@@ -1271,7 +1284,9 @@ gsr_status gsr_lsqr_setup(const gsr_dims* dims, const double* vals, const int32_
         if ((st = dalloc(&h->ref, 1)) != GSR_OK) return bail(st);
         hipError_t e = hipHostMalloc((void**)&h->ref_host, sizeof(RefState), hipHostMallocDefault);
         if (e != hipSuccess) return bail(hip_fail(e, "hipHostMalloc"));
+        second_u(h->fwd32);
     }
+    second_u(h->fwd64);
     *out = h;
     return GSR_OK;
 }
@@ -1405,7 +1420,9 @@ gsr_status gsr_set_constraints(gsr_handle* h, int64_t n_con, const int64_t* ptr,
         h->r = nullptr;
         rc2 = dalloc(&h->r, h->rows());
         if (rc2 == GSR_OK) rc2 = ensure_work(h->fwd32, h->rows(), h->g.n);
+        if (rc2 == GSR_OK) second_u(h->fwd32);
     }
+    if (rc2 == GSR_OK) second_u(h->fwd64);
     return rc != GSR_OK ? rc : rc2;
 }
 

@@ -37,12 +37,18 @@ def _free():
 
 @contextlib.contextmanager
 def _room(nbytes):
-    """All free device memory but `nbytes` held."""
-    held = torch.empty(_free() - nbytes, dtype=torch.uint8, device="cuda")
+    """All free device memory but `nbytes` held (in a few pieces: the free memory reported grows
+    by half a GiB once most of it is taken)."""
+    held = []
+    for _ in range(4):
+        more = (_free() - nbytes) // (2 * MIB) * (2 * MIB)
+        if more > 0:
+            held.append(torch.empty(more, dtype=torch.uint8, device="cuda"))
+    print(f"[memory] room {_free() / MIB:.0f} MiB of {nbytes / MIB:.0f}", flush=True)
     try:
         yield
     finally:
-        del held
+        held.clear()
         torch.cuda.empty_cache()
 
 
@@ -106,5 +112,23 @@ def test_setup_needs_no_more_than_the_handle_keeps():
         h = gsr.gsr_lsqr_setup(dims, *arrays, allow_empty_cols=True)
     ref = gsr.gsr_lsqr_setup(dims, *arrays, allow_empty_cols=True)
     _compare(h, ref, with_f32=False)
+    h.close()
+    ref.close()
+
+
+def test_one_residual_vector_where_the_second_does_not_fit():
+    """The forward solves' second u~ is left out when the memory ends before it; the row pass then
+    works in place."""
+    dims, arrays = _system(300_000, 20, 3000, 1200, seed=302)
+    before = _free()
+    ref = gsr.gsr_lsqr_setup(dims, *arrays, allow_empty_cols=True, build_f32=True)
+    kept = before - _free()
+    ref.close()
+    one = 8 * dims.n_rows
+    print(f"[memory] handle {kept / MIB:.0f} MiB, one u~ {one / MIB:.0f}", flush=True)
+    with _room(kept - one - one // 2):  # neither the binary32 form's nor the binary64 form's
+        h = gsr.gsr_lsqr_setup(dims, *arrays, allow_empty_cols=True, build_f32=True)
+    ref = gsr.gsr_lsqr_setup(dims, *arrays, allow_empty_cols=True, build_f32=True)
+    _compare(h, ref, with_f32=True)
     h.close()
     ref.close()
