@@ -107,6 +107,43 @@ __device__ __forceinline__ void ld_tile_idx(const VT* __restrict__ tiles, int64_
     r.ib = v.y;
 }
 
+// The caller's arrays, for systems whose row tiles did not fit: lane q of a row's quad takes from
+// them what the tiles would have given it (binary32: rounded to nearest, as the tiles are).  A
+// wave load then touches sixteen pieces of 32 bytes.
+struct RowSrc {
+    const double* vals;
+    const int32_t *star, *att, *instr;
+};
+template <typename VT>
+__device__ __forceinline__ void ld_row(const RowSrc& a, int64_t row, int q, TileRow& r) {
+    const double* __restrict__ v = a.vals + row * kPar;
+    auto at = [&](int slot) { return (double)(VT)ld_val(v + slot); };
+    const int32_t* __restrict__ in = a.instr + row * kInstr;
+    r.e0 = at(tile_slot(q, 0));
+    r.e1 = at(tile_slot(q, 1));
+    r.e2 = at(tile_slot(q, 2));
+    r.as = at(tile_slot(q, 3));
+    r.z = at(tile_slot(q, 4));
+    r.wi = at(tile_slot(q, 5));
+    r.star = a.star[row];
+    r.att = a.att[row];
+    r.ia = in[q == 0 ? 3 : q - 1];
+    r.ib = in[q == 1 || q == 2 ? q + 3 : 3];
+}
+
+// A wave step's rows from the tiles, or (ROWS) from the caller's arrays; rows past m repeat the
+// last one there.
+template <bool ROWS, typename VT>
+__device__ __forceinline__ void ld_step(const VT* __restrict__ tiles, const RowSrc& src, int64_t m,
+                                        int64_t tile, int lane, TileRow& r) {
+    if (ROWS) {
+        ld_row<VT>(src, min(tile * kStepRows + lane / kQuad, m - 1), lane % kQuad, r);
+    } else {
+        ld_tile(tiles, tile, lane, r);
+        ld_tile_idx(tiles, tile, lane, r);
+    }
+}
+
 // Setup: row tiles from the paper's row layout (one thread per tile element).
 template <typename VT>
 static __global__ void k_make_tiles(int64_t m, int64_t ntiles, const double* __restrict__ vals,
@@ -771,12 +808,12 @@ static __global__ __launch_bounds__(kRowBlock) void k_aprod12_reg(RowArgs<VT> p)
 // xx, three loads per lane.  LDSI: the instrumental part of xx is staged in LDS.
 enum { A1_ADD = 0, A1_LSQR = 1, A1_LSQR_T = 2, A1_RESID = 3 };
 
-template <typename VT, int MODE, bool IL, bool LDSI>
+template <typename VT, int MODE, bool IL, bool LDSI, bool ROWS = false>
 static __global__ __launch_bounds__(kRowBlock) void k_aprod1(
     Geo g, const VT* __restrict__ tiles, const int32_t* __restrict__ star,
     const double* __restrict__ xx, const double* __restrict__ xa, double* y,
     const double* __restrict__ b, const LsqrState* __restrict__ st,
-    double* __restrict__ partials, int tw, const int32_t* __restrict__ gate) {
+    double* __restrict__ partials, int tw, const int32_t* __restrict__ gate, RowSrc src) {
     extern __shared__ double lds[];  // [n_instr] staged unknowns (LDSI), [tw][kRoundRows] sums
     __shared__ double sh[kRowWaves];
     if (gate && *gate) return;
@@ -809,8 +846,7 @@ static __global__ __launch_bounds__(kRowBlock) void k_aprod1(
         const double yo1st = r1st < R1 ? yo[r1st] : 0.0;
         for (int64_t t = ch * bt + w; t < te; t += kRowWaves) {
             TileRow a;
-            ld_tile(tiles, t, lane, a);
-            ld_tile_idx(tiles, t, lane, a);
+            ld_step<ROWS>(tiles, src, g.m, t, lane, a);
             const double sum = row_dot<IL>(g, a, q, xx, xa, xi, xglob);
             if (q == 0) ubuf[(t - ch * bt) * kStepRows + rg] = sum;
         }
@@ -859,11 +895,11 @@ __device__ __forceinline__ double contrib(double a, double yy) {
     return MODE == A2_SQ ? a * a : a * yy;
 }
 
-template <typename VT, int MODE, bool LDSI>
+template <typename VT, int MODE, bool LDSI, bool ROWS = false>
 static __global__ __launch_bounds__(kRowBlock) void k_aprod2_star(
     Geo g, const VT* __restrict__ tiles, const int32_t* __restrict__ star,
     const double* __restrict__ y, double* __restrict__ x, const LsqrState* __restrict__ st,
-    double* __restrict__ part, int tw, int nsb) {
+    double* __restrict__ part, int tw, int nsb, RowSrc src) {
     extern __shared__ double lds[];  // [n_instr + 1] sums (LDSI) or [1] global, [nsb][5] stars
     if ((MODE == A2_LSQR || MODE == A2_LSQR_T) && st->stop) return;
     const int nI = LDSI ? g.I : 0;
@@ -883,8 +919,7 @@ static __global__ __launch_bounds__(kRowBlock) void k_aprod2_star(
         const bool shf = R0 > 0 && star[R0 - 1] == S0, shl = R1 < g.m && star[R1] == S1;
         for (int64_t t = ch * bt + w; t < te; t += kRowWaves) {
             TileRow a;
-            ld_tile(tiles, t, lane, a);
-            ld_tile_idx(tiles, t, lane, a);
+            ld_step<ROWS>(tiles, src, g.m, t, lane, a);
             const int64_t r = t * kStepRows + rg;
             const double yy = (MODE == A2_SQ) ? 0.0 : y[min(r, g.m - 1)];
             if (r >= R1) continue;

@@ -132,3 +132,25 @@ def test_one_residual_vector_where_the_second_does_not_fit():
     _compare(h, ref, with_f32=True)
     h.close()
     ref.close()
+
+
+@pytest.mark.parametrize("n_instr", [11_000, 21_000])  # instrumental sums in LDS and beyond it
+def test_unfused_system_whose_row_tiles_do_not_fit(n_instr):
+    """Products and solves from the caller's arrays, binary64 and binary32, with new values too."""
+    dims, arrays = _system(300_000, 20, 3000, n_instr, seed=303)
+    before = _free()
+    ref = gsr.gsr_lsqr_setup(dims, *arrays, allow_empty_cols=True, build_f32=True)
+    kept = before - _free()
+    ref.close()
+    short = 224 * dims.n_rows + 100 * MIB  # what stays holds neither of the two tile arrays
+    print(f"[memory] handle {kept / MIB:.0f} MiB, {short / MIB:.0f} short", flush=True)
+    with _room(kept - short):
+        h = gsr.gsr_lsqr_setup(dims, *arrays, allow_empty_cols=True, build_f32=True)
+    ref = gsr.gsr_lsqr_setup(dims, *arrays, allow_empty_cols=True, build_f32=True)
+    _compare(h, ref, with_f32=True)
+    new = torch.randn_like(arrays[0])
+    for k in (h, ref):
+        gsr.gsr_update_values(k, new)
+    _compare(h, ref, with_f32=True)
+    h.close()
+    ref.close()
