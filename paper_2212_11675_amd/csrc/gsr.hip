@@ -299,8 +299,8 @@ bool good_rounds(const Geo& g, int n_cu, const RowPlan& r) {
 }
 
 // The fused pass: the LDS form where a round holds at least kRoundLds wave steps or the whole
-// system fits one round, the register form otherwise (2e7 rows, n_instr 6,000: LDS form 0.84
-// ms at 22 wave steps, 0.90 at 9, 0.95 at 8; register form 0.90).
+// system fits one round, the register form otherwise (2e7 rows, n_instr 6,000, the pass launched
+// by itself: LDS form 0.84 ms at 22 wave steps, 0.90 at 9, 0.95 at 8; register form 0.90).
 RowPlan plan_fused(const Geo& g, int n_cu) {
     RowPlan r = plan_rows(g, n_cu, 2 * (int64_t)g.I + 2, true, true);
     if (good_rounds(g, n_cu, r)) return r;

@@ -355,19 +355,22 @@ static __global__ void k_reduce_partials(int ncols, int nblocks, const double* _
 // cost as much as the stores: 0.87 -> 1.05 ms with two such stars per wave and round).
 // Two forms:
 //   k_aprod12     : u~ and the star sums in LDS, beside the block's instrumental sums and the
-//                   staged instrumental unknowns (needs room for kRoundLds wave steps: n_instr
-//                   up to about 8,900).  The block's waves take the round's wave steps in
+//                   staged instrumental unknowns (needs room for kRoundLds wave steps: with 20
+//                   rows a star n_instr up to about 8,700, with one row a star and its many
+//                   slots up to about 3,300).  The block's waves take the round's wave steps in
 //                   turn, so that the block reads one contiguous stream, and every lane adds
 //                   its products to the star's LDS slot (0.86 ms against 0.89 with a run of
 //                   steps per wave and the sums of equal stars reduced over the lanes first);
-//   k_aprod12_reg : u~ and the star sums in registers (the LDS is full at n_instr = 10,000).
-//                   Each wave takes a run of wave steps; sums of equal stars stay in registers
-//                   until the star ends (run_step).
+//   k_aprod12_reg : u~ and the star sums in registers (the LDS is full at n_instr = 10,000, or
+//                   several rounds of the LDS form would each be shorter than kRoundLds).  Each
+//                   wave takes a run of wave steps; sums of equal stars stay in registers until
+//                   the star ends (run_step).
 // Attitude operand: xa holds the attitude part of xt knot by knot (three axes of a knot
 // together), so a row's twelve elements are 96 contiguous bytes: one or two cache lines
 // instead of three to six, two loads per lane instead of three.
-// Measured, one pass: 2e7 rows, n_instr 6,000: 1.09 -> 0.84 ms (4.4 -> 5.7 TB/s of the
-// algorithmic bytes); 2.5e7 rows, n_instr 10,000: 1.35 -> 1.10 ms (register form).
+// Measured inside a solve: 2e7 rows, n_instr 6,000: 1.12 -> 0.90 to 0.98 ms from process to
+// process (4.4 -> 5.0 to 5.5 TB/s of the algorithmic bytes; 0.84 ms launched by itself);
+// register form, n_instr 10,000: 2.5e7 rows 1.39 -> 1.21 ms, 2e8 rows 9.67 -> 9.36 ms.
 //
 // TRANS: the same pass for the transposed operator D A^T (the adjoint solve), where the
 // row-space vector is v~:  v~[r] = su (A xt)[r] - beta sv v~[r]  (xt = p o u~), preceded on
