@@ -40,7 +40,10 @@ gsr_status fail(gsr_status s, const char* fmt, ...) {
     return s;
 }
 
+// The failure is reported by its status: it does not stay behind as the runtime's last error, where
+// the caller's next launch would find it.
 gsr_status hip_fail(hipError_t e, const char* what) {
+    (void)hipGetLastError();
     return fail(GSR_E_HIP, "%s: %s", what, hipGetErrorString(e));
 }
 
@@ -100,7 +103,9 @@ hipError_t device_alloc(void** p, size_t bytes) {
             return hipSuccess;
         (void)hipGetLastError();
     }
-    return hipMalloc(p, bytes);
+    const hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
 }
 
 }  // namespace gsr
@@ -246,7 +251,6 @@ void second_u(LsqrWork& w) {
     if (dalloc(&w.u2, w.rows) != GSR_OK) {
         w.u2 = w.u;
         g_last_error.clear();
-        (void)hipGetLastError();
     }
 }
 
@@ -579,7 +583,6 @@ gsr_status build_tiles(gsr_handle* h, VT** tiles, hipStream_t s) {
     if (st != GSR_OK) {
         if (h->fused) return st;
         g_last_error.clear();
-        (void)hipGetLastError();
         return GSR_OK;
     }
     const int64_t nv = h->ntiles * kTileVals, ni = h->ntiles * kTileIdx;

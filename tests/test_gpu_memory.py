@@ -154,3 +154,15 @@ def test_unfused_system_whose_row_tiles_do_not_fit(n_instr):
     _compare(h, ref, with_f32=True)
     h.close()
     ref.close()
+
+
+def test_a_failed_setup_leaves_no_error_behind():
+    """The status says that the memory ended; the runtime's last error is clear again, and the
+    caller's next launch is fine."""
+    dims, arrays = _system(300_000, 20, 3000, 1200, seed=305)
+    with _room(600 * MIB):
+        with pytest.raises(gsr.GsrError):  # in the attitude copy's arrays or its sort
+            gsr.gsr_lsqr_setup(dims, *arrays, allow_empty_cols=True)
+        assert float(torch.ones(8, device="cuda").sum()) == 8.0
+    h = gsr.gsr_lsqr_setup(dims, *arrays, allow_empty_cols=True)
+    h.close()
