@@ -1422,32 +1422,40 @@ gsr_status gsr_set_constraints(gsr_handle* h, int64_t n_con, const int64_t* ptr,
             return fail(GSR_E_UNSUPPORTED, "more than 2^31-1 constraint coefficients");
         if (ends[1] > 0 && (!col || !val)) return fail(GSR_E_INVAL, "col or val is NULL");
     }
-    // every solve's state depends on the number of rows: drop it (graphs included)
     HIP_TRY(hipStreamSynchronize(s));
     HIP_TRY(hipStreamSynchronize(h->cap));
-    free_work(h->fwd64);
-    free_work(h->fwd64v);
-    free_work(h->fwd32);
-    free_work(h->trans);
-    release_constraints(h);
-    gsr_status rc = build_constraints(h, n_con, ends[1], ptr, col, val, s);
-    if (rc != GSR_OK) release_constraints(h);
-    // the preconditioner includes the constraint rows (binary64 coefficients in both
-    // precisions); the workspaces of the stream-ordered solves are allocated again here
-    unsigned long long n_empty = 0;
-    gsr_status rc2 = colnorm<double>(h, h->attT64, h->p64, s, &n_empty);
-    if (rc2 == GSR_OK && h->has_f32)
-        rc2 = colnorm<float>(h, h->attT32, h->p32, s, &n_empty);
-    if (rc2 == GSR_OK) rc2 = ensure_work(h->fwd64, h->rows(), h->g.n);
-    if (rc2 == GSR_OK && h->has_f32) {
+    // every solve's state depends on the number of rows: drop it (graphs included)
+    auto drop = [&]() {
+        for (LsqrWork* w : {&h->fwd64, &h->fwd64v, &h->fwd32, &h->trans}) free_work(*w);
         dfree(h->r);
         h->r = nullptr;
-        rc2 = dalloc(&h->r, h->rows());
-        if (rc2 == GSR_OK) rc2 = ensure_work(h->fwd32, h->rows(), h->g.n);
-        if (rc2 == GSR_OK) second_u(h->fwd32);
+        release_constraints(h);
+    };
+    // the preconditioner includes the constraint rows (binary64 coefficients in both
+    // precisions); the workspaces of the stream-ordered solves are allocated again here
+    auto rebuild = [&]() -> gsr_status {
+        unsigned long long n_empty = 0;
+        GSR_TRY(colnorm<double>(h, h->attT64, h->p64, s, &n_empty));
+        if (h->has_f32) GSR_TRY(colnorm<float>(h, h->attT32, h->p32, s, &n_empty));
+        GSR_TRY(ensure_work(h->fwd64, h->rows(), h->g.n));
+        if (h->has_f32) {
+            GSR_TRY(dalloc(&h->r, h->rows()));
+            GSR_TRY(ensure_work(h->fwd32, h->rows(), h->g.n));
+            second_u(h->fwd32);
+        }
+        second_u(h->fwd64);
+        return GSR_OK;
+    };
+    drop();
+    gsr_status rc = build_constraints(h, n_con, ends[1], ptr, col, val, s);
+    if (rc == GSR_OK) rc = rebuild();
+    if (rc != GSR_OK) {  // the handle without constraint rows, and the first error's message
+        const std::string why = g_last_error;
+        drop();
+        (void)rebuild();
+        g_last_error = why;
     }
-    if (rc2 == GSR_OK) second_u(h->fwd64);
-    return rc != GSR_OK ? rc : rc2;
+    return rc;
 }
 
 gsr_status gsr_aprod1(gsr_handle* h, const double* x, double* y, void* stream) {
@@ -1561,6 +1569,10 @@ gsr_status gsr_lsqr_solve_async(gsr_handle* h, const double* b, double* x,
     GSR_TRY(check_opts(o));
     if (o.profile) return fail(GSR_E_INVAL, "profile needs host synchronization");
     GSR_TRY(set_device(h));
+    // complete unless an allocation failed in gsr_set_constraints (u2 comes last)
+    const LsqrWork& w = o.precision == GSR_F64 ? h->fwd64 : h->fwd32;
+    if (!w.u2 && (o.precision == GSR_F64 || h->has_f32))
+        return fail(GSR_E_NOMEM, "the solve's workspace could not be allocated");
     if (o.precision == GSR_F64) return fwd_solve_async(h, b, x, o, info_dev, as_stream(stream));
     if (!h->has_f32) return fail(GSR_E_UNSUPPORTED, "binary32 copy not built (build_f32 = 0)");
     return f32v_solve_async(h, b, x, o, info_dev, as_stream(stream));

@@ -166,3 +166,31 @@ def test_a_failed_setup_leaves_no_error_behind():
         assert float(torch.ones(8, device="cuda").sum()) == 8.0
     h = gsr.gsr_lsqr_setup(dims, *arrays, allow_empty_cols=True)
     h.close()
+
+
+def test_constraint_rows_whose_workspace_does_not_fit():
+    """After the error the handle is the one without constraint rows, its workspaces in place."""
+    dims, arrays = _system(100_000, 20, 3000, 1200, seed=304)
+    h = gsr.gsr_lsqr_setup(dims, *arrays, allow_empty_cols=True, build_f32=True)
+    ref = gsr.gsr_lsqr_setup(dims, *arrays, allow_empty_cols=True, build_f32=True)
+    n_con = 40_000_000  # rows without entries: 320 MB for their sums, as much for every u~
+    con = (torch.zeros(n_con + 1, dtype=torch.int64, device="cuda"),
+           torch.zeros(0, dtype=torch.int64, device="cuda"),
+           torch.zeros(0, dtype=torch.float64, device="cuda"))
+    with _room(400 * MIB):
+        with pytest.raises(gsr.GsrError) as e:
+            gsr.gsr_set_constraints(h, *con)
+    assert "GSR_E_NOMEM" in str(e.value)
+    assert h.m == dims.n_rows
+    _compare(h, ref, with_f32=True)
+    b = torch.randn(h.m, dtype=torch.float64, device="cuda")
+    x = torch.empty(h.n, dtype=torch.float64, device="cuda")
+    want = torch.empty_like(x)
+    buf = gsr.solve_info_buffer()
+    for precision in (gsr.GSR_F64, gsr.GSR_F32V):
+        o = gsr.solve_opts(itnlim=5, fixed_iters=True, precision=precision, max_refine=1)
+        gsr.gsr_lsqr_solve_async(h, b, x, buf, o)
+        gsr.gsr_lsqr_solve(ref, b, want, o)
+        assert rel(host(x), host(want)) <= 1e-10
+    h.close()
+    ref.close()
