@@ -235,8 +235,8 @@ gsr_status gsr_lsqr_solve_var(gsr_handle *h, const double *b, double *x, double 
  * n_refine the correction steps taken; ms_pass1 = ms_pass2 = 0 and n_pass = 0); a
  * non-finite value sets info_dev->nonfinite instead of returning GSR_E_BREAKDOWN.
  * opts->profile must be 0 (GSR_E_INVAL).  The workspaces it uses belong to the handle and
- * are allocated by gsr_lsqr_setup and gsr_set_constraints (GSR_E_NOMEM if the latter could not): calls on one handle must not overlap (nor overlap any
- * other solve on the handle).
+ * are allocated by gsr_lsqr_setup and gsr_set_constraints (GSR_E_NOMEM if the latter could
+ * not): calls on one handle must not overlap (nor overlap any other solve on the handle).
  */
 gsr_status gsr_lsqr_solve_async(gsr_handle *h, const double *b, double *x,
                                 const gsr_solve_opts *opts, gsr_solve_info *info_dev,
